@@ -91,6 +91,7 @@ void free_all(Ctx &c) {
   dfree(c.d_tps_node);
   dfree(c.d_tps_ptr);
   dfree(c.d_tps_slot);
+  dfree(c.d_tn_ptr);
   dfree(c.d_gslot);
   dfree(c.d_gx_ptr);
   dfree(c.d_gx_slot);
@@ -194,7 +195,8 @@ fnpf_status ensure32(Ctx &c) {
   HIPCHK(dalloc(&c.d_p32, c.n_v));
   HIPCHK(dalloc(&c.d_q32, c.n_v));
   HIPCHK(dalloc(&c.d_d32, c.n_v));
-  HIPCHK(dalloc(&c.d_F32, (size_t)(c.p * c.nz + 1) * std::max<int64_t>(std::max(c.n_slots, c.n_tslots), 1)));
+  HIPCHK(dalloc(&c.d_F32, std::max((size_t)(c.p * c.nz + 1) * std::max<int64_t>(c.n_slots, 1),
+                                   face_buffer_elements(c, c.n_tslots))));
   c.want32 = true;
   c.have_geom32 = false;
   return FNPF_OK;
@@ -717,7 +719,11 @@ fnpf_status fnpf_create(const fnpf_mesh_desc *m, fnpf_ctx *out) {
     UP(c.d_ps_node, c.h_ps_node.data(), c.h_ps_node.size());
     UP(c.d_ps_ptr, c.h_ps_ptr.data(), c.h_ps_ptr.size());
     UP(c.d_ps_slot, c.h_ps_slot.data(), c.h_ps_slot.size());
-    AL(c.d_F64, (size_t)(c.p * c.nz + 1) * std::max<int64_t>(std::max({c.n_slots, c.n_tslots, c.n_gslots}), 1));
+    c.lpc = owner_chunk_layers(c.n_eh, c.p, c.nz);
+    // a split that the allocation-free apply's scratch cannot hold is not made
+    if (face_buffer_elements(c, c.n_tslots) * sizeof(double) > noalloc_scratch_bytes()) c.lpc = c.nz;
+    AL(c.d_F64, std::max((size_t)(c.p * c.nz + 1) * std::max<int64_t>(std::max(c.n_slots, c.n_gslots), 1),
+                         face_buffer_elements(c, c.n_tslots)));
     if (c.dim == 3) {
       // the lists may be empty (a mesh within one tile): upload one unused entry then
       if (c.h_tps_node.empty()) c.h_tps_node.push_back(0);
@@ -727,6 +733,10 @@ fnpf_status fnpf_create(const fnpf_mesh_desc *m, fnpf_ctx *out) {
       UP(c.d_tps_node, c.h_tps_node.data(), c.h_tps_node.size());
       UP(c.d_tps_ptr, c.h_tps_ptr.data(), c.h_tps_ptr.size());
       UP(c.d_tps_slot, c.h_tps_slot.data(), c.h_tps_slot.size());
+      std::vector<int32_t> np(c.n_s + 1, 0);
+      for (int k = 0; k < c.n_tps; ++k) np[c.h_tps_node[k] + 1] = c.h_tps_ptr[k + 1] - c.h_tps_ptr[k];
+      for (int64_t n = 0; n < c.n_s; ++n) np[n + 1] += np[n];
+      UP(c.d_tn_ptr, np.data(), np.size());
       if (c.h_gx_slot.empty()) c.h_gx_slot.push_back(0);
       UP(c.d_gslot, c.h_gslot.data(), c.h_gslot.size());
       UP(c.d_gx_ptr, c.h_gx_ptr.data(), c.h_gx_ptr.size());
@@ -904,7 +914,7 @@ fnpf_status fnpf_laplace_apply_noalloc(fnpf_ctx ctx, fnpf_dtype dtype, const voi
     return fail(&c, FNPF_ERR_STATE, "no FP32 factors: call fnpf_enable_fp32, then fnpf_geom");
   // only the owner-computes schedule uses face slots; the others need no scratch
   const size_t word = dtype == FNPF_F64 ? sizeof(double) : sizeof(float);
-  const size_t need = owner_apply_active(c) ? (size_t)(c.p * c.nz + 1) * (size_t)c.n_tslots * word : 0;
+  const size_t need = owner_apply_active(c) ? face_buffer_elements(c, c.n_tslots) * word : 0;
   if (need > noalloc_scratch_bytes()) {
     char buf[200];
     std::snprintf(buf, sizeof buf,

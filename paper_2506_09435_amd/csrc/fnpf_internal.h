@@ -46,6 +46,23 @@ struct PcgScalars {
   int32_t pad;
 };
 
+// Tiles of the owner-computes apply: columns per workgroup, the plane stride of its eta-line array
+// and the entries of its LDS exchange buffer (per level), for degree p in 3D.  The exchange takes
+// at most what leaves room for four workgroups per CU in FP64 (three at degree 8) beside the line
+// arrays, so that the registers, not the 160 KB of LDS, bound the waves in flight; a strip of
+// columns needs (columns - 1) (p + 1) entries, and what does not fit goes through face slots.
+constexpr int tile_columns(int p) { return 256 / ((p + 1) * (p + 1)); }
+constexpr int eta_plane_stride(int p) {
+  const int n1 = p + 1, nh = n1 * n1, m = p >= 4 ? 64 : 16;
+  return nh + (((n1 - nh) % m) + m) % m;
+}
+constexpr int tile_exchange_entries(int p) {
+  const int n1 = p + 1, nh = n1 * n1, cpb = tile_columns(p);
+  const int lines = cpb * n1 * (nh + eta_plane_stride(p)) * 8, lds = 160 * 1024 / (p == 8 ? 3 : 4) - 64;
+  const int fit = (lds - lines) / (8 * n1), most = cpb * nh / 2;
+  return fit < most ? fit : most;
+}
+
 // Launch helpers for one colour of the column colouring.
 struct ColourRange {
   int32_t offset;
@@ -217,6 +234,8 @@ struct Ctx {
   int64_t n_tslots = 0;
   int n_tps = 0;
   int32_t *d_tslot = nullptr, *d_tps_node = nullptr, *d_tps_ptr = nullptr, *d_tps_slot = nullptr;
+  int32_t *d_tn_ptr = nullptr;            // [n_s + 1] the slots of every node in d_tps_slot
+  int lpc = 1;                            // layers per block of the owner-computes apply
   int16_t *d_xch = nullptr;
   // the geometry's face layout (k_geom, k_diag_faces): per column node its place in a level row
   // of n_gslots entries (-1 none): the owner tile's value at a node with slots at k (its position
@@ -339,9 +358,12 @@ struct Ctx {
 };
 
 // owner-computes apply (3D line schedule): active for the current settings, and its block count
-// (pass 1 + pass 2 partials of the fused dot product)
+// (pass 1, which takes the fused dot product)
 bool owner_apply_active(const Ctx &c);
 int owner_apply_blocks(const Ctx &c);
+int owner_chunk_layers(int n_eh, int p, int nz);
+// elements of a face-slot buffer of the owner-computes apply with n_slots slots per level
+size_t face_buffer_elements(const Ctx &c, int64_t n_slots);
 
 // p-multigrid (multigrid.hip)
 fnpf_status mg_build(Ctx &c);

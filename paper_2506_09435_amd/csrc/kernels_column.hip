@@ -165,6 +165,45 @@ __device__ __forceinline__ float dmat<float>(int P, int r, int c) {
   return c_D32[P * kDStride + r * (P + 1) + c];
 }
 __device__ __forceinline__ double wgt(int P, int i) { return c_W[P * kMaxN1 + i]; }
+
+// GLL nodes and weights of degree P as compile-time constants: where a loop over the nodes is
+// unrolled they become literals, so a phase does not wait for scalar loads of them.  Newton's
+// iteration on P_p' from the Chebyshev-like guesses below; Legendre's recurrence gives P_p, P_p'.
+template <int P>
+struct GllTab {
+  double x[P + 1], w[P + 1];
+  static constexpr double leg(double z, double &dp) {   // P_p(z), dp = P_p'(z), |z| < 1
+    double p0 = 1.0, p1 = z;
+    for (int n = 2; n <= P; ++n) {
+      const double p2 = ((2.0 * n - 1.0) * z * p1 - (n - 1.0) * p0) / n;
+      p0 = p1;
+      p1 = p2;
+    }
+    dp = P * (p0 - z * p1) / (1.0 - z * z);
+    return p1;
+  }
+  constexpr GllTab() : x(), w() {
+    // guesses of the positive interior nodes (cos(pi i / p), two digits are enough)
+    constexpr double guess[9][4] = {{}, {}, {0.0}, {0.45}, {0.65, 0.0}, {0.76, 0.28}, {0.83, 0.47, 0.0},
+                                    {0.87, 0.59, 0.21}, {0.90, 0.68, 0.36, 0.0}};
+    x[0] = -1.0;
+    x[P] = 1.0;
+    w[0] = w[P] = 2.0 / (P * (P + 1.0));
+    for (int k = 1; 2 * k <= P; ++k) {
+      double z = guess[P][k - 1];
+      double dp = 0.0, v = leg(z, dp);
+      if (z != 0.0)
+        for (int it = 0; it < 8; ++it) {
+          const double d2 = (2.0 * z * dp - P * (P + 1.0) * v) / (1.0 - z * z);   // P_p''(z)
+          z -= dp / d2;
+          v = leg(z, dp);
+        }
+      x[P - k] = z;
+      x[k] = -z;
+      w[k] = w[P - k] = 2.0 / (P * (P + 1.0) * v * v);
+    }
+  }
+};
 // 1/a for the Jacobi inverses: the hardware reciprocal estimate refined by two Newton steps
 // (r <- r + r (1 - a r)), within an ulp or two of the correctly rounded quotient at a fraction of
 // the IEEE division's instruction count; a is a positive diagonal entry
@@ -687,7 +726,13 @@ __global__ __launch_bounds__(256) void k_apply_fused2(const T *__restrict__ x, T
 // whose exchange entry did not fit); k_apply_faces then adds the slots to the owners.  Blocks are
 // mapped so that each XCD (blocks dispatched round-robin over 8) walks a contiguous range of
 // tiles, keeping neighbouring tiles' shared cache lines in the same L2.
-template <int P, typename T, bool MASK, bool DOT, bool OWN = false>
+// SPLIT (with OWN): a block takes one tile and a chunk of lpc layers.  The level between two chunks
+// gets a value from each: the upper chunk stores its own into y (and F) as any level, the lower one
+// apart, behind F's level rows: its tile-owned nodes in Z[chunk][n], its face slots in row
+// p nz + 1 + chunk of F.  k_apply_faces adds them.
+// What bounds it: on large meshes the barrier-separated phases, on small ones the chain of first
+// loads, which is why these are issued together.
+template <int P, typename T, bool MASK, bool DOT, bool OWN = false, bool SPLIT = false>
 __global__ __launch_bounds__(256) void k_apply_lines(const T *__restrict__ x, T *__restrict__ y,
                                                      const T *__restrict__ cg, const T *__restrict__ hmT,
                                                      int64_t hstride, const T *__restrict__ sig,
@@ -699,16 +744,16 @@ __global__ __launch_bounds__(256) void k_apply_lines(const T *__restrict__ x, T 
                                                      T *__restrict__ F = nullptr,
                                                      const int32_t *__restrict__ slot = nullptr,
                                                      int64_t n_slots = 0,
-                                                     const int16_t *__restrict__ xch = nullptr) {
+                                                     const int16_t *__restrict__ xch = nullptr, int lpc = 0) {
   using S = Sh<P, 3>;
   constexpr int N1 = S::N1, NH = S::NH, NP = S::NP, CPB = S::CPB;
-  constexpr int XM = CPB * NH / 2;   // exchange entries per tile (the host's tile_xmax)
+  constexpr GllTab<P> gll{};
+  constexpr int XM = tile_exchange_entries(P);
   // sA holds the xi-lines (planes of NH, line stride N1: lane t reads from 7t, conflict-free);
   // sB the eta-lines with the plane stride padded to SB = N1 (mod 64), so that lane t = b N1 + a
   // of the eta-line (i = a, k = b) starts at b SB + a = t (mod 64) and a wave's loads fall in
   // distinct banks (degrees < 4: N1 mod 16, to bound the LDS of their many columns per block)
-  constexpr int SBM = P >= 4 ? 64 : 16;
-  constexpr int SB = NH + (((N1 - NH) % SBM) + SBM) % SBM;
+  constexpr int SB = eta_plane_stride(P);
   constexpr int NPB = N1 * SB;
   __shared__ T sA[CPB * NP];
   __shared__ T sB[CPB * NPB];
@@ -719,31 +764,40 @@ __global__ __launch_bounds__(256) void k_apply_lines(const T *__restrict__ x, T 
   const int t = threadIdx.x - lc * NH;
   const int i = t % N1, j = t / N1;
   int blk = blockIdx.x;
+  // the layers [l0, l1) of this block: all of them, or (SPLIT) its chunk of lpc layers
+  int l0 = 0, l1 = nz, chunk = 0, nchunk = 1;
   if constexpr (OWN) {
     const int nb = gridDim.x, q = nb >> 3, r = nb & 7, xc = blk & 7;
     blk = (xc < r ? xc * (q + 1) : r * (q + 1) + (xc - r) * q) + (blk >> 3);
   }
+  if constexpr (SPLIT) {
+    nchunk = (nz + lpc - 1) / lpc;
+    chunk = blk % nchunk;
+    blk /= nchunk;
+    l0 = chunk * lpc;
+    l1 = min(l0 + lpc, nz);
+  }
+  // Every load whose address does not depend on another load is issued at once and without a
+  // branch: a block's first loads all miss the L2 caches, and one after the other they were most of
+  // the time of a small mesh's apply.  The ragged end of the last tile repeats the last column (and
+  // stores nothing).
   const int ci = blk * CPB + lc;
   const bool active = ci < ncols;
-  const int col = active ? (OWN ? ci : cols[ci]) : 0;
-  const int hn = active ? eh_nodes[(int64_t)col * NH + t] : 0;
-  const uint8_t fl = active ? flags[(int64_t)col * NH + t] : 0;
-  const int64_t ho = (int64_t)col * NH + t;
-
-  T H = T(1), Hx = T(0), hx = T(0), Hy = T(0), hy = T(0);
-  T A00 = T(1), A01 = T(0), A10 = T(0), A11 = T(1), dJ = T(1);
-  if (active) {
-    H = cg[0 * hstride + ho];
-    Hx = cg[1 * hstride + ho];
-    hx = cg[2 * hstride + ho];
-    Hy = cg[3 * hstride + ho];
-    hy = cg[4 * hstride + ho];
-    A00 = hmT[0 * hstride + ho];
-    A01 = hmT[1 * hstride + ho];
-    A10 = hmT[2 * hstride + ho];
-    A11 = hmT[3 * hstride + ho];
-    dJ = hmT[4 * hstride + ho];
+  const int cc = min(ci, ncols - 1);
+  const int col = OWN ? cc : cols[cc];
+  const uint32_t ho = (uint32_t)col * NH + t;   // < 2^31: the face-slot counts are checked at set-up
+  const int hn = eh_nodes[ho];
+  const uint8_t fl0_ = flags[ho];
+  int32_t sl0 = -1;
+  int2 xx = make_int2(-1, -1);
+  if constexpr (OWN) {
+    sl0 = slot[ho];
+    xx = reinterpret_cast<const int2 *>(xch)[ho];
   }
+  const T H = cg[ho], Hx = cg[hstride + ho], hx = cg[2 * hstride + ho];
+  const T Hy = cg[3 * hstride + ho], hy = cg[4 * hstride + ho];
+  const T A00 = hmT[ho], A01 = hmT[hstride + ho], A10 = hmT[2 * hstride + ho], A11 = hmT[3 * hstride + ho];
+  const T dJ = hmT[4 * hstride + ho];
   const T wdJ = (T)(wgt(P, i) * wgt(P, j)) * dJ;
 
   T *Ab = sA + lc * NP;
@@ -757,36 +811,39 @@ __global__ __launch_bounds__(256) void k_apply_lines(const T *__restrict__ x, T 
   const __amdgpu_buffer_rsrc_t rx = vec_rsrc(x, nbytes), ry = vec_rsrc(y, nbytes);
   const uint32_t hb = (uint32_t)hn * (uint32_t)sizeof(T);
   const uint32_t rowb = (uint32_t)n_s * (uint32_t)sizeof(T);
-  // face slots (OWN): [p nz + 1][n_slots]
-  __amdgpu_buffer_rsrc_t rf = ry;
-  uint32_t fb = 0, rowf = 0, fbytes = 0;
+  // face slots (OWN): [p nz + 1 + nchunk - 1][n_slots], then the chunk tops [nchunk - 1][n_s]
+  uint32_t fb = 0, rowf = 0, fbytes = 0, ztop = 0;
   bool has_slot = false;
   int xw = -1, xr0 = -1, xr1 = -1, xr2 = -1;
   if constexpr (OWN) {
-    fbytes = (uint32_t)((int64_t)(P * nz + 1) * n_slots * (int64_t)sizeof(T));
-    rf = vec_rsrc(F, fbytes);
-    const int32_t sl = active ? slot[ho] : -1;
-    has_slot = sl >= 0;
-    fb = (uint32_t)(sl < 0 ? 0 : sl) * (uint32_t)sizeof(T);
+    const int64_t slot_rows = (int64_t)(P * nz + nchunk) * n_slots;
+    fbytes = (uint32_t)((slot_rows + (int64_t)(nchunk - 1) * n_s) * (int64_t)sizeof(T));
+    ztop = (uint32_t)((slot_rows + (int64_t)chunk * n_s) * (int64_t)sizeof(T));
     rowf = (uint32_t)n_slots * (uint32_t)sizeof(T);
-    if (active) {
-      xw = xch[ho * 4];
-      xr0 = xch[ho * 4 + 1];
-      xr1 = xch[ho * 4 + 2];
-      xr2 = xch[ho * 4 + 3];
-    }
   }
 
   T ucol[N1];
   T carry = T(0);
   double dot = 0.0;
-  ucol[0] = active ? buf_ld<T>(rx, hb, 0) : T(0);
+  ucol[0] = buf_ld<T>(rx, hb, (uint32_t)(l0 * P) * rowb);
   const int vtop = P * nz;
   T nxt[N1];
 #pragma unroll
-  for (int k = 1; k < N1; ++k) nxt[k] = active ? buf_ld<T>(rx, hb, (uint32_t)k * rowb) : T(0);
+  for (int k = 1; k < N1; ++k) nxt[k] = buf_ld<T>(rx, hb, (uint32_t)(l0 * P + k) * rowb);
+  const uint8_t fl = active ? fl0_ : 0;
+  if constexpr (OWN) {
+    const int32_t sl = active ? sl0 : -1;
+    has_slot = sl >= 0;
+    fb = (uint32_t)(sl < 0 ? 0 : sl) * (uint32_t)sizeof(T);
+    if (active) {
+      xw = (int16_t)(xx.x & 0xffff);
+      xr0 = xx.x >> 16;
+      xr1 = (int16_t)(xx.y & 0xffff);
+      xr2 = xx.y >> 16;
+    }
+  }
 
-  for (int l = 0; l < nz; ++l) {
+  for (int l = l0; l < l1; ++l) {
     // FP64 up to degree 7: the row strides pass through an opaque copy per layer, so that the
     // level offsets below are formed by scalar arithmetic where they are used (kept live across
     // the loop, one per level, they spilled from scalar to vector registers; FP32 has the scalar
@@ -807,11 +864,14 @@ __global__ __launch_bounds__(256) void k_apply_lines(const T *__restrict__ x, T 
     line_eo<P, T>(ucol, uz, E0);
     __syncthreads();
     // next layer's x loads complete behind this layer's arithmetic
-    if (l + 1 < nz) {
+    if (l + 1 < l1) {
 #pragma unroll
-      for (int k = 1; k < N1; ++k) nxt[k] = active ? buf_ld<T>(rx, hb, (uint32_t)((l + 1) * P + k) * rb) : T(0);
+      for (int k = 1; k < N1; ++k) nxt[k] = buf_ld<T>(rx, hb, (uint32_t)((l + 1) * P + k) * rb);
     }
 
+    // the layer's scalars, loaded ahead of the barrier before their use: half its thickness and its
+    // middle in sigma
+    const T hds = half_ds[l], smid = (T)0.5 * (sig[l * P] + sig[l * P + P]);
     // phase 1 (in place: each line is read and written by its one thread)
     {
       T in[N1], out[N1];
@@ -829,23 +889,25 @@ __global__ __launch_bounds__(256) void k_apply_lines(const T *__restrict__ x, T 
     __syncthreads();
 
     // phase 2
-    const T zz = half_ds[l] * H;
+    const T zz = hds * H;
     const T izz = T(1) / zz;
     const T fl0 = wdJ * zz;
     // the horizontal part of J^-T grad u picks up b2 = -(J_h^-T grad z) / z_zeta, and
-    // grad z = sigma grad H - grad h is linear in sigma along the line: b2 = sigma a + b
-    const T ax = -(Hx * A00 + Hy * A10) * izz, bx = (hx * A00 + hy * A10) * izz;
-    const T ay = -(Hx * A01 + Hy * A11) * izz, by = (hx * A01 + hy * A11) * izz;
+    // grad z = sigma grad H - grad h is linear in sigma along the line, and sigma in the layer's
+    // reference coordinate: sigma = smid + hds x_k, b2 = x_k a + b
+    const T izd = izz * hds;
+    const T ax0 = -(Hx * A00 + Hy * A10), ay0 = -(Hx * A01 + Hy * A11);
+    const T ax = ax0 * izd, bx = (ax0 * smid + (hx * A00 + hy * A10)) * izz;
+    const T ay = ay0 * izd, by = (ay0 * smid + (hx * A01 + hy * A11)) * izz;
     const T izz2 = izz * izz;
     T vz[N1], yz[N1];
 #pragma unroll
     for (int k = 0; k < N1; ++k) {
       const int q = k * NH + t, qb = k * SB + t;
       const T ux = Ab[q], uy = Bb[qb];
-      const T sg = sig[l * P + k];
-      const T f = (T)wgt(P, k) * fl0;
-      const T b2x = sg * ax + bx;
-      const T b2y = sg * ay + by;
+      const T f = (T)gll.w[k] * fl0;
+      const T b2x = (T)gll.x[k] * ax + bx;
+      const T b2y = (T)gll.x[k] * ay + by;
       const T gx = A00 * ux + A10 * uy + b2x * uz[k];
       const T gy = A01 * ux + A11 * uy + b2y * uz[k];
       Ab[q] = f * (A00 * gx + A01 * gy);
@@ -871,7 +933,7 @@ __global__ __launch_bounds__(256) void k_apply_lines(const T *__restrict__ x, T 
       for (int r = 0; r < N1; ++r) Bb[eta_base + r * N1] = out[r];
     }
     // read-add-write loads of the colour schedule, in flight across the barrier
-    const int kend = (l == nz - 1) ? N1 : P;
+    const int kend = (l == l1 - 1) ? N1 : P;
     T old[N1];
 #pragma unroll
     for (int k = 0; k < N1; ++k) old[k] = T(0);
@@ -886,6 +948,11 @@ __global__ __launch_bounds__(256) void k_apply_lines(const T *__restrict__ x, T 
     T yv[N1];
 #pragma unroll
     for (int k = 0; k < N1; ++k) yv[k] = yz[k] + (Ab[k * NH + t] + Bb[k * SB + t]);
+    if constexpr (OWN && DOT) {
+      // x.Ax is the sum of the columns' own contributions: it needs no assembled value
+#pragma unroll
+      for (int k = 0; k < N1; ++k) dot += (double)ucol[k] * (double)yv[k];
+    }
     yv[0] += carry;
     carry = yv[P];
     if constexpr (OWN) {
@@ -919,12 +986,15 @@ __global__ __launch_bounds__(256) void k_apply_lines(const T *__restrict__ x, T 
         for (int k = 0; k < N1; ++k) {
           if (k < kend) {
             const int v = l * P + k;
+            const bool below = SPLIT && k == P && l1 < nz;   // the next chunk's bottom level: apart from it
             if (fl & kTOwn) {
               const T val = (MASK && v == vtop) ? T(0) : yv[k];
-              buf_st(val, rys, hb, (uint32_t)v * rb);
-              if (DOT && !(fl & kTShared)) dot += (double)ucol[k] * (double)val;
+              if (below)
+                buf_st(val, rfo, hb, ztop);
+              else
+                buf_st(val, rys, hb, (uint32_t)v * rb);
             } else if (!(MASK && v == vtop)) {
-              buf_st(yv[k], rfo, fb, (uint32_t)v * rfs);
+              buf_st(yv[k], rfo, fb, (below ? (uint32_t)(P * nz + 1 + chunk) : (uint32_t)v) * rfs);
             }
           }
         }
@@ -943,31 +1013,42 @@ __global__ __launch_bounds__(256) void k_apply_lines(const T *__restrict__ x, T 
     ucol[0] = ucol[P];
   }
   if constexpr (DOT) {
+    if (!active) dot = 0.0;
     double s = block_sum<CPB * NH>(dot);
     if (threadIdx.x == 0) partial[blockIdx.x] = s;
   }
 }
 
-// Second pass of the owner-computes apply: y[v][n] += sum of the face slots of the other
-// columns at shared node n (slots in increasing column order), for every node level v; the
-// dot-product contribution x.y of the shared nodes is taken here.  A thread takes one shared
-// node and a chunk of kFaceLevels levels, with all its loads issued before the sums.  Blocks
-// are remapped so that each XCD walks a contiguous range of nodes of one level chunk (the slots
-// of neighbouring columns then meet in the same L2).
+// Second pass of the owner-computes apply: y[v][n] += the face slots of the other tiles at node n
+// (in increasing slot order), for every node level v; with the layers split into chunks of lpc,
+// also the lower chunk's value Z at the chunk interfaces, and its face slots (rows nlev.. of F).
+// Blocks below nba: a thread takes one node with slots and a chunk of kFaceLevels levels, with all
+// its loads issued before the sums, and each XCD walks a contiguous range of nodes of one level
+// chunk (the slots of neighbouring tiles then meet in the same L2).  The other blocks: one chunk
+// interface each, the nodes without slots.
 constexpr int kFaceLevels = 8;
 
-template <typename T, bool MASK, bool DOT>
-__global__ __launch_bounds__(256) void k_apply_faces(const T *__restrict__ x, T *__restrict__ y,
-                                                     const T *__restrict__ F, const int32_t *__restrict__ ps_node,
+template <typename T, bool MASK>
+__global__ __launch_bounds__(256) void k_apply_faces(T *__restrict__ y, const T *__restrict__ F,
+                                                     const int32_t *__restrict__ ps_node,
                                                      const int32_t *__restrict__ ps_ptr,
                                                      const int32_t *__restrict__ ps_slot, int n_ps, int nlev,
-                                                     int64_t n_s, int64_t n_slots, double *__restrict__ partial,
+                                                     int64_t n_s, int64_t n_slots, int nba,
+                                                     const int32_t *__restrict__ node_ptr, int clev, int nchunk,
                                                      const int32_t *__restrict__ skip) {
   if (skip != nullptr && *skip) return;
   constexpr int LC = kFaceLevels;
+  const T *Z = F + (int64_t)(nlev + nchunk - 1) * n_slots;
+  if ((int)blockIdx.x >= nba) {
+    const int nbx = (int)((n_s + 255) >> 8);
+    const int c = ((int)blockIdx.x - nba) / nbx;
+    const int64_t n = (int64_t)(((int)blockIdx.x - nba) - c * nbx) * 256 + threadIdx.x;
+    if (n < n_s && node_ptr[n] == node_ptr[n + 1]) y[(int64_t)(c + 1) * clev * n_s + n] += Z[c * n_s + n];
+    return;
+  }
   int blk = blockIdx.x;
   {
-    const int nb = gridDim.x, q = nb >> 3, r = nb & 7, xc = blk & 7;
+    const int q = nba >> 3, r = nba & 7, xc = blk & 7;
     blk = (xc < r ? xc * (q + 1) : r * (q + 1) + (xc - r) * q) + (blk >> 3);
   }
   const int nbx = (n_ps + 255) >> 8;
@@ -975,38 +1056,33 @@ __global__ __launch_bounds__(256) void k_apply_faces(const T *__restrict__ x, T 
   const int k = (blk - chunk * nbx) * 256 + threadIdx.x;
   const int v0 = chunk * LC;
   const int vend = MASK ? nlev - 1 : nlev;   // the masked top level stays 0
-  double dot = 0.0;
-  if (k < n_ps) {
-    const int64_t n = ps_node[k];
-    const int a = ps_ptr[k], b = ps_ptr[k + 1];
-    T acc[LC];
+  if (k >= n_ps) return;
+  const int64_t n = ps_node[k];
+  const int a = ps_ptr[k], b = ps_ptr[k + 1];
+  T acc[LC];
 #pragma unroll
-    for (int u = 0; u < LC; ++u) acc[u] = (v0 + u < vend) ? y[(v0 + u) * n_s + n] : T(0);
-    for (int q = a; q < b; ++q) {
-      const int64_t sl = ps_slot[q];
-      T f[LC];
+  for (int u = 0; u < LC; ++u) acc[u] = (v0 + u < vend) ? y[(v0 + u) * n_s + n] : T(0);
+  for (int q = a; q < b; ++q) {
+    const int64_t sl = ps_slot[q];
+    T f[LC];
 #pragma unroll
-      for (int u = 0; u < LC; ++u) f[u] = (v0 + u < vend) ? F[(v0 + u) * n_slots + sl] : T(0);
+    for (int u = 0; u < LC; ++u) f[u] = (v0 + u < vend) ? F[(v0 + u) * n_slots + sl] : T(0);
 #pragma unroll
-      for (int u = 0; u < LC; ++u) acc[u] += f[u];
-    }
-    T xv[LC];
-    if constexpr (DOT) {
-#pragma unroll
-      for (int u = 0; u < LC; ++u) xv[u] = (v0 + u < vend) ? x[(v0 + u) * n_s + n] : T(0);
-    }
+    for (int u = 0; u < LC; ++u) acc[u] += f[u];
+  }
+  if (nchunk > 1) {
 #pragma unroll
     for (int u = 0; u < LC; ++u) {
-      if (v0 + u < vend) {
-        y[(v0 + u) * n_s + n] = acc[u];
-        if (DOT) dot += (double)xv[u] * (double)acc[u];
+      const int v = v0 + u, c = v / clev - 1;
+      if (v > 0 && v < nlev - 1 && v == (c + 1) * clev) {
+        acc[u] += Z[c * n_s + n];
+        for (int q = a; q < b; ++q) acc[u] += F[(nlev + c) * n_slots + ps_slot[q]];
       }
     }
   }
-  if constexpr (DOT) {
-    double s = block_sum<256>(dot);
-    if (threadIdx.x == 0) partial[blockIdx.x] = s;
-  }
+#pragma unroll
+  for (int u = 0; u < LC; ++u)
+    if (v0 + u < vend) y[(v0 + u) * n_s + n] = acc[u];
 }
 
 bool owner_apply_active(const Ctx &c) {
@@ -1015,44 +1091,59 @@ bool owner_apply_active(const Ctx &c) {
   return c.n_v * 8 < lim && (int64_t)(c.p * c.nz + 1) * std::max(c.n_slots, c.n_tslots) * 8 < lim;
 }
 
+// Layers per block of the owner-computes apply.  A block walks its layers one after the other, so a
+// mesh with too few tiles to fill the chip splits its layers over several blocks, at the price of
+// one more value per node at every chunk interface.  The line: as many chunks as still leave all
+// blocks resident at once (four per CU on 256 CUs); from 513 tiles on the layers stay together.
+// FP64 apply of the periodic wave (40 x 40 x 4, p = 5; 229 tiles): 1, 2 and 4 chunks 20.4, 17.9 and
+// 17.9 us; Jacobi CG on the bar (64 x 16 x 4, p = 5; 147 tiles), 5,775 iterations: 207, 195, 191 ms.
+constexpr int kResidentBlocks = 4 * 256;
+int owner_chunk_layers(int n_eh, int p, int nz) {
+  const int cpb = tile_columns(p), tiles = (n_eh + cpb - 1) / cpb;
+  const int nchunk = std::min(nz, std::max(1, kResidentBlocks / tiles));
+  return (nz + nchunk - 1) / nchunk;
+}
+static int owner_chunks(const Ctx &c) { return (c.nz + c.lpc - 1) / c.lpc; }
+
+size_t face_buffer_elements(const Ctx &c, int64_t n_slots) {
+  const int nc = c.dim == 3 ? owner_chunks(c) : 1;
+  return (size_t)((c.p * c.nz + nc) * n_slots + (nc - 1) * c.n_s);
+}
+
 // blocks of a face pass over n nodes with face slots
 static int face_blocks_n(const Ctx &c, int n) {
   return ((n + 255) / 256) * ((c.p * c.nz + 1 + kFaceLevels - 1) / kFaceLevels);
 }
-static int face_blocks(const Ctx &c) { return face_blocks_n(c, c.n_ps); }
 
-// the face pass alone (k_apply_faces without the dot product): y at the shared nodes += the face
-// slots of the context's F buffer of y's precision
-hipError_t launch_faces(Ctx &c, fnpf_dtype dt, void *y, bool mask, hipStream_t s, const int32_t *skip) {
-  if (c.n_ps == 0) return hipSuccess;
-  const int nb = face_blocks(c);
-  const int nlev = c.p * c.nz + 1;
-  if (dt == FNPF_F64) {
-    if (mask)
-      k_apply_faces<double, true, false><<<nb, 256, 0, s>>>(nullptr, (double *)y, c.d_F64, c.d_ps_node, c.d_ps_ptr,
-                                                            c.d_ps_slot, c.n_ps, nlev, c.n_s, c.n_slots, nullptr,
-                                                            skip);
-    else
-      k_apply_faces<double, false, false><<<nb, 256, 0, s>>>(nullptr, (double *)y, c.d_F64, c.d_ps_node,
-                                                             c.d_ps_ptr, c.d_ps_slot, c.n_ps, nlev, c.n_s,
-                                                             c.n_slots, nullptr, skip);
-  } else {
-    if (mask)
-      k_apply_faces<float, true, false><<<nb, 256, 0, s>>>(nullptr, (float *)y, c.d_F32, c.d_ps_node, c.d_ps_ptr,
-                                                           c.d_ps_slot, c.n_ps, nlev, c.n_s, c.n_slots, nullptr,
-                                                           skip);
-    else
-      k_apply_faces<float, false, false><<<nb, 256, 0, s>>>(nullptr, (float *)y, c.d_F32, c.d_ps_node, c.d_ps_ptr,
-                                                            c.d_ps_slot, c.n_ps, nlev, c.n_s, c.n_slots, nullptr,
-                                                            skip);
-  }
+// y at the nodes with face slots += the slots of F, over all levels (mask: but the top one)
+template <typename T>
+static hipError_t faces_impl(Ctx &c, T *y, const T *F, bool mask, const int32_t *node, const int32_t *ptr,
+                             const int32_t *slot, int n, int64_t n_slots, const int32_t *node_ptr, int nchunk,
+                             const int32_t *skip, hipStream_t s) {
+  const int nba = face_blocks_n(c, n);
+  const int nb = nba + (nchunk - 1) * (int)((c.n_s + 255) / 256);
+  if (nb == 0) return hipSuccess;
+  auto kern = mask ? k_apply_faces<T, true> : k_apply_faces<T, false>;
+  kern<<<nb, 256, 0, s>>>(y, F, node, ptr, slot, n, c.p * c.nz + 1, c.n_s, n_slots, nba, node_ptr, c.lpc * c.p,
+                          nchunk, skip);
   return hipGetLastError();
 }
 
+// the face pass of the restriction: y at the shared nodes += the per-column face slots of the
+// context's F buffer of y's precision
+hipError_t launch_faces(Ctx &c, fnpf_dtype dt, void *y, bool mask, hipStream_t s, const int32_t *skip) {
+  if (dt == FNPF_F64)
+    return faces_impl<double>(c, (double *)y, c.d_F64, mask, c.d_ps_node, c.d_ps_ptr, c.d_ps_slot, c.n_ps, c.n_slots,
+                              nullptr, 1, skip, s);
+  return faces_impl<float>(c, (float *)y, c.d_F32, mask, c.d_ps_node, c.d_ps_ptr, c.d_ps_slot, c.n_ps, c.n_slots,
+                           nullptr, 1, skip, s);
+}
+
+// blocks of pass 1 (one partial each of the fused dot product)
 int owner_apply_blocks(const Ctx &c) {
   if (c.dim != 3) return 0;
-  const int cpb = 256 / c.nh;
-  return (c.n_eh + cpb - 1) / cpb + face_blocks_n(c, c.n_tps);
+  const int cpb = tile_columns(c.p);
+  return (c.n_eh + cpb - 1) / cpb * owner_chunks(c);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1085,7 +1176,7 @@ __global__ __launch_bounds__(256) void k_geom(const double *__restrict__ eta, co
                                               const int16_t *__restrict__ xch = nullptr, int full_diag = 1) {
   using S = Sh<P, DIM>;
   constexpr int N1 = S::N1, NH = S::NH, NP = S::NP, NG = S::NG, CPB = S::CPB;
-  constexpr int XM = CPB * NH / 2;   // exchange entries per tile (the host's tile_xmax)
+  constexpr int XM = DIM == 3 ? tile_exchange_entries(P) : 1;
   // The diagonal at node (i, j, k) of an element, collocated quadrature:
   //   sum_m D[m][i]^2 G_xx(m, j, k) + sum_m D[m][j]^2 G_yy(i, m, k) + sum_m D[m][k]^2 G_zz(i, j, m)
   //   + 2 (D_ii D_jj G_xy + D_ii D_kk G_xz + D_jj D_kk G_yz)(i, j, k).
@@ -1096,8 +1187,7 @@ __global__ __launch_bounds__(256) void k_geom(const double *__restrict__ eta, co
   constexpr int NX0 = 2 * CPB * NH, NX1 = OWN ? N1 * XM : 0;
   // sB's plane stride padded as the apply's eta-line array: SB = N1 (mod 64), so the 64 lanes of
   // a wave reading their eta-lines start in distinct banks (degrees < 4: N1 mod 16)
-  constexpr int SBM = P >= 4 ? 64 : 16;
-  constexpr int SB = DIM == 3 ? NH + (((N1 - NH) % SBM) + SBM) % SBM : NH;
+  constexpr int SB = DIM == 3 ? eta_plane_stride(P) : NH;
   __shared__ double sA[CPB * NP];
   __shared__ double sB[DIM == 3 ? CPB * N1 * SB : 1];
   __shared__ double sX[NX0 > NX1 ? NX0 : NX1];
@@ -1863,15 +1953,13 @@ static hipError_t apply_impl(Ctx &c, const T *x, T *y, const T *G, double *parti
           if (F == nullptr) {
             if constexpr (sizeof(T) == 8) F = (T *)c.d_F64; else F = (T *)c.d_F32;
           }
-          const int nb1 = (c.n_eh + S::CPB - 1) / S::CPB;
-          k_apply_lines<P, T, MASK, DOT, true><<<nb1, S::NT, 0, s>>>(
+          auto kern = owner_chunks(c) > 1 ? k_apply_lines<P, T, MASK, DOT, true, true>
+                                          : k_apply_lines<P, T, MASK, DOT, true, false>;
+          kern<<<owner_apply_blocks(c), S::NT, 0, s>>>(
               x, y, cg, hmT, hs, sig, hds, c.d_eh_nodes, c.d_flags, nullptr, c.n_eh, c.nz, c.n_s,
-              DOT ? partial : nullptr, skip, F, c.d_tslot, c.n_tslots, c.d_xch);
-          if (c.n_tps > 0)
-            k_apply_faces<T, MASK, DOT><<<face_blocks_n(c, c.n_tps), 256, 0, s>>>(
-                x, y, F, c.d_tps_node, c.d_tps_ptr, c.d_tps_slot, c.n_tps, c.p * c.nz + 1, c.n_s, c.n_tslots,
-                DOT ? partial + nb1 : nullptr, skip);
-          return hipGetLastError();
+              DOT ? partial : nullptr, skip, F, c.d_tslot, c.n_tslots, c.d_xch, c.lpc);
+          return faces_impl<T>(c, y, F, MASK, c.d_tps_node, c.d_tps_ptr, c.d_tps_slot, c.n_tps, c.n_tslots,
+                               c.d_tn_ptr, owner_chunks(c), skip, s);
         }
         if (c.apply_lines && (int64_t)c.n_v * (int64_t)sizeof(T) < (int64_t(1) << 32)) {
           k_apply_lines<P, T, MASK, DOT><<<nb, S::NT, 0, s>>>(x, y, cg, hmT, hs, sig, hds, c.d_eh_nodes, c.d_flags,

@@ -411,9 +411,9 @@ std::string build_host_mesh(const fnpf_mesh_desc &m, Ctx &c, std::vector<double>
     // owns the node and writes the tile's sum to a face slot elsewhere; the face pass adds the
     // slots of a node (in increasing slot order) to the owner's value.
     if (dim == 3) {
-      const int tc = 256 / nh;
+      const int tc = tile_columns(p);
       c.tile_cols = tc;
-      c.tile_xmax = tc * nh / 2;
+      c.tile_xmax = tile_exchange_entries(p);
       c.h_tslot.assign(n_eh * nh, -1);
       c.h_xch.assign(n_eh * nh * 4, (int16_t)-1);
       std::vector<std::vector<int32_t>> node_slots;        // per node with slots: its slots
