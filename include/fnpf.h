@@ -220,8 +220,9 @@ fnpf_status fnpf_surface_interp_weights(fnpf_ctx ctx, int32_t n_pts, const doubl
  *     face slots, (p*nz+1) * n_slots * 8 bytes, reach 4 GiB (n_v >= 2^29,
  *     about 537 million nodes) the apply falls back to the colour assembly
  *     of 6 while n_v * sizeof(element) stays below 4 GiB, else to that of
- *     7; the result is the same.  2D: colour schedule with read-add-write
- *     of shared nodes;
+ *     7; the result is the same.  Small meshes split the layers over several
+ *     workgroups.  2D: the same assembly column by column (the schedule of
+ *     7 when the face slots exceed 128 MiB);
  *   1 stored factors: fnpf_geom stores G (6 or 3 per point, FP64 and FP32)
  *     and the apply streams it from HBM;
  *   6 fused geometry, line schedule with colour assembly (3D): in the
@@ -264,13 +265,13 @@ fnpf_status fnpf_laplace_apply(fnpf_ctx ctx, fnpf_dtype dtype, const void *x, vo
 /* Allocation-free variant of fnpf_laplace_apply, for callers that cannot allocate device memory
  * during the call: code under HIP graph capture, tight serving loops, harnesses that forbid
  * hipMalloc.  Same arguments, operator and result as fnpf_laplace_apply (bitwise identical).
- * The owner-computes schedule's face slots, which fnpf_laplace_apply keeps in the context,
+ * The owner-computes assembly's face slots, which fnpf_laplace_apply keeps in the context,
  * live here in one library-wide device array of 128 MiB per GPU (allocated when the library's
  * device code is loaded, held until the process ends); the call allocates nothing.  Every call
  * on a GPU uses that GPU's one array: calls that overlap on a GPU (other streams, other
  * contexts, other host threads) race and must be serialised by the caller.  The slots are
  * written before they are read within each call, so nothing carries over between calls.
- * Errors: ARG when the face slots, (p nz + 1) * n_tile_slots elements of the dtype, exceed the
+ * Errors: ARG when the face slots, at least (p nz + 1) * n_tile_slots elements of the dtype, exceed the
  * array (then use fnpf_laplace_apply); as fnpf_laplace_apply otherwise. */
 fnpf_status fnpf_laplace_apply_noalloc(fnpf_ctx ctx, fnpf_dtype dtype, const void *x, void *y,
                                        int32_t mask_dirichlet, void *stream);

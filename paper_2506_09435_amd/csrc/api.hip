@@ -81,9 +81,8 @@ void free_all(Ctx &c) {
   dfree(c.d_eh_nodes);
   dfree(c.d_cols);
   dfree(c.d_slot);
-  dfree(c.d_ps_node);
-  dfree(c.d_ps_ptr);
-  dfree(c.d_ps_slot);
+  dfree(c.d_p_slots);
+  dfree(c.d_p_lists);
   dfree(c.d_F64);
   dfree(c.d_F32);
   dfree(c.d_tslot);
@@ -91,7 +90,8 @@ void free_all(Ctx &c) {
   dfree(c.d_tps_node);
   dfree(c.d_tps_ptr);
   dfree(c.d_tps_slot);
-  dfree(c.d_tn_ptr);
+  dfree(c.d_t_slots);
+  dfree(c.d_t_lists);
   dfree(c.d_gslot);
   dfree(c.d_gx_ptr);
   dfree(c.d_gx_slot);
@@ -195,8 +195,7 @@ fnpf_status ensure32(Ctx &c) {
   HIPCHK(dalloc(&c.d_p32, c.n_v));
   HIPCHK(dalloc(&c.d_q32, c.n_v));
   HIPCHK(dalloc(&c.d_d32, c.n_v));
-  HIPCHK(dalloc(&c.d_F32, std::max((size_t)(c.p * c.nz + 1) * std::max<int64_t>(c.n_slots, 1),
-                                   face_buffer_elements(c, c.n_tslots))));
+  HIPCHK(dalloc(&c.d_F32, c.n_F));
   c.want32 = true;
   c.have_geom32 = false;
   return FNPF_OK;
@@ -401,16 +400,14 @@ fnpf_status pcg64(Ctx &c, const double *f, double *x, const fnpf_solve_opts &o, 
   const int nb = apply_blocks(c);
   auto body = [&](hipStream_t st) -> fnpf_status {
     for (int k = 0; k < o.check_every; ++k) {
-      HIPCHK(launch_apply(c, FNPF_F64, c.d_p, c.d_q, true, c.d_partial, &sc->done, st));
-      HIPCHK(launch_finalize_pq(c.d_partial, nb, sc, st));
+      HIPCHK(launch_apply(c, FNPF_F64, c.d_p, c.d_q, true, c.d_partial, &sc->done, st, nullptr, true));
       if (mg) {
-        HIPCHK(launch_mg_update(c, FNPF_F64, x, c.d_r, c.d_p, c.d_q, c.d_partial, sc, st, o.cheb_degree));
+        HIPCHK(launch_mg_update(c, FNPF_F64, x, c.d_r, c.d_p, c.d_q, c.d_partial, nb, sc, st, o.cheb_degree));
         bool fused = false;
         HIPCHK(mg_vcycle<double>(c, c.d_r, z, &sc->done, o.cheb_degree, st, c.d_partial, &fused, true));
         HIPCHK(launch_mg_dot_dir(c, FNPF_F64, c.d_r, z, c.d_p, c.d_partial, sc, 0, st, fused));
       } else {
-        HIPCHK((launch_pcg_update<double, double>(x, c.d_r, c.d_p, c.d_q, dinv, c.n_v, c.d_partial, sc, st)));
-        HIPCHK(launch_pcg_dir<double>(c.d_p, c.d_r, dinv, c.n_v, sc, st));
+        HIPCHK(launch_pcg_iteration<double>(c, x, c.d_r, c.d_p, c.d_q, dinv, c.d_partial, nb, sc, st));
       }
     }
     return FNPF_OK;
@@ -451,18 +448,15 @@ fnpf_status pcg_mixed(Ctx &c, const double *f, double *x, const fnpf_solve_opts 
   const int nb = apply_blocks(c);
   auto body = [&](hipStream_t st) -> fnpf_status {
     for (int k = 0; k < o.check_every; ++k) {
-      HIPCHK(launch_apply(c, FNPF_F32, c.d_p32, c.d_q32, true, c.d_partial, &si->done, st));
-      HIPCHK(launch_finalize_pq(c.d_partial, nb, si, st));
+      HIPCHK(launch_apply(c, FNPF_F32, c.d_p32, c.d_q32, true, c.d_partial, &si->done, st, nullptr, true));
       if (mg) {
-        HIPCHK(launch_mg_update(c, FNPF_F32, c.d_d32, c.d_r32, c.d_p32, c.d_q32, c.d_partial, si, st,
+        HIPCHK(launch_mg_update(c, FNPF_F32, c.d_d32, c.d_r32, c.d_p32, c.d_q32, c.d_partial, nb, si, st,
                                 o.cheb_degree));
         bool fused = false;
         HIPCHK(mg_vcycle<float>(c, c.d_r32, z, &si->done, o.cheb_degree, st, c.d_partial, &fused, true));
         HIPCHK(launch_mg_dot_dir(c, FNPF_F32, c.d_r32, z, c.d_p32, c.d_partial, si, 0, st, fused));
       } else {
-        HIPCHK((launch_pcg_update<float, float>(c.d_d32, c.d_r32, c.d_p32, c.d_q32, dinv, c.n_v, c.d_partial, si,
-                                                st)));
-        HIPCHK(launch_pcg_dir<float>(c.d_p32, c.d_r32, dinv, c.n_v, si, st));
+        HIPCHK(launch_pcg_iteration<float>(c, c.d_d32, c.d_r32, c.d_p32, c.d_q32, dinv, c.d_partial, nb, si, st));
       }
     }
     return FNPF_OK;
@@ -670,7 +664,8 @@ fnpf_status fnpf_create(const fnpf_mesh_desc *m, fnpf_ctx *out) {
   }
   c.h_hm = hm;
   c.ncg = c.dim == 3 ? 5 : 3;
-  c.apply_lines = c.apply_owner = c.dim == 3;   // default schedule of the 3D apply
+  c.apply_lines = c.dim == 3;   // default schedule of the apply
+  c.apply_owner = true;
   c.h_half_ds.resize(c.nz);
   for (int l = 0; l < c.nz; ++l) c.h_half_ds[l] = 0.5 * (c.h_layer_s[l + 1] - c.h_layer_s[l]);
   // total apply blocks over colours (partials of the fused dot product)
@@ -714,29 +709,51 @@ fnpf_status fnpf_create(const fnpf_mesh_desc *m, fnpf_ctx *out) {
   UP(c.d_cols, cols.data(), cols.size());
   {
     UP(c.d_slot, c.h_slot.data(), c.h_slot.size());
-    if (c.h_ps_node.empty()) c.h_ps_node.push_back(0);   // a mesh without shared nodes: one unused entry
-    if (c.h_ps_slot.empty()) c.h_ps_slot.push_back(0);
-    UP(c.d_ps_node, c.h_ps_node.data(), c.h_ps_node.size());
-    UP(c.d_ps_ptr, c.h_ps_ptr.data(), c.h_ps_ptr.size());
-    UP(c.d_ps_slot, c.h_ps_slot.data(), c.h_ps_slot.size());
-    c.lpc = owner_chunk_layers(c.n_eh, c.p, c.nz);
+    // slots by node as the vector kernels read them (deferred.h)
+    std::vector<int4> s1;
+    std::vector<int32_t> lists;
+    auto by_node = [&](const std::vector<int32_t> &node, const std::vector<int32_t> &ptr,
+                       const std::vector<int32_t> &slot, int n) {
+      const int64_t hi = n > 0 ? (int64_t)node[n - 1] + 1 : 0;   // nodes ascend
+      s1.assign(std::max<int64_t>(hi, 1), make_int4(-1, -1, -1, 0));
+      lists.assign(1, 0);
+      for (int k = 0; k < n; ++k) {
+        const int32_t a = ptr[k], m = ptr[k + 1] - a;
+        int4 &s = s1[node[k]];
+        if (m > 0) s.x = slot[a];
+        if (m > 1) s.y = slot[a + 1];
+        if (m > 2) s.z = slot[a + 2];
+        if (m > 3) {
+          s.w = (int32_t)lists.size();
+          lists.push_back(m - 3);
+          lists.insert(lists.end(), slot.begin() + a + 3, slot.begin() + a + m);
+        }
+      }
+      return hi;
+    };
+    c.p_n_hi = by_node(c.h_ps_node, c.h_ps_ptr, c.h_ps_slot, c.n_ps);
+    UP(c.d_p_slots, s1.data(), s1.size());
+    UP(c.d_p_lists, lists.data(), lists.size());
+    c.lpc = owner_chunk_layers(c.n_eh, c.nh, c.nz);
     // a split that the allocation-free apply's scratch cannot hold is not made
     if (face_buffer_elements(c, c.n_tslots) * sizeof(double) > noalloc_scratch_bytes()) c.lpc = c.nz;
-    AL(c.d_F64, std::max((size_t)(c.p * c.nz + 1) * std::max<int64_t>(std::max(c.n_slots, c.n_gslots), 1),
-                         face_buffer_elements(c, c.n_tslots)));
+    // the apply's slots, the geometry's, the restriction's (its chunks are those of the finer level,
+    // at most this level's)
+    c.n_F = std::max({face_buffer_elements(c, c.n_tslots), (size_t)(c.p * c.nz + 1) * (size_t)c.n_gslots,
+                      face_buffer_elements(c, c.n_slots), (size_t)1});
+    AL(c.d_F64, c.n_F);
+    // the lists may be empty (a mesh within one tile): upload one unused entry then
+    if (c.h_tps_node.empty()) c.h_tps_node.push_back(0);
+    if (c.h_tps_slot.empty()) c.h_tps_slot.push_back(0);
+    UP(c.d_tslot, c.h_tslot.data(), c.h_tslot.size());
+    UP(c.d_tps_node, c.h_tps_node.data(), c.h_tps_node.size());
+    UP(c.d_tps_ptr, c.h_tps_ptr.data(), c.h_tps_ptr.size());
+    UP(c.d_tps_slot, c.h_tps_slot.data(), c.h_tps_slot.size());
+    c.t_n_hi = by_node(c.h_tps_node, c.h_tps_ptr, c.h_tps_slot, c.n_tps);
+    UP(c.d_t_slots, s1.data(), s1.size());
+    UP(c.d_t_lists, lists.data(), lists.size());
     if (c.dim == 3) {
-      // the lists may be empty (a mesh within one tile): upload one unused entry then
-      if (c.h_tps_node.empty()) c.h_tps_node.push_back(0);
-      if (c.h_tps_slot.empty()) c.h_tps_slot.push_back(0);
-      UP(c.d_tslot, c.h_tslot.data(), c.h_tslot.size());
       UP(c.d_xch, c.h_xch.data(), c.h_xch.size());
-      UP(c.d_tps_node, c.h_tps_node.data(), c.h_tps_node.size());
-      UP(c.d_tps_ptr, c.h_tps_ptr.data(), c.h_tps_ptr.size());
-      UP(c.d_tps_slot, c.h_tps_slot.data(), c.h_tps_slot.size());
-      std::vector<int32_t> np(c.n_s + 1, 0);
-      for (int k = 0; k < c.n_tps; ++k) np[c.h_tps_node[k] + 1] = c.h_tps_ptr[k + 1] - c.h_tps_ptr[k];
-      for (int64_t n = 0; n < c.n_s; ++n) np[n + 1] += np[n];
-      UP(c.d_tn_ptr, np.data(), np.size());
       if (c.h_gx_slot.empty()) c.h_gx_slot.push_back(0);
       UP(c.d_gslot, c.h_gslot.data(), c.h_gslot.size());
       UP(c.d_gx_ptr, c.h_gx_ptr.data(), c.h_gx_ptr.size());
@@ -837,7 +854,7 @@ fnpf_status fnpf_set_apply_variant(fnpf_ctx ctx, int32_t variant) {
   if (variant != 0 && variant != 1 && variant != 6 && variant != 7)
     return fail(&c, FNPF_ERR_ARG, "apply variant must be 0, 1, 6 or 7");
   c.apply_lines = c.dim == 3 && (variant == 0 || variant == 6);
-  c.apply_owner = c.dim == 3 && variant == 0;
+  c.apply_owner = variant == 0;
   if (variant >= 6) variant = 0;   // 6 and 7 are schedules of the fused apply (apply_lines, apply_owner)
   if (variant == c.apply_variant) return FNPF_OK;
   c.apply_variant = variant;

@@ -32,7 +32,8 @@ constexpr int kHm2 = 2;
 
 // Device-side PCG scalars (FP64 even for the FP32 inner solve).
 struct PcgScalars {
-  double rz;       // r^T z of the current iterate
+  double rz;       // r^T z that alpha was formed with (the direction update divides by it)
+  double rz2;      // r^T z of the newest iterate
   double rr;       // r^T r of the current iterate
   double pq;       // p^T A p
   double alpha;
@@ -93,7 +94,7 @@ hipError_t launch_geom(Ctx &c, const double *eta, const double *h, bool store_G,
 // geometry update did not store it
 hipError_t ensure_diag(Ctx &c, hipStream_t s);
 hipError_t launch_apply(Ctx &c, fnpf_dtype dt, const void *x, void *y, bool mask, double *partial,
-                        const int32_t *skip, hipStream_t s, void *face_scratch = nullptr);
+                        const int32_t *skip, hipStream_t s, void *face_scratch = nullptr, bool defer = false);
 hipError_t launch_neumann(Ctx &c, const double *q, double *f, hipStream_t s);
 hipError_t launch_wsurf(Ctx &c, const double *phi, double *w, hipStream_t s);
 struct RkStageArgs {
@@ -154,12 +155,11 @@ hipError_t launch_resid_to32(const double *f, const double *Ax, float *r, float 
                              int64_t n_v, int64_t n_s, double *partial, PcgScalars *outer, PcgScalars *inner,
                              double inner_rtol, hipStream_t s);
 hipError_t launch_finalize_pq(const double *partial, int np, PcgScalars *sc, hipStream_t s);
-template <typename T, typename TX>
-hipError_t launch_pcg_update(TX *x, T *r, const T *p, const T *q, const T *dinv, int64_t n_v, double *partial,
-                             PcgScalars *sc, hipStream_t s);
-hipError_t launch_finalize_rz(const double *partial, int np, PcgScalars *sc, hipStream_t s);
+// one PCG iteration's updates after q = A p as launch_apply(..., defer) left it, with its npq partials
+// of p.q at the front of partial: x, r, the convergence test, the next direction
 template <typename T>
-hipError_t launch_pcg_dir(T *p, const T *r, const T *dinv, int64_t n_v, PcgScalars *sc, hipStream_t s);
+hipError_t launch_pcg_iteration(const Ctx &c, T *x, T *r, T *p, const T *q, const T *dinv, double *partial, int npq,
+                                PcgScalars *sc, hipStream_t s);
 hipError_t launch_add_f32(double *x, const float *d, int64_t n_v, hipStream_t s);
 hipError_t launch_cast_f32(const double *a, float *b, int64_t n, hipStream_t s);
 hipError_t launch_fill(double *v, double val, int64_t n, hipStream_t s);
@@ -213,14 +213,17 @@ struct Ctx {
   // 2 fused geometry, unrolled schedule; the schedule of 0 is refined by the fields below
   int apply_variant = 0;
   bool apply_lines = false;               // 3D fused apply with the xi/eta line schedule
-  bool apply_owner = false;               // 3D line schedule with owner-computes assembly (two passes)
+  bool apply_owner = false;               // owner-computes assembly (3D: of the line schedule; 2D: of columns)
   // owner-computes assembly: contributions of a column at nodes it does not own go to face
   // slots (column-major numbering); the second pass adds them at the owner
   std::vector<int32_t> h_slot;            // [n_eh][nh] slot id, -1 where owned
   std::vector<int32_t> h_ps_node, h_ps_ptr, h_ps_slot;  // shared nodes, CSR of their slots
   int64_t n_slots = 0;
   int n_ps = 0;
-  int32_t *d_slot = nullptr, *d_ps_node = nullptr, *d_ps_ptr = nullptr, *d_ps_slot = nullptr;
+  int32_t *d_slot = nullptr;
+  int4 *d_p_slots = nullptr;              // the slots by node (deferred.h), nodes below p_n_hi
+  int32_t *d_p_lists = nullptr;
+  int64_t p_n_hi = 0;
   // tile assembly of the owner-computes apply: a tile is tile_cols consecutive columns (one
   // workgroup); contributions of a tile's columns at a node are summed in LDS by the tile's
   // representative column of the node (exchange entries h_xch: [n_eh][nh][4] int16, the entry this
@@ -234,8 +237,11 @@ struct Ctx {
   int64_t n_tslots = 0;
   int n_tps = 0;
   int32_t *d_tslot = nullptr, *d_tps_node = nullptr, *d_tps_ptr = nullptr, *d_tps_slot = nullptr;
-  int32_t *d_tn_ptr = nullptr;            // [n_s + 1] the slots of every node in d_tps_slot
+  int4 *d_t_slots = nullptr;              // the slots by node (deferred.h), nodes below t_n_hi
+  int32_t *d_t_lists = nullptr;
+  int64_t t_n_hi = 0;
   int lpc = 1;                            // layers per block of the owner-computes apply
+  size_t n_F = 0;                         // elements of d_F64 (and d_F32)
   int16_t *d_xch = nullptr;
   // the geometry's face layout (k_geom, k_diag_faces): per column node its place in a level row
   // of n_gslots entries (-1 none): the owner tile's value at a node with slots at k (its position
@@ -361,7 +367,7 @@ struct Ctx {
 // (pass 1, which takes the fused dot product)
 bool owner_apply_active(const Ctx &c);
 int owner_apply_blocks(const Ctx &c);
-int owner_chunk_layers(int n_eh, int p, int nz);
+int owner_chunk_layers(int n_eh, int nh, int nz);
 // elements of a face-slot buffer of the owner-computes apply with n_slots slots per level
 size_t face_buffer_elements(const Ctx &c, int64_t n_slots);
 
@@ -373,17 +379,16 @@ fnpf_status mg_refresh(Ctx &c, hipStream_t s);
 template <typename T>
 hipError_t mg_vcycle(Ctx &c, const T *r, T *z, const int32_t *skip, int smooth, hipStream_t s,
                      double *dot_partial = nullptr, bool *dot_done = nullptr, bool pre_scaled = false);
-// x += alpha p, r -= alpha q with the partials of r.r; with the degree-2 V-cycle (smooth == 2 and a
+// alpha from the npq partials of p.q, x += alpha p, r -= alpha q and r.r; with the degree-2 V-cycle (smooth == 2 and a
 // hierarchy) it also writes the cycle's first smoothing step, and the mg_vcycle call on this r that
 // follows must pass pre_scaled = true.
 hipError_t launch_mg_update(Ctx &c, fnpf_dtype dt, void *x, void *r, const void *p, const void *q, double *partial,
-                            PcgScalars *sc, hipStream_t s, int smooth);
+                            int npq, PcgScalars *sc, hipStream_t s, int smooth);
 hipError_t launch_mg_dot_dir(Ctx &c, fnpf_dtype dt, const void *r, const void *z, void *p, double *partial,
                              PcgScalars *sc, int first, hipStream_t s, bool have_partials = false);
 Ctx &ctx_of(fnpf_ctx h);
 fnpf_status ctx_ensure32(Ctx &c);
 fnpf_status geom_impl_total(Ctx &c, const double *H, const double *h, hipStream_t s);
-hipError_t launch_faces(Ctx &c, fnpf_dtype dt, void *y, bool mask, hipStream_t s, const int32_t *skip);
 // vertical line smoother (line_smoother.hip): band[d][v][n] of B assembled from the geometry,
 // the level's Cholesky factors (FP64, and FP32 when the level keeps FP32 data), and the smoothing
 // steps with them

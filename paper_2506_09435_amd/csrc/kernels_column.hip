@@ -519,7 +519,11 @@ __global__ __launch_bounds__(256) void k_apply(const T *__restrict__ x, T *__res
 // zeta part of the transposed contraction, y_zeta[k'] += D[k][k'] v_zeta[k], straight into a
 // register line; the backward loop is unrolled.  Live registers: the thread's D rows, its
 // vertical line, the y_zeta line and the column geometry.
-template <int P, int DIM, typename T, bool MASK, bool DOT>
+// OWN (2D): one launch over all columns and chunks of lpc layers (blockIdx.y), assembled as the line
+// schedule's OWN and SPLIT below but without tiles: a column stores the nodes it owns into y and its
+// other end node into a face slot.  It halves the launches of the colour schedule, which is what a
+// slice's solve costs (8 x 2, p = 4: about 3 us a launch whatever its work).
+template <int P, int DIM, typename T, bool MASK, bool DOT, bool OWN = false>
 __global__ __launch_bounds__(256) void k_apply_fused2(const T *__restrict__ x, T *__restrict__ y,
                                                       const T *__restrict__ cg, const T *__restrict__ hmT,
                                                       int64_t hstride, const T *__restrict__ sig,
@@ -527,7 +531,10 @@ __global__ __launch_bounds__(256) void k_apply_fused2(const T *__restrict__ x, T
                                                       const int32_t *__restrict__ eh_nodes,
                                                       const uint8_t *__restrict__ flags,
                                                       const int32_t *__restrict__ cols, int ncols, int nz, int64_t n_s,
-                                                      double *__restrict__ partial, const int32_t *__restrict__ skip) {
+                                                      double *__restrict__ partial, const int32_t *__restrict__ skip,
+                                                      T *__restrict__ F = nullptr,
+                                                      const int32_t *__restrict__ slot = nullptr,
+                                                      int64_t n_slots = 0, int lpc = 0) {
   using S = Sh<P, DIM>;
   constexpr int N1 = S::N1, NH = S::NH, NP = S::NP, CPB = S::CPB;
   __shared__ T su[CPB * NP];
@@ -540,8 +547,10 @@ __global__ __launch_bounds__(256) void k_apply_fused2(const T *__restrict__ x, T
   const int i = t % N1, j = t / N1;
   const int ci = blockIdx.x * CPB + lc;
   const bool active = ci < ncols;
-  const int col = active ? cols[ci] : 0;
+  const int col = active ? (OWN ? ci : cols[ci]) : 0;
   const int hn = active ? eh_nodes[(int64_t)col * NH + t] : 0;
+  const int chunk = OWN ? blockIdx.y : 0, nchunk = OWN ? gridDim.y : 1;
+  const int l0 = OWN ? chunk * lpc : 0, l1 = OWN ? min(l0 + lpc, nz) : nz;
   const uint8_t fl = active ? flags[(int64_t)col * NH + t] : 0;
   const int64_t ho = (int64_t)col * NH + t;
 
@@ -583,20 +592,21 @@ __global__ __launch_bounds__(256) void k_apply_fused2(const T *__restrict__ x, T
   T ucol[N1];
   T carry = T(0);
   double dot = 0.0;
-  ucol[0] = active ? x[hn] : T(0);
+  const int32_t sl = OWN && active ? slot[ho] : -1;
+  ucol[0] = active ? x[(int64_t)(l0 * P) * n_s + hn] : T(0);
   const int vtop = P * nz;
 
   T nxt[N1];
 #pragma unroll
-  for (int k = 1; k < N1; ++k) nxt[k] = active ? x[(int64_t)k * n_s + hn] : T(0);
-  for (int l = 0; l < nz; ++l) {
+  for (int k = 1; k < N1; ++k) nxt[k] = active ? x[(int64_t)(l0 * P + k) * n_s + hn] : T(0);
+  for (int l = l0; l < l1; ++l) {
 #pragma unroll
     for (int k = 1; k < N1; ++k) ucol[k] = nxt[k];
 #pragma unroll
     for (int k = 0; k < N1; ++k) u_c[k * NH + t] = ucol[k];
     __syncthreads();
     // issue the next layer's loads now; they complete behind this layer's arithmetic
-    if (l + 1 < nz) {
+    if (l + 1 < l1) {
 #pragma unroll
       for (int k = 1; k < N1; ++k) nxt[k] = active ? x[(int64_t)((l + 1) * P + k) * n_s + hn] : T(0);
     }
@@ -672,16 +682,21 @@ __global__ __launch_bounds__(256) void k_apply_fused2(const T *__restrict__ x, T
       u_c[k * NH + t] = (a0 + a1) + (a2 + a3);
     }
     if (active) {
-      const int kend = (l == nz - 1) ? N1 : P;
+      const int kend = (l == l1 - 1) ? N1 : P;
       T yv[N1], old[N1];
 #pragma unroll
       for (int k = 0; k < N1; ++k) {
         yv[k] = u_c[k * NH + t];
         old[k] = T(0);
       }
+      if constexpr (OWN && DOT) {
+        // x.Ax is the sum of the columns' own contributions: it needs no assembled value
+#pragma unroll
+        for (int k = 0; k < N1; ++k) dot += (double)ucol[k] * (double)yv[k];
+      }
       yv[0] += carry;
       // colour schedule: all read-add-write loads of the line in flight together
-      if (!(fl & kFirst)) {
+      if (!OWN && !(fl & kFirst)) {
 #pragma unroll
         for (int k = 0; k < N1; ++k)
           if (k < kend) old[k] = y[(int64_t)(l * P + k) * n_s + hn];
@@ -691,8 +706,16 @@ __global__ __launch_bounds__(256) void k_apply_fused2(const T *__restrict__ x, T
         if (k < kend) {
           const int v = l * P + k;
           const T val = (MASK && v == vtop) ? T(0) : yv[k] + old[k];
-          y[(int64_t)v * n_s + hn] = val;
-          if (DOT && (fl & kLast)) dot += (double)ucol[k] * (double)val;
+          if constexpr (OWN) {
+            const bool below = k == P && l1 < nz;   // the next chunk's bottom level: apart from it
+            if (sl < 0)
+              (below ? F + (int64_t)(vtop + nchunk) * n_slots + chunk * n_s : y + (int64_t)v * n_s)[hn] = val;
+            else if (!(MASK && v == vtop))
+              F[(int64_t)(below ? vtop + 1 + chunk : v) * n_slots + sl] = val;
+          } else {
+            y[(int64_t)v * n_s + hn] = val;
+            if (DOT && (fl & kLast)) dot += (double)ucol[k] * (double)val;
+          }
         }
       }
     }
@@ -701,7 +724,7 @@ __global__ __launch_bounds__(256) void k_apply_fused2(const T *__restrict__ x, T
   }
   if constexpr (DOT) {
     double s = block_sum<CPB * NH>(dot);
-    if (threadIdx.x == 0) partial[blockIdx.x] = s;
+    if (threadIdx.x == 0) partial[blockIdx.y * gridDim.x + blockIdx.x] = s;
   }
 }
 
@@ -758,7 +781,9 @@ __global__ __launch_bounds__(256) void k_apply_lines(const T *__restrict__ x, T 
   __shared__ T sA[CPB * NP];
   __shared__ T sB[CPB * NPB];
   __shared__ T sX[OWN ? N1 * XM : 1];
-  if (skip != nullptr && *skip) return;
+  // small meshes (SPLIT) test the flag after the first loads are issued: see below
+  const int dn = skip != nullptr ? *skip : 0;
+  if (!SPLIT && dn) return;
 
   const int lc = threadIdx.x / NH;
   const int t = threadIdx.x - lc * NH;
@@ -830,6 +855,10 @@ __global__ __launch_bounds__(256) void k_apply_lines(const T *__restrict__ x, T 
   T nxt[N1];
 #pragma unroll
   for (int k = 1; k < N1; ++k) nxt[k] = buf_ld<T>(rx, hb, (uint32_t)(l0 * P + k) * rowb);
+  if constexpr (SPLIT) {
+    asm volatile("" ::: "memory");   // keeps the loads above the test
+    if (dn) return;
+  }
   const uint8_t fl = active ? fl0_ : 0;
   if constexpr (OWN) {
     const int32_t sl = active ? sl0 : -1;
@@ -1034,7 +1063,7 @@ __global__ __launch_bounds__(256) void k_apply_faces(T *__restrict__ y, const T 
                                                      const int32_t *__restrict__ ps_ptr,
                                                      const int32_t *__restrict__ ps_slot, int n_ps, int nlev,
                                                      int64_t n_s, int64_t n_slots, int nba,
-                                                     const int32_t *__restrict__ node_ptr, int clev, int nchunk,
+                                                     const int4 *__restrict__ slots, int64_t n_hi, int clev, int nchunk,
                                                      const int32_t *__restrict__ skip) {
   if (skip != nullptr && *skip) return;
   constexpr int LC = kFaceLevels;
@@ -1043,7 +1072,7 @@ __global__ __launch_bounds__(256) void k_apply_faces(T *__restrict__ y, const T 
     const int nbx = (int)((n_s + 255) >> 8);
     const int c = ((int)blockIdx.x - nba) / nbx;
     const int64_t n = (int64_t)(((int)blockIdx.x - nba) - c * nbx) * 256 + threadIdx.x;
-    if (n < n_s && node_ptr[n] == node_ptr[n + 1]) y[(int64_t)(c + 1) * clev * n_s + n] += Z[c * n_s + n];
+    if (n < n_s && (n >= n_hi || slots[n].x < 0)) y[(int64_t)(c + 1) * clev * n_s + n] += Z[c * n_s + n];
     return;
   }
   int blk = blockIdx.x;
@@ -1086,7 +1115,9 @@ __global__ __launch_bounds__(256) void k_apply_faces(T *__restrict__ y, const T 
 }
 
 bool owner_apply_active(const Ctx &c) {
-  if (c.dim != 3 || c.apply_variant != 0 || !c.apply_owner) return false;
+  if (c.apply_variant != 0 || !c.apply_owner) return false;
+  // slices: while their slots fit the allocation-free apply's scratch, so that it has the same result
+  if (c.dim == 2) return face_buffer_elements(c, c.n_tslots) * sizeof(double) <= noalloc_scratch_bytes();
   const int64_t lim = int64_t(1) << 32;
   return c.n_v * 8 < lim && (int64_t)(c.p * c.nz + 1) * std::max(c.n_slots, c.n_tslots) * 8 < lim;
 }
@@ -1098,15 +1129,18 @@ bool owner_apply_active(const Ctx &c) {
 // FP64 apply of the periodic wave (40 x 40 x 4, p = 5; 229 tiles): 1, 2 and 4 chunks 20.4, 17.9 and
 // 17.9 us; Jacobi CG on the bar (64 x 16 x 4, p = 5; 147 tiles), 5,775 iterations: 207, 195, 191 ms.
 constexpr int kResidentBlocks = 4 * 256;
-int owner_chunk_layers(int n_eh, int p, int nz) {
-  const int cpb = tile_columns(p), tiles = (n_eh + cpb - 1) / cpb;
+// (A mesh of one tile has no face pass that could add them: its layers stay together as well.)
+static int owner_tiles(int n_eh, int nh) { return (n_eh + 256 / nh - 1) / (256 / nh); }
+int owner_chunk_layers(int n_eh, int nh, int nz) {
+  const int tiles = owner_tiles(n_eh, nh);
+  if (tiles == 1) return nz;
   const int nchunk = std::min(nz, std::max(1, kResidentBlocks / tiles));
   return (nz + nchunk - 1) / nchunk;
 }
 static int owner_chunks(const Ctx &c) { return (c.nz + c.lpc - 1) / c.lpc; }
 
 size_t face_buffer_elements(const Ctx &c, int64_t n_slots) {
-  const int nc = c.dim == 3 ? owner_chunks(c) : 1;
+  const int nc = owner_chunks(c);
   return (size_t)((c.p * c.nz + nc) * n_slots + (nc - 1) * c.n_s);
 }
 
@@ -1118,32 +1152,20 @@ static int face_blocks_n(const Ctx &c, int n) {
 // y at the nodes with face slots += the slots of F, over all levels (mask: but the top one)
 template <typename T>
 static hipError_t faces_impl(Ctx &c, T *y, const T *F, bool mask, const int32_t *node, const int32_t *ptr,
-                             const int32_t *slot, int n, int64_t n_slots, const int32_t *node_ptr, int nchunk,
+                             const int32_t *slot, int n, int64_t n_slots, const int4 *slots, int64_t n_hi, int nchunk,
                              const int32_t *skip, hipStream_t s) {
   const int nba = face_blocks_n(c, n);
   const int nb = nba + (nchunk - 1) * (int)((c.n_s + 255) / 256);
   if (nb == 0) return hipSuccess;
   auto kern = mask ? k_apply_faces<T, true> : k_apply_faces<T, false>;
-  kern<<<nb, 256, 0, s>>>(y, F, node, ptr, slot, n, c.p * c.nz + 1, c.n_s, n_slots, nba, node_ptr, c.lpc * c.p,
+  kern<<<nb, 256, 0, s>>>(y, F, node, ptr, slot, n, c.p * c.nz + 1, c.n_s, n_slots, nba, slots, n_hi, c.lpc * c.p,
                           nchunk, skip);
   return hipGetLastError();
 }
 
-// the face pass of the restriction: y at the shared nodes += the per-column face slots of the
-// context's F buffer of y's precision
-hipError_t launch_faces(Ctx &c, fnpf_dtype dt, void *y, bool mask, hipStream_t s, const int32_t *skip) {
-  if (dt == FNPF_F64)
-    return faces_impl<double>(c, (double *)y, c.d_F64, mask, c.d_ps_node, c.d_ps_ptr, c.d_ps_slot, c.n_ps, c.n_slots,
-                              nullptr, 1, skip, s);
-  return faces_impl<float>(c, (float *)y, c.d_F32, mask, c.d_ps_node, c.d_ps_ptr, c.d_ps_slot, c.n_ps, c.n_slots,
-                           nullptr, 1, skip, s);
-}
-
 // blocks of pass 1 (one partial each of the fused dot product)
 int owner_apply_blocks(const Ctx &c) {
-  if (c.dim != 3) return 0;
-  const int cpb = tile_columns(c.p);
-  return (c.n_eh + cpb - 1) / cpb * owner_chunks(c);
+  return owner_tiles(c.n_eh, c.nh) * owner_chunks(c);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1925,7 +1947,7 @@ hipError_t ensure_diag(Ctx &c, hipStream_t s) {
 
 template <int P, int DIM, typename T, bool MASK, bool DOT>
 static hipError_t apply_impl(Ctx &c, const T *x, T *y, const T *G, double *partial, const int32_t *skip,
-                             hipStream_t s, T *face_scratch) {
+                             hipStream_t s, T *face_scratch, bool defer) {
   using S = Sh<P, DIM>;
   const int64_t hs = (int64_t)c.n_eh * c.nh;
   const bool fused = c.apply_variant == 0;
@@ -1946,21 +1968,28 @@ static hipError_t apply_impl(Ctx &c, const T *x, T *y, const T *G, double *parti
     if (cr.count == 0) continue;
     const int nb = (cr.count + S::CPB - 1) / S::CPB;
     if (fused) {
-      if constexpr (DIM == 3) {
-        if (owner_apply_active(c)) {
+      if (owner_apply_active(c)) {
+        T *F = face_scratch;
+        if (F == nullptr) {
+          if constexpr (sizeof(T) == 8) F = (T *)c.d_F64; else F = (T *)c.d_F32;
+        }
+        if constexpr (DIM == 3) {
           if (c.tile_cols != S::CPB) return hipErrorInvalidValue;   // host tiles = workgroups
-          T *F = face_scratch;
-          if (F == nullptr) {
-            if constexpr (sizeof(T) == 8) F = (T *)c.d_F64; else F = (T *)c.d_F32;
-          }
           auto kern = owner_chunks(c) > 1 ? k_apply_lines<P, T, MASK, DOT, true, true>
                                           : k_apply_lines<P, T, MASK, DOT, true, false>;
           kern<<<owner_apply_blocks(c), S::NT, 0, s>>>(
               x, y, cg, hmT, hs, sig, hds, c.d_eh_nodes, c.d_flags, nullptr, c.n_eh, c.nz, c.n_s,
               DOT ? partial : nullptr, skip, F, c.d_tslot, c.n_tslots, c.d_xch, c.lpc);
-          return faces_impl<T>(c, y, F, MASK, c.d_tps_node, c.d_tps_ptr, c.d_tps_slot, c.n_tps, c.n_tslots,
-                               c.d_tn_ptr, owner_chunks(c), skip, s);
+        } else {
+          k_apply_fused2<P, DIM, T, MASK, DOT, true><<<dim3(owner_tiles(c.n_eh, c.nh), owner_chunks(c)), S::NT, 0, s>>>(
+              x, y, cg, hmT, hs, sig, hds, c.d_eh_nodes, c.d_flags, nullptr, c.n_eh, c.nz, c.n_s,
+              DOT ? partial : nullptr, skip, F, c.d_tslot, c.n_tslots, c.lpc);
         }
+        if (defer) return hipGetLastError();
+        return faces_impl<T>(c, y, F, MASK, c.d_tps_node, c.d_tps_ptr, c.d_tps_slot, c.n_tps, c.n_tslots,
+                             c.d_t_slots, c.t_n_hi, owner_chunks(c), skip, s);
+      }
+      if constexpr (DIM == 3) {
         if (c.apply_lines && (int64_t)c.n_v * (int64_t)sizeof(T) < (int64_t(1) << 32)) {
           k_apply_lines<P, T, MASK, DOT><<<nb, S::NT, 0, s>>>(x, y, cg, hmT, hs, sig, hds, c.d_eh_nodes, c.d_flags,
                                                                c.d_cols + cr.offset, cr.count, c.nz, c.n_s,
@@ -1983,36 +2012,37 @@ static hipError_t apply_impl(Ctx &c, const T *x, T *y, const T *G, double *parti
 
 template <int P, int DIM>
 static hipError_t apply_dispatch(Ctx &c, fnpf_dtype dt, const void *x, void *y, bool mask, double *partial,
-                                 const int32_t *skip, hipStream_t s, void *fs) {
+                                 const int32_t *skip, hipStream_t s, void *fs, bool defer) {
   const bool dot = partial != nullptr;
   if (dt == FNPF_F64) {
     const double *xx = (const double *)x;
     double *yy = (double *)y;
     double *F = (double *)fs;
-    if (!mask) return apply_impl<P, DIM, double, false, false>(c, xx, yy, c.d_G64, nullptr, skip, s, F);
-    if (!dot) return apply_impl<P, DIM, double, true, false>(c, xx, yy, c.d_G64, nullptr, skip, s, F);
-    return apply_impl<P, DIM, double, true, true>(c, xx, yy, c.d_G64, partial, skip, s, F);
+    if (!mask) return apply_impl<P, DIM, double, false, false>(c, xx, yy, c.d_G64, nullptr, skip, s, F, defer);
+    if (!dot) return apply_impl<P, DIM, double, true, false>(c, xx, yy, c.d_G64, nullptr, skip, s, F, defer);
+    return apply_impl<P, DIM, double, true, true>(c, xx, yy, c.d_G64, partial, skip, s, F, defer);
   }
   const float *xx = (const float *)x;
   float *yy = (float *)y;
   float *F = (float *)fs;
-  if (!mask) return apply_impl<P, DIM, float, false, false>(c, xx, yy, c.d_G32, nullptr, skip, s, F);
-  if (!dot) return apply_impl<P, DIM, float, true, false>(c, xx, yy, c.d_G32, nullptr, skip, s, F);
-  return apply_impl<P, DIM, float, true, true>(c, xx, yy, c.d_G32, partial, skip, s, F);
+  if (!mask) return apply_impl<P, DIM, float, false, false>(c, xx, yy, c.d_G32, nullptr, skip, s, F, defer);
+  if (!dot) return apply_impl<P, DIM, float, true, false>(c, xx, yy, c.d_G32, nullptr, skip, s, F, defer);
+  return apply_impl<P, DIM, float, true, true>(c, xx, yy, c.d_G32, partial, skip, s, F, defer);
 }
 
+// defer: leave the owner-computes apply's face pass to the reader (deferred.h, apply_result).
 // face_scratch: device memory for the face slots in place of the context's own (nullptr: the
 // context's); it must hold (p nz + 1) * n_tslots elements of the apply's precision
 hipError_t launch_apply(Ctx &c, fnpf_dtype dt, const void *x, void *y, bool mask, double *partial,
-                        const int32_t *skip, hipStream_t s, void *face_scratch) {
+                        const int32_t *skip, hipStream_t s, void *face_scratch, bool defer) {
   // one partial per block of every launch when the dot product is fused
   if (partial != nullptr &&
       !partials_fit(c.n_partial, owner_apply_active(c) ? owner_apply_blocks(c) : c.max_colour_blocks, 1))
     return hipErrorInvalidValue;
   if (c.dim == 3) {
-    FNPF_DISPATCH(3, c.p, return (apply_dispatch<P_, 3>(c, dt, x, y, mask, partial, skip, s, face_scratch)));
+    FNPF_DISPATCH(3, c.p, return (apply_dispatch<P_, 3>(c, dt, x, y, mask, partial, skip, s, face_scratch, defer)));
   } else {
-    FNPF_DISPATCH(2, c.p, return (apply_dispatch<P_, 2>(c, dt, x, y, mask, partial, skip, s, face_scratch)));
+    FNPF_DISPATCH(2, c.p, return (apply_dispatch<P_, 2>(c, dt, x, y, mask, partial, skip, s, face_scratch, defer)));
   }
   return hipSuccess;
 }

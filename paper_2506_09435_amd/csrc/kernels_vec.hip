@@ -13,62 +13,15 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
+#include "deferred.h"
 #include "fnpf_internal.h"
+#include "reduce.h"
 
 namespace fnpf {
 
 namespace {
-
-__device__ __forceinline__ double wsum(double v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
-}
-
-// Block reduction of NS sums; thread 0 writes them to partial[blockIdx.x * NS + k].
-template <int NS>
-__device__ __forceinline__ void block_partials(double (&v)[NS], double *partial) {
-  constexpr int NW = kVecThreads / 64;
-  __shared__ double s[NS][NW];
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-#pragma unroll
-  for (int k = 0; k < NS; ++k) {
-    double r = wsum(v[k]);
-    if (lane == 0) s[k][wv] = r;
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-#pragma unroll
-    for (int k = 0; k < NS; ++k) {
-      double a = 0.0;
-      for (int w = 0; w < NW; ++w) a += s[k][w];
-      partial[blockIdx.x * NS + k] = a;
-    }
-  }
-}
-
-// Fixed-order sum of np partial tuples (stride NS) by one block.
-template <int NS>
-__device__ __forceinline__ void final_sums(const double *partial, int np, double (&out)[NS]) {
-  __shared__ double s[NS][kVecThreads];
-  double a[NS];
-#pragma unroll
-  for (int k = 0; k < NS; ++k) a[k] = 0.0;
-  for (int b = threadIdx.x; b < np; b += kVecThreads)
-#pragma unroll
-    for (int k = 0; k < NS; ++k) a[k] += partial[b * NS + k];
-#pragma unroll
-  for (int k = 0; k < NS; ++k) s[k][threadIdx.x] = a[k];
-  __syncthreads();
-  for (int w = kVecThreads / 2; w > 0; w >>= 1) {
-    if (threadIdx.x < w)
-#pragma unroll
-      for (int k = 0; k < NS; ++k) s[k][threadIdx.x] += s[k][threadIdx.x + w];
-    __syncthreads();
-  }
-#pragma unroll
-  for (int k = 0; k < NS; ++k) out[k] = s[k][0];
-}
 
 __global__ void k_set_lift(double *v, const double *phis, int64_t n_v, int64_t top0) {
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n_v; i += (int64_t)gridDim.x * blockDim.x)
@@ -136,7 +89,7 @@ __global__ __launch_bounds__(kVecThreads) void k_fin_init(const double *partial,
   double s[2];
   final_sums<2>(partial, np, s);
   if (threadIdx.x == 0) {
-    sc->rz = s[0];
+    sc->rz2 = s[0];
     sc->rr = s[1];
     sc->rr0 = s[1];
     if (relative) sc->tol2 = inner_rtol * inner_rtol * s[1];
@@ -181,7 +134,7 @@ __global__ __launch_bounds__(kVecThreads) void k_fin_outer(const double *partial
     outer->rr = s[0];
     outer->breakdown = (s[0] == s[0] && s[0] <= 1e300) ? 0 : 2;
     outer->done = (outer->breakdown != 0 || s[0] <= outer->tol2) ? 1 : 0;
-    inner->rz = s[1];
+    inner->rz2 = s[1];
     inner->rr = s[2];
     inner->rr0 = s[2];
     inner->tol2 = fmax(inner_rtol * inner_rtol * s[2], kInnerFloor * kInnerFloor * outer->tol2);
@@ -197,20 +150,63 @@ __global__ __launch_bounds__(kVecThreads) void k_fin_pq(const double *partial, i
   if (sc->done) return;
   double s[1];
   final_sums<1>(partial, np, s);
-  if (threadIdx.x == 0) {
-    sc->pq = s[0];
-    if (!(s[0] > 0.0) || !(s[0] <= 1e300)) {
-      sc->breakdown = (s[0] == s[0]) ? 1 : 2;
-      sc->done = 1;
-      sc->alpha = 0.0;
-    } else {
-      sc->alpha = sc->rz / s[0];
-    }
+  if (threadIdx.x == 0) cg_set_alpha(sc, s[0], sc->rz2);
+}
+
+// x += alpha p ; r -= alpha q ; partial sums (r.z, r.r) with z = dinv r.  q comes straight from
+// the apply's first pass and is assembled here.  Bound by HBM on large meshes (seven vector
+// accesses and the slots), by launches on small ones.
+template <typename T>
+struct PcgLoads { T x, r, p, d; };
+// np > 0: alpha from the np partials of p.q, else as k_fin_pq left it
+template <int LV, typename T>
+__global__ __launch_bounds__(kVecThreads) void k_pcg_update(T *x, T *r, const T *p, Deferred<T> q, const T *dinv,
+                                                            int64_t n_s, double *partial, PcgScalars *sc,
+                                                            const double *pq, int np) {
+  const int dn = sc->done;
+  const double rz = sc->rz2, alpha = sc->alpha;
+  const PartialLoads<1> pv(pq, np);
+  T a = T(0);
+  double v[2] = {0.0, 0.0};
+  for_nodes<LV>(q, n_s, [&](int64_t i) { return PcgLoads<T>{x[i], r[i], p[i], dinv[i]}; },
+            [&] {
+              if (dn) return false;
+              a = (T)(np > 0 ? cg_alpha(pv, rz, sc) : alpha);
+              return true;
+            },
+            [&](int64_t i, const PcgLoads<T> &l, T qi) {
+              x[i] = l.x + a * l.p;
+              const T ri = l.r - a * qi;
+              r[i] = ri;
+              const T zi = l.d * ri;
+              v[0] += (double)ri * (double)zi;
+              v[1] += (double)ri * (double)ri;
+            });
+  if (dn) return;
+  block_partials<2>(v, partial);
+}
+
+// after an iteration: the new r.z and r.r, convergence
+__device__ __forceinline__ void pcg_store(PcgScalars *sc, double rz, double rr, double beta) {
+  sc->beta = beta;
+  sc->rz2 = rz;
+  sc->rr = rr;
+  sc->iters += 1;
+  if (!(rr == rr) || !(rr <= 1e300)) {
+    sc->breakdown = 2;
+    sc->done = 1;
+  } else if (rr <= sc->tol2) {
+    sc->done = 1;
   }
 }
 
-// x += alpha p ; r -= alpha q ; partial sums (r.z, r.r) with z = dinv r.
-// Vectorised over 16-byte chunks (VW elements); the tail is handled element-wise.
+__global__ __launch_bounds__(kVecThreads) void k_fin_rz(const double *partial, int np, PcgScalars *sc) {
+  if (sc->done) return;
+  double s[2];
+  final_sums<2>(partial, np, s);
+  if (threadIdx.x == 0) pcg_store(sc, s[0], s[1], s[0] / sc->rz);
+}
+
 template <typename T>
 struct Vec16;
 template <>
@@ -224,107 +220,55 @@ struct Vec16<float> {
   static constexpr int W = 4;
 };
 
-template <typename T>
-__device__ __forceinline__ void upd_one(T *x, T *r, const T *p, const T *q, const T *dinv, int64_t i, T a,
-                                        double (&v)[2]) {
-  x[i] = x[i] + a * p[i];
-  T ri = r[i] - a * q[i];
-  r[i] = ri;
-  T zi = dinv[i] * ri;
-  v[0] += (double)ri * (double)zi;
-  v[1] += (double)ri * (double)ri;
-}
-
-// element-wise fallback (operands not 16-byte aligned)
-template <typename T>
-__global__ __launch_bounds__(kVecThreads) void k_pcg_update_scalar(T *x, T *r, const T *p, const T *q, const T *dinv,
-                                                                   int64_t n_v, double *partial,
-                                                                   const PcgScalars *sc) {
-  if (sc->done) return;
-  const T a = (T)sc->alpha;
-  double v[2] = {0.0, 0.0};
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n_v; i += (int64_t)gridDim.x * blockDim.x)
-    upd_one(x, r, p, q, dinv, i, a, v);
-  block_partials<2>(v, partial);
-}
-
-template <typename T, typename TX>
-__global__ __launch_bounds__(kVecThreads) void k_pcg_update(TX *x, T *r, const T *p, const T *q, const T *dinv,
-                                                            int64_t n_v, double *partial, const PcgScalars *sc) {
-  static_assert(sizeof(T) == sizeof(TX), "the solution and the residual share the precision");
-  if (sc->done) return;
-  const T a = (T)sc->alpha;
-  double v[2] = {0.0, 0.0};
-  using V = typename Vec16<T>::type;
-  constexpr int W = Vec16<T>::W;
-  const int64_t nvec = n_v / W;
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t c = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; c < nvec; c += stride) {
-    V xv = reinterpret_cast<V *>(x)[c];
-    V rv = reinterpret_cast<V *>(r)[c];
-    const V pv = reinterpret_cast<const V *>(p)[c];
-    const V qv = reinterpret_cast<const V *>(q)[c];
-    const V dv = reinterpret_cast<const V *>(dinv)[c];
-    T *xs = reinterpret_cast<T *>(&xv);
-    T *rs = reinterpret_cast<T *>(&rv);
-    const T *ps = reinterpret_cast<const T *>(&pv);
-    const T *qs = reinterpret_cast<const T *>(&qv);
-    const T *ds = reinterpret_cast<const T *>(&dv);
-#pragma unroll
-    for (int w = 0; w < W; ++w) {
-      xs[w] = xs[w] + a * ps[w];
-      const T ri = rs[w] - a * qs[w];
-      rs[w] = ri;
-      const T zi = ds[w] * ri;
-      v[0] += (double)ri * (double)zi;
-      v[1] += (double)ri * (double)ri;
-    }
-    reinterpret_cast<V *>(x)[c] = xv;
-    reinterpret_cast<V *>(r)[c] = rv;
-  }
-  if (blockIdx.x == 0)
-    for (int64_t i = nvec * W + threadIdx.x; i < n_v; i += blockDim.x) upd_one(x, r, p, q, dinv, i, a, v);
-  block_partials<2>(v, partial);
-}
-
-__global__ __launch_bounds__(kVecThreads) void k_fin_rz(const double *partial, int np, PcgScalars *sc) {
-  if (sc->done) return;
-  double s[2];
-  final_sums<2>(partial, np, s);
-  if (threadIdx.x == 0) {
-    sc->beta = s[0] / sc->rz;
-    sc->rz = s[0];
-    sc->rr = s[1];
-    sc->iters += 1;
-    if (!(s[1] == s[1]) || !(s[1] <= 1e300)) {
-      sc->breakdown = 2;
-      sc->done = 1;
-    } else if (s[1] <= sc->tol2) {
-      sc->done = 1;
-    }
-  }
-}
-
-// p = dinv r + beta p
+// p = dinv r + beta p, in 16-byte chunks (all three are allocations of the library).  np > 0: beta
+// from the np partials of (r.z, r.r), which every block sums and the first one stores with the
+// convergence test (a late block that already sees `done` leaves p, which is not used any more).
 template <typename T>
 __global__ __launch_bounds__(kVecThreads) void k_pcg_dir(T *p, const T *r, const T *dinv, int64_t n_v,
-                                                         const PcgScalars *sc) {
-  if (sc->done) return;
-  const T b = (T)sc->beta;
+                                                         PcgScalars *sc, const double *partial, int np) {
   using V = typename Vec16<T>::type;
   constexpr int W = Vec16<T>::W;
   const int64_t nvec = n_v / W;
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t c = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; c < nvec; c += stride) {
-    V pv = reinterpret_cast<V *>(p)[c];
-    const V rv = reinterpret_cast<const V *>(r)[c];
-    const V dv = reinterpret_cast<const V *>(dinv)[c];
+  const int dn = sc->done;
+  const double rz = sc->rz, beta0 = sc->beta;
+  const PartialLoads<2> sums(partial, np);
+  int64_t c = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+  V pv{}, rv{}, dv{};
+  if (c < nvec) {
+    pv = reinterpret_cast<const V *>(p)[c];
+    rv = reinterpret_cast<const V *>(r)[c];
+    dv = reinterpret_cast<const V *>(dinv)[c];
+  }
+  asm volatile("" ::: "memory");   // the first loads stay ahead of the test
+  if (dn) return;
+  double beta;
+  if (np > 0) {
+    double s[2];
+    sums.sums(s);
+    beta = s[0] / rz;
+    if (blockIdx.x == 0 && threadIdx.x == 0) pcg_store(sc, s[0], s[1], beta);
+  } else {
+    beta = beta0;
+  }
+  const T b = (T)beta;
+  for (; c < nvec; c += stride) {
+    const int64_t c2 = c + stride;
+    V p2{}, r2{}, d2{};
+    if (c2 < nvec) {
+      p2 = reinterpret_cast<const V *>(p)[c2];
+      r2 = reinterpret_cast<const V *>(r)[c2];
+      d2 = reinterpret_cast<const V *>(dinv)[c2];
+    }
     T *ps = reinterpret_cast<T *>(&pv);
     const T *rs = reinterpret_cast<const T *>(&rv);
     const T *ds = reinterpret_cast<const T *>(&dv);
 #pragma unroll
     for (int w = 0; w < W; ++w) ps[w] = ds[w] * rs[w] + b * ps[w];
     reinterpret_cast<V *>(p)[c] = pv;
+    pv = p2;
+    rv = r2;
+    dv = d2;
   }
   if (blockIdx.x == 0)
     for (int64_t i = nvec * W + threadIdx.x; i < n_v; i += blockDim.x) p[i] = dinv[i] * r[i] + b * p[i];
@@ -442,36 +386,28 @@ hipError_t launch_finalize_pq(const double *partial, int np, PcgScalars *sc, hip
   return hipGetLastError();
 }
 
-template <typename T, typename TX>
-hipError_t launch_pcg_update(TX *x, T *r, const T *p, const T *q, const T *dinv, int64_t n_v, double *partial,
-                             PcgScalars *sc, hipStream_t s) {
-  // every vector here is a device allocation (256-byte aligned) except x, which may be a caller
-  // tensor: the vectorised kernel requires 16-byte alignment of all operands
-  if ((reinterpret_cast<uintptr_t>(x) & 15) != 0)
-    k_pcg_update_scalar<T><<<kVecBlocks, kVecThreads, 0, s>>>(x, r, p, q, dinv, n_v, partial, sc);
-  else
-    k_pcg_update<T, TX><<<kVecBlocks, kVecThreads, 0, s>>>(x, r, p, q, dinv, n_v, partial, sc);
-  k_fin_rz<<<1, kVecThreads, 0, s>>>(partial, kVecBlocks, sc);
-  return hipGetLastError();
-}
-template hipError_t launch_pcg_update<double, double>(double *, double *, const double *, const double *,
-                                                      const double *, int64_t, double *, PcgScalars *, hipStream_t);
-template hipError_t launch_pcg_update<float, float>(float *, float *, const float *, const float *, const float *,
-                                                    int64_t, double *, PcgScalars *, hipStream_t);
-
-hipError_t launch_finalize_rz(const double *partial, int np, PcgScalars *sc, hipStream_t s) {
-  k_fin_rz<<<1, kVecThreads, 0, s>>>(partial, np, sc);
-  return hipGetLastError();
-}
-
+// One PCG iteration's updates after q = A p (deferred), npq partials of p.q at the front of partial:
+// x, r, the convergence test and the next direction.
 template <typename T>
-hipError_t launch_pcg_dir(T *p, const T *r, const T *dinv, int64_t n_v, PcgScalars *sc, hipStream_t s) {
-  k_pcg_dir<T><<<kVecBlocks, kVecThreads, 0, s>>>(p, r, dinv, n_v, sc);
+hipError_t launch_pcg_iteration(const Ctx &c, T *x, T *r, T *p, const T *q, const T *dinv, double *partial, int npq,
+                                PcgScalars *sc, hipStream_t s) {
+  const int nlv = node_levels(c), nb = node_blocks(c, nlv, nlv > 1 ? kNodeBlocks : kVecBlocks);
+  double *rz = partial + npq;   // behind the partials of p.q, which other blocks may still be reading
+  const int np = npq <= kFinPartials ? npq : 0;
+  if (np == 0) k_fin_pq<<<1, kVecThreads, 0, s>>>(partial, npq, sc);
+  with_levels(nlv, [&](auto lv) {
+    k_pcg_update<lv(), T><<<nb, kVecThreads, 0, s>>>(x, r, p, apply_result<T>(c, q), dinv, c.n_s, rz, sc, partial, np);
+  });
+  const bool fin = nb <= kFinPartials;
+  if (!fin) k_fin_rz<<<1, kVecThreads, 0, s>>>(rz, nb, sc);
+  const int nd = (int)std::min<int64_t>((c.n_v / Vec16<T>::W + kVecThreads) / kVecThreads, kVecBlocks);
+  k_pcg_dir<T><<<nd, kVecThreads, 0, s>>>(p, r, dinv, c.n_v, sc, rz, fin ? nb : 0);
   return hipGetLastError();
 }
-template hipError_t launch_pcg_dir<double>(double *, const double *, const double *, int64_t, PcgScalars *,
-                                           hipStream_t);
-template hipError_t launch_pcg_dir<float>(float *, const float *, const float *, int64_t, PcgScalars *, hipStream_t);
+template hipError_t launch_pcg_iteration<double>(const Ctx &, double *, double *, double *, const double *,
+                                                 const double *, double *, int, PcgScalars *, hipStream_t);
+template hipError_t launch_pcg_iteration<float>(const Ctx &, float *, float *, float *, const float *,
+                                                const float *, double *, int, PcgScalars *, hipStream_t);
 
 hipError_t launch_add_f32(double *x, const float *d, int64_t n_v, hipStream_t s) {
   k_add_f32<<<kVecBlocks, kVecThreads, 0, s>>>(x, d, n_v);

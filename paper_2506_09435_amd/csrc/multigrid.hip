@@ -18,13 +18,16 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdint>
 #include <cstring>
 #include <utility>
 #include <vector>
 
+#include "deferred.h"
 #include "fnpf_internal.h"
+#include "reduce.h"
 
 namespace fnpf {
 
@@ -135,29 +138,24 @@ __global__ __launch_bounds__(256) void k_mg_surf(const double *__restrict__ Hf, 
   hc[n] = sh;
 }
 
-// Restriction b_c = P^T (r_f - q_f) (q_f = NULL: P^T r_f).  One thread per (column, fine
+// Restriction b_c = P^T (r_f - q_f) (q_f.y = NULL: P^T r_f).  One thread per (column, fine
 // horizontal node) loads its fine line (owner columns only; the shared layer level counts in the
 // upper layer) and contracts it vertically in registers; the horizontal contraction is split in
 // two LDS stages over all threads of the column: (a, j, c) sums over i, then (a, b, c) over j.
-// Coarse nodes owned by the column go to b_c, the others to the coarse face slots (summed by the
-// coarse level's face pass); the coarse surface level is set to zero.  The vertical carry of the
+// q_f comes straight from the apply's first pass and is assembled here.  blockIdx.y takes a chunk of
+// lpc layers.  Coarse nodes owned by the column go to b_c, the others to the coarse face slots, and
+// a chunk's top level below the next chunk behind them (deferred.h: the coarse level's first kernel
+// adds them); the coarse surface level is set to zero.  The vertical carry of the
 // shared layer level passes through a double-buffered LDS slot per coarse horizontal node.
-// waves per SIMD the restriction is compiled for: six for the FP64 p = 6 -> 3 transfer (at most 80
-// VGPRs; the compiler's own choice lands just above and leaves five), else the compiler's choice
-template <int PF, typename T>
-struct RestrictWaves {
-  static constexpr int v = (PF == 6 && sizeof(T) == 8) ? 6 : 1;
-};
-
 template <int PF, int DIM, typename T>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(RestrictWaves<PF, T>::v))) void k_restrict(const T *__restrict__ rf, const T *__restrict__ qf,
+__global__ __launch_bounds__(256) void k_restrict(const T *__restrict__ rf, Deferred<T> qf,
                                                   T *__restrict__ bc, T *__restrict__ Fc,
                                                   const int32_t *__restrict__ nodes_f,
                                                   const uint8_t *__restrict__ flags_f,
                                                   const int32_t *__restrict__ nodes_c,
                                                   const uint8_t *__restrict__ flags_c,
                                                   const int32_t *__restrict__ slot_c, int ncols, int nz,
-                                                  int64_t ns_f, int64_t ns_c, int64_t nslots_c,
+                                                  int64_t ns_f, int64_t ns_c, int64_t nslots_c, int lpc,
                                                   const int32_t *__restrict__ skip) {
   using LF = Lay<PF, DIM>;
   constexpr int PC = PF / 2, N1F = PF + 1, N1C = PC + 1;
@@ -176,6 +174,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(RestrictWav
   const int col = active ? ci : 0;
   const int hn = active ? nodes_f[col * NHF + t] : 0;
   const bool own = active && (flags_f[col * NHF + t] & kOwned);
+  const int chunk = blockIdx.y, nchunk = gridDim.y, l0 = chunk * lpc, l1 = min(l0 + lpc, nz);
+  int4 sl = make_int4(-1, -1, -1, 0);
+  if (own && hn < qf.n_hi) sl = qf.slots[hn];
   T *W = sW + lc * N1C * NHF;
   T *A = sA + lc * NA;
   T *Cr = sC + lc * 2 * NHC;
@@ -194,7 +195,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(RestrictWav
   }
   // the fine line of layer l + 1 is loaded while layer l is contracted (raw values of both
   // operands, so that nothing waits for them before their use)
-  T nr[N1F], nq[N1F];
+  T nr[N1F], nq[N1F], nf[N1F];
   auto load_layer = [&](int l) {
     const int kmax = (l == nz - 1) ? N1F : PF;
 #pragma unroll
@@ -202,15 +203,36 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(RestrictWav
       const int64_t idx = (int64_t)(l * PF + k) * ns_f + hn;
       const bool ld = own && k < kmax;
       nr[k] = ld ? rf[idx] : T(0);
-      nq[k] = (ld && qf) ? qf[idx] : T(0);
+      nq[k] = (ld && qf.y) ? qf.y[idx] : T(0);
+      nf[k] = (sl.x >= 0 && k < PF) ? qf.F[(int64_t)(l * PF + k) * qf.n_slots + sl.x] : T(0);
     }
   };
-  load_layer(0);
-  for (int l = 0; l < nz; ++l) {
+  load_layer(l0);
+  for (int l = l0; l < l1; ++l) {
     T rv[N1F];
 #pragma unroll
-    for (int k = 0; k < N1F; ++k) rv[k] = nr[k] - nq[k];
-    if (l + 1 < nz) load_layer(l + 1);
+    for (int k = 0; k < N1F; ++k) rv[k] = nr[k] - (nq[k] + nf[k]);
+    // the rest of q: further face slots, and at the bottom of a chunk of the apply the lower chunk's value
+    auto more = [&](int s) {
+      const T *f = qf.F + (int64_t)(l * PF) * qf.n_slots + s;
+#pragma unroll
+      for (int k = 0; k < PF; ++k) rv[k] -= f[k * qf.n_slots];
+    };
+    if (sl.y >= 0) more(sl.y);
+    if (sl.z >= 0) more(sl.z);
+    if (sl.w > 0)
+      for (int q = 1; q <= qf.lists[sl.w]; ++q) more(qf.lists[sl.w + q]);
+    if (qf.nchunk > 1 && l > 0 && (l * PF) % qf.clev == 0 && own) {
+      const int c = l * PF / qf.clev - 1;
+      const T *top = qf.F + (int64_t)(qf.nlev + c) * qf.n_slots;
+      T z = (qf.F + (int64_t)(qf.nlev + qf.nchunk - 1) * qf.n_slots)[c * ns_f + hn];
+      if (sl.x >= 0) z += top[sl.x];
+      if (sl.y >= 0) z += top[sl.y];
+      if (sl.z >= 0) z += top[sl.z];
+      if (sl.w > 0) z = list_sum(qf, top, sl.w, z);
+      rv[0] -= z;
+    }
+    if (l + 1 < l1) load_layer(l + 1);
     T w[N1C];
 #pragma unroll
     for (int c = 0; c < N1C; ++c) w[c] = T(0);
@@ -249,32 +271,41 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(RestrictWav
 #pragma unroll
         for (int i = 0; i < N1F; ++i) acc += ip<T>(PF, i * N1C + a) * W[c * NHF + i];
       }
-      if (c == 0 && l > 0) acc += Cr[((l - 1) & 1) * NHC + h];
-      if (c == PC && l < nz - 1) {
+      if (c == 0 && l > l0) acc += Cr[((l - 1) & 1) * NHC + h];
+      if (c == PC && l < l1 - 1) {
         Cr[(l & 1) * NHC + h] = acc;                   // the shared layer level, finished above
         continue;
       }
       const int v = l * PC + c;
+      const bool below = c == PC && l1 < nz;           // the next chunk's bottom level
       int d = dst[0];   // dst[m] by selects (constant indices keep dst in registers)
 #pragma unroll
       for (int q = 1; q < MI; ++q)
         if (m == q) d = dst[q];
-      if (d >= 0)
+      if (below) {
+        if (d >= 0)
+          (Fc + (int64_t)(vtop + nchunk) * nslots_c)[chunk * ns_c + d] = acc;
+        else
+          Fc[(int64_t)(vtop + 1 + chunk) * nslots_c + (-1 - d)] = acc;
+      } else if (d >= 0) {
         bc[(int64_t)v * ns_c + d] = (v == vtop) ? T(0) : acc;
-      else if (v != vtop)
+      } else if (v != vtop) {
         Fc[(int64_t)v * nslots_c + (-1 - d)] = acc;
+      }
     }
     __syncthreads();
   }
 }
 
-// Prolongation x_f += P x_c, written by the owner column of each fine node.
+// Prolongation x_f += P x_c, written by the owner column of each fine node; blockIdx.y takes a chunk
+// of lpc layers.
 template <int PF, int DIM, typename T>
 __global__ __launch_bounds__(256) void k_prolong_add(const T *__restrict__ xc, T *__restrict__ xf,
                                                      const int32_t *__restrict__ nodes_f,
                                                      const uint8_t *__restrict__ flags_f,
                                                      const int32_t *__restrict__ nodes_c, int ncols, int nz,
-                                                     int64_t ns_f, int64_t ns_c, const int32_t *__restrict__ skip) {
+                                                     int64_t ns_f, int64_t ns_c, int lpc,
+                                                     const int32_t *__restrict__ skip) {
   using LF = Lay<PF, DIM>;
   constexpr int PC = PF / 2, N1F = PF + 1, N1C = PC + 1;
   constexpr int NHF = LF::NH, CPB = LF::CPB, NHC = Lay<PC, DIM>::NH;
@@ -298,8 +329,9 @@ __global__ __launch_bounds__(256) void k_prolong_add(const T *__restrict__ xc, T
 #pragma unroll
     for (int c = 0; c < N1C; ++c) xn[c] = cthr ? xc[(int64_t)(l * PC + c) * ns_c + hnc] : T(0);
   };
-  load_coarse(0);
-  for (int l = 0; l < nz; ++l) {
+  const int l0 = blockIdx.y * lpc, l1 = min(l0 + lpc, nz);
+  load_coarse(l0);
+  for (int l = l0; l < l1; ++l) {
     const int kend = (l == nz - 1) ? N1F : PF;
     T old[N1F];
 #pragma unroll
@@ -308,7 +340,7 @@ __global__ __launch_bounds__(256) void k_prolong_add(const T *__restrict__ xc, T
 #pragma unroll
       for (int c = 0; c < N1C; ++c) X[c * NHC + t] = xn[c];
     }
-    if (l + 1 < nz) load_coarse(l + 1);
+    if (l + 1 < l1) load_coarse(l + 1);
     __syncthreads();
     if (own) {
       T w[N1C];
@@ -340,170 +372,150 @@ __global__ __launch_bounds__(256) void k_prolong_add(const T *__restrict__ xc, T
 
 // ---- vector kernels (grid-stride, fixed grid, deterministic partials) -----------------------
 
-__device__ __forceinline__ double wsum(double v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
-}
-
-template <int NS>
-__device__ __forceinline__ void block_partials(double (&v)[NS], double *partial) {
-  constexpr int NW = kVecThreads / 64;
-  __shared__ double s[NS][NW];
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-#pragma unroll
-  for (int k = 0; k < NS; ++k) {
-    double r = wsum(v[k]);
-    if (lane == 0) s[k][wv] = r;
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-#pragma unroll
-    for (int k = 0; k < NS; ++k) {
-      double a = 0.0;
-      for (int w = 0; w < NW; ++w) a += s[k][w];
-      partial[blockIdx.x * NS + k] = a;
-    }
-  }
-}
-
-template <int NS>
-__device__ __forceinline__ void final_sums(const double *partial, int np, double (&out)[NS]) {
-  __shared__ double s[NS][kVecThreads];
-  double a[NS];
-#pragma unroll
-  for (int k = 0; k < NS; ++k) a[k] = 0.0;
-  for (int b = threadIdx.x; b < np; b += kVecThreads)
-#pragma unroll
-    for (int k = 0; k < NS; ++k) a[k] += partial[b * NS + k];
-#pragma unroll
-  for (int k = 0; k < NS; ++k) s[k][threadIdx.x] = a[k];
-  __syncthreads();
-  for (int w = kVecThreads / 2; w > 0; w >>= 1) {
-    if ((int)threadIdx.x < w)
-#pragma unroll
-      for (int k = 0; k < NS; ++k) s[k][threadIdx.x] += s[k][threadIdx.x + w];
-    __syncthreads();
-  }
-#pragma unroll
-  for (int k = 0; k < NS; ++k) out[k] = s[k][0];
-}
-
 #define GRID_STRIDE(i, n) \
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < (n); i += (int64_t)gridDim.x * blockDim.x)
 
-// first Chebyshev step from x = 0: r = b, d = c dinv b, x = d
+// The smoothing kernels below read operator products (and restricted right-hand sides) as the
+// apply's first pass (the restriction) left them and add the face slots themselves (deferred.h).
+
 template <typename T>
-__global__ __launch_bounds__(kVecThreads) void k_cheb0(const T *b, T *r, T *d, T *x, const T *dinv,
-                                                       const double *cf, int64_t n, const int32_t *skip) {
-  if (skip != nullptr && *skip) return;
+struct L1 { T a; };
+template <typename T>
+struct L2 { T a, b; };
+template <typename T>
+struct L3 { T a, b, c; };
+template <typename T>
+struct L4 { T a, b, c, d; };
+
+// first Chebyshev step from x = 0: r = b, d = c dinv b, x = d; a deferred b is completed in bw
+template <int LV, typename T>
+__global__ __launch_bounds__(kVecThreads) void k_cheb0(Deferred<T> b, T *bw, T *r, T *d, T *x, const T *dinv,
+                                                       const double *cf, int64_t n_s, const int32_t *skip) {
   const T c = (T)cf[0];
-  GRID_STRIDE(i, n) {
-    const T bi = b[i];
-    const T di = c * dinv[i] * bi;
-    r[i] = bi;
-    d[i] = di;
-    x[i] = di;
-  }
+  for_nodes<LV>(b, n_s, skip, [&](int64_t i) { return L1<T>{dinv[i]}; },
+            [&](int64_t i, const L1<T> &l, T bi) {
+              const T di = c * l.a * bi;
+              if (bw != nullptr) bw[i] = bi;
+              r[i] = bi;
+              d[i] = di;
+              x[i] = di;
+            });
 }
 
 // first Chebyshev step from x: r = b - q (q = A x), d = c dinv r, x += d
-template <typename T>
-__global__ __launch_bounds__(kVecThreads) void k_cheb1(const T *b, const T *q, T *r, T *d, T *x, const T *dinv,
-                                                       const double *cf, int64_t n, const int32_t *skip) {
-  if (skip != nullptr && *skip) return;
+template <int LV, typename T>
+__global__ __launch_bounds__(kVecThreads) void k_cheb1(const T *b, Deferred<T> q, T *r, T *d, T *x, const T *dinv,
+                                                       const double *cf, int64_t n_s, const int32_t *skip) {
   const T c = (T)cf[0];
-  GRID_STRIDE(i, n) {
-    const T ri = b[i] - q[i];
-    const T di = c * dinv[i] * ri;
-    r[i] = ri;
-    d[i] = di;
-    x[i] += di;
-  }
+  for_nodes<LV>(q, n_s, skip, [&](int64_t i) { return L3<T>{b[i], dinv[i], x[i]}; },
+            [&](int64_t i, const L3<T> &l, T qi) {
+              const T ri = l.a - qi;
+              const T di = c * l.b * ri;
+              r[i] = ri;
+              d[i] = di;
+              x[i] = l.c + di;
+            });
 }
 
 // later steps: r -= q (q = A d), d = c1 d + c2 dinv r, x += d
-template <typename T>
-__global__ __launch_bounds__(kVecThreads) void k_cheb_step(T *r, const T *q, T *d, T *x, const T *dinv,
-                                                           const double *cf, int k, int64_t n,
+template <int LV, typename T>
+__global__ __launch_bounds__(kVecThreads) void k_cheb_step(T *r, Deferred<T> q, T *d, T *x, const T *dinv,
+                                                           const double *cf, int k, int64_t n_s,
                                                            const int32_t *skip) {
-  if (skip != nullptr && *skip) return;
   const T c1 = (T)cf[3 + 2 * (k - 2)], c2 = (T)cf[4 + 2 * (k - 2)];
-  GRID_STRIDE(i, n) {
-    const T ri = r[i] - q[i];
-    const T di = c1 * d[i] + c2 * dinv[i] * ri;
-    r[i] = ri;
-    d[i] = di;
-    x[i] += di;
-  }
+  for_nodes<LV>(q, n_s, skip, [&](int64_t i) { return L4<T>{r[i], d[i], dinv[i], x[i]}; },
+            [&](int64_t i, const L4<T> &l, T qi) {
+              const T ri = l.a - qi;
+              const T di = c1 * l.b + c2 * l.c * ri;
+              r[i] = ri;
+              d[i] = di;
+              x[i] = l.d + di;
+            });
 }
 
 // Two-step smoothing written out (the default degree): with d1 = c0 D^-1 r0 and
 // d2 = c1 d1 + c2 D^-1 (r0 - A d1), x2 = x0 + a1 d1 + a2 D^-1 (r0 - A d1) (a1 = 1 + c1, a2 = c2)
-// = x0 + D^-1 ((a1 c0 + a2) r0 - a2 A d1): d1 is needed only as the input of its product, and
-// no residual or step vector survives it.
-//   y = c dinv b
-template <typename T>
-__global__ __launch_bounds__(kVecThreads) void k_scale(T *y, const T *b, const T *dinv, const double *cf, int64_t n,
-                                                       const int32_t *skip) {
-  if (skip != nullptr && *skip) return;
+// = x0 + D^-1 ((a1 c0 + a2) r0 - a2 A d1) = x0 + (a1 + a2 / c0) d1 - a2 D^-1 A d1: no residual or
+// step vector survives it.
+//   y = c dinv b; a deferred b is completed in bw
+template <int LV, typename T>
+__global__ __launch_bounds__(kVecThreads) void k_scale(T *y, Deferred<T> b, T *bw, const T *dinv, const double *cf,
+                                                       int64_t n_s, const int32_t *skip) {
   const T c = (T)cf[0];
-  GRID_STRIDE(i, n) y[i] = c * dinv[i] * b[i];
+  for_nodes<LV>(b, n_s, skip, [&](int64_t i) { return L1<T>{dinv[i]}; },
+            [&](int64_t i, const L1<T> &l, T bi) {
+              if (bw != nullptr) bw[i] = bi;
+              y[i] = c * l.a * bi;
+            });
 }
 
 //   from zero: x = dinv ((a1 c0 + a2) b - a2 q), q = A d1
-template <typename T>
-__global__ __launch_bounds__(kVecThreads) void k_pre2(T *x, const T *b, const T *q, const T *dinv,
-                                                      const double *cf, int64_t n, const int32_t *skip) {
-  if (skip != nullptr && *skip) return;
+template <int LV, typename T>
+__global__ __launch_bounds__(kVecThreads) void k_pre2(T *x, const T *b, Deferred<T> q, const T *dinv,
+                                                      const double *cf, int64_t n_s, const int32_t *skip) {
   const T e = (T)(cf[1] * cf[0] + cf[2]), a2 = (T)cf[2];
-  GRID_STRIDE(i, n) x[i] = dinv[i] * (e * b[i] - a2 * q[i]);
+  for_nodes<LV>(q, n_s, skip, [&](int64_t i) { return L2<T>{b[i], dinv[i]}; },
+            [&](int64_t i, const L2<T> &l, T qi) { x[i] = l.b * (e * l.a - a2 * qi); });
 }
 
 //   from x: d1 = c dinv (b - q1), q1 = A x
-template <typename T>
-__global__ __launch_bounds__(kVecThreads) void k_post2a(T *d, const T *b, const T *q1, const T *dinv,
-                                                        const double *cf, int64_t n, const int32_t *skip) {
-  if (skip != nullptr && *skip) return;
+template <int LV, typename T>
+__global__ __launch_bounds__(kVecThreads) void k_post2a(T *d, const T *b, Deferred<T> q1, const T *dinv,
+                                                        const double *cf, int64_t n_s, const int32_t *skip) {
   const T c = (T)cf[0];
-  GRID_STRIDE(i, n) d[i] = c * dinv[i] * (b[i] - q1[i]);
+  for_nodes<LV>(q1, n_s, skip, [&](int64_t i) { return L2<T>{b[i], dinv[i]}; },
+            [&](int64_t i, const L2<T> &l, T qi) { d[i] = c * l.b * (l.a - qi); });
 }
 
-//   x += dinv ((a1 c0 + a2) (b - q1) - a2 q2), q1 = A x, q2 = A d1
+//   x += (a1 + a2 / c0) d1 - a2 dinv q2, q2 = A d1 (without b - q1, so q1 needs no assembly in memory)
 // DOT: also the block partials of b.x (the CG's r.z when b is the residual and x the V-cycle's
-// result), in the order k_dot takes them, so the sum is the same bit for bit
-template <typename T, bool DOT>
-__global__ __launch_bounds__(kVecThreads) void k_post2b(T *x, const T *b, const T *q1, const T *q2,
-                                                        const T *dinv, const double *cf, int64_t n,
+// result)
+template <int LV, typename T, bool DOT>
+__global__ __launch_bounds__(kVecThreads) void k_post2b(T *x, const T *b, const T *d, Deferred<T> q2,
+                                                        const T *dinv, const double *cf, int64_t n_s,
                                                         const int32_t *skip, double *partial) {
-  if (skip != nullptr && *skip) return;
-  const T e = (T)(cf[1] * cf[0] + cf[2]), a2 = (T)cf[2];
+  const T e = (T)(cf[1] + cf[2] / cf[0]), a2 = (T)cf[2];
+  const int dn = skip != nullptr ? *skip : 0;
   double v[1] = {0.0};
-  GRID_STRIDE(i, n) {
-    const T xi = x[i] + dinv[i] * (e * (b[i] - q1[i]) - a2 * q2[i]);
-    x[i] = xi;
-    if constexpr (DOT) v[0] += (double)b[i] * (double)xi;
+  for_nodes<LV>(q2, n_s, [&](int64_t i) { return L4<T>{x[i], d[i], dinv[i], DOT ? b[i] : T(0)}; },
+            [&] { return dn == 0; },
+            [&](int64_t i, const L4<T> &l, T qi) {
+              const T xi = l.a + (e * l.b - a2 * l.c * qi);
+              x[i] = xi;
+              if constexpr (DOT) v[0] += (double)l.d * (double)xi;
+            });
+  if constexpr (DOT) {
+    if (dn == 0) block_partials<1>(v, partial);
   }
-  if constexpr (DOT) block_partials<1>(v, partial);
 }
 
 // PCG with a general preconditioner: x += alpha p, r -= alpha q; partial r.r.  SCALE: also the
-// first step of the degree-2 V-cycle that follows on the new residual, d = c0 dinv r.
-template <typename T, bool SCALE>
-__global__ __launch_bounds__(kVecThreads) void k_mg_update(T *x, T *r, const T *p, const T *q, int64_t n,
-                                                           double *partial, const PcgScalars *sc, T *d,
-                                                           const T *dinv, const double *cf) {
-  if (sc->done) return;
-  const T a = (T)sc->alpha;
+// first step of the degree-2 V-cycle that follows on the new residual, d = c0 dinv r.  np > 0: alpha
+// from the np partials of p.q (cg_alpha), else as k_fin_pq left it.
+template <int LV, typename T, bool SCALE>
+__global__ __launch_bounds__(kVecThreads) void k_mg_update(T *x, T *r, const T *p, Deferred<T> q, int64_t n_s,
+                                                           double *partial, PcgScalars *sc, T *d, const T *dinv,
+                                                           const double *cf, const double *pq, int np) {
   const T c0 = SCALE ? (T)cf[0] : T(0);
+  const int dn = sc->done;
+  const double rz = sc->rz2, alpha = sc->alpha;
+  const PartialLoads<1> pv(pq, np);
+  T a = T(0);
   double v[1] = {0.0};
-  GRID_STRIDE(i, n) {
-    x[i] += a * p[i];
-    const T ri = r[i] - a * q[i];
-    r[i] = ri;
-    if constexpr (SCALE) d[i] = c0 * dinv[i] * ri;
-    v[0] += (double)ri * (double)ri;
-  }
+  for_nodes<LV>(q, n_s, [&](int64_t i) { return L4<T>{x[i], r[i], p[i], SCALE ? dinv[i] : T(0)}; },
+            [&] {
+              if (dn) return false;
+              a = (T)(np > 0 ? cg_alpha(pv, rz, sc) : alpha);
+              return true;
+            },
+            [&](int64_t i, const L4<T> &l, T qi) {
+              x[i] = l.a + a * l.c;
+              const T ri = l.b - a * qi;
+              r[i] = ri;
+              if constexpr (SCALE) d[i] = c0 * l.d * ri;
+              v[0] += (double)ri * (double)ri;
+            });
+  if (dn) return;
   block_partials<1>(v, partial);
 }
 
@@ -534,27 +546,61 @@ __global__ __launch_bounds__(kVecThreads) void k_dot(const T *a, const T *b, int
 
 // beta = (r.z)_new / (r.z)_old (first: beta = 0); a non-positive r.z means the preconditioner
 // is not positive definite on this residual
+__device__ __forceinline__ void cg_store_rz(PcgScalars *sc, double rz, double beta) {
+  sc->beta = beta;
+  sc->rz2 = rz;
+  if (!(rz > 0.0) || !(rz <= 1e300)) {
+    sc->breakdown = (rz == rz) ? 1 : 2;
+    sc->done = 1;
+  }
+}
+
 __global__ __launch_bounds__(kVecThreads) void k_mg_fin_rz(const double *partial, int np, PcgScalars *sc,
                                                            int first) {
   if (sc->done) return;
   double s[1];
   final_sums<1>(partial, np, s);
-  if (threadIdx.x == 0) {
-    sc->beta = first ? 0.0 : s[0] / sc->rz;
-    sc->rz = s[0];
-    if (!(s[0] > 0.0) || !(s[0] <= 1e300)) {
-      sc->breakdown = (s[0] == s[0]) ? 1 : 2;
-      sc->done = 1;
-    }
-  }
+  if (threadIdx.x == 0) cg_store_rz(sc, s[0], first ? 0.0 : s[0] / sc->rz);
 }
 
+// p = z + beta p.  np > 0: beta from the np partials of r.z (every block sums them; the first one
+// stores what the next kernels read), else as k_mg_fin_rz left it.
 template <typename T>
-__global__ __launch_bounds__(kVecThreads) void k_mg_dir(T *p, const T *z, int64_t n, const PcgScalars *sc,
-                                                        int first) {
-  if (sc->done) return;
-  const T b = (T)sc->beta;
-  GRID_STRIDE(i, n) p[i] = first ? z[i] : z[i] + b * p[i];
+__global__ __launch_bounds__(kVecThreads) void k_mg_dir(T *p, const T *z, int64_t n, PcgScalars *sc, int first,
+                                                        const double *partial, int np) {
+  const int dn = sc->done;
+  const double rz = sc->rz, beta0 = sc->beta;
+  const PartialLoads<1> pv(partial, np);
+  int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+  T z0 = T(0), p0 = T(0);
+  if (i < n) {
+    z0 = z[i];
+    if (!first) p0 = p[i];
+  }
+  asm volatile("" ::: "memory");   // the first loads stay ahead of the test
+  if (dn) return;
+  double beta;
+  if (np > 0) {
+    double s[1];
+    pv.sums(s);
+    beta = first ? 0.0 : s[0] / rz;
+    if (blockIdx.x == 0 && threadIdx.x == 0) cg_store_rz(sc, s[0], beta);
+  } else {
+    beta = beta0;
+  }
+  const T b = (T)beta;
+  const int64_t st = (int64_t)gridDim.x * blockDim.x;
+  for (; i < n; i += st) {
+    const int64_t i2 = i + st;
+    T z1 = T(0), p1 = T(0);
+    if (i2 < n) {
+      z1 = z[i2];
+      if (!first) p1 = p[i2];
+    }
+    p[i] = first ? z0 : z0 + b * p0;
+    z0 = z1;
+    p0 = p1;
+  }
 }
 
 // Largest eigenvalue of D^-1 A.  D^-1 A is self-adjoint in <u, v>_D = sum u_i v_i / dinv_i over
@@ -706,22 +752,28 @@ hipError_t dalloc_t(T **p, size_t n) {
     default: return hipErrorInvalidValue;              \
   }
 
+// layers per block of the transfers: the finer level's, and at most as many chunks as the coarse
+// level's face buffer has room for
+int transfer_lpc(const Ctx &F, const Ctx &C) { return std::max(F.lpc, C.lpc); }
+
 template <int PF, int DIM, typename T>
-hipError_t restrict_impl(Ctx &F, Ctx &C, const T *rf, const T *qf, T *bc, T *Fc, const int32_t *skip,
+hipError_t restrict_impl(Ctx &F, Ctx &C, const T *rf, const Deferred<T> &qf, T *bc, T *Fc, const int32_t *skip,
                          hipStream_t s) {
   using LF = Lay<PF, DIM>;
-  const int nb = (F.n_eh + LF::CPB - 1) / LF::CPB;
+  const int lpc = transfer_lpc(F, C);
+  const dim3 nb((F.n_eh + LF::CPB - 1) / LF::CPB, (F.nz + lpc - 1) / lpc);
   k_restrict<PF, DIM, T><<<nb, LF::NT, 0, s>>>(rf, qf, bc, Fc, F.d_eh_nodes, F.d_flags, C.d_eh_nodes, C.d_flags,
-                                               C.d_slot, F.n_eh, F.nz, F.n_s, C.n_s, C.n_slots, skip);
+                                               C.d_slot, F.n_eh, F.nz, F.n_s, C.n_s, C.n_slots, lpc, skip);
   return hipGetLastError();
 }
 
 template <int PF, int DIM, typename T>
 hipError_t prolong_impl(Ctx &F, Ctx &C, const T *xc, T *xf, const int32_t *skip, hipStream_t s) {
   using LF = Lay<PF, DIM>;
-  const int nb = (F.n_eh + LF::CPB - 1) / LF::CPB;
+  const int lpc = transfer_lpc(F, C);
+  const dim3 nb((F.n_eh + LF::CPB - 1) / LF::CPB, (F.nz + lpc - 1) / lpc);
   k_prolong_add<PF, DIM, T><<<nb, LF::NT, 0, s>>>(xc, xf, F.d_eh_nodes, F.d_flags, C.d_eh_nodes, F.n_eh, F.nz,
-                                                  F.n_s, C.n_s, skip);
+                                                  F.n_s, C.n_s, lpc, skip);
   return hipGetLastError();
 }
 
@@ -734,16 +786,27 @@ hipError_t surf_impl(Ctx &F, Ctx &C, double *Hc, double *hc, hipStream_t s) {
   return hipGetLastError();
 }
 
+// b_c = P^T (r_f - q_f), its assembly left to the reader
 template <typename T>
-hipError_t restrict_to(Ctx &F, Ctx &C, const T *rf, const T *qf, T *bc, const int32_t *skip, hipStream_t s) {
-  T *Fc = nullptr;
-  if constexpr (sizeof(T) == 8) Fc = (T *)C.d_F64; else Fc = (T *)C.d_F32;
+hipError_t restrict_to(Ctx &F, Ctx &C, const T *rf, const Deferred<T> &qf, T *bc, Deferred<T> &out, const int32_t *skip,
+                       hipStream_t s) {
+  T *Fc = face_buffer<T>(C);
   if (F.dim == 3) {
     MG_DISPATCH(3, F.p, { hipError_t e = (restrict_impl<PF_, 3, T>(F, C, rf, qf, bc, Fc, skip, s)); if (e != hipSuccess) return e; });
   } else {
     MG_DISPATCH(2, F.p, { hipError_t e = (restrict_impl<PF_, 2, T>(F, C, rf, qf, bc, Fc, skip, s)); if (e != hipSuccess) return e; });
   }
-  return launch_faces(C, Prec<T>::dt, bc, true, s, skip);
+  out = complete<T>(C, bc);
+  out.F = Fc;
+  out.slots = C.d_p_slots;
+  out.lists = C.d_p_lists;
+  out.n_hi = C.p_n_hi;
+  out.n_slots = C.n_slots;
+  out.vend = out.nlev - 1;
+  const int lpc = transfer_lpc(F, C);
+  out.clev = lpc * C.p;
+  out.nchunk = (F.nz + lpc - 1) / lpc;
+  return hipSuccess;
 }
 
 template <typename T>
@@ -810,20 +873,31 @@ __global__ void k_set_scalar(double *p, double v) {
   if (threadIdx.x == 0 && blockIdx.x == 0) *p = v;
 }
 
+// blocks of the (level, node) kernels that write partials
+template <typename T>
+int partial_blocks(const Ctx &L) {
+  return node_blocks(L, node_levels(L), node_levels(L) > 1 ? kNodeBlocks : kVB<T>);
+}
+
 // Chebyshev smoothing of A x = b on level L (D^-1 A spectrum estimate lam), m steps.  From zero:
 // x = p(D^-1 A) D^-1 b; otherwise x += p(D^-1 A) D^-1 (b - A x).  On return r = b - A x_{m-1}
-// and d = x_m - x_{m-1}.
+// and d = x_m - x_{m-1}.  A deferred b (from zero only) is completed in place.
 // line: B^-1 (the level's vertical line blocks, line_smoother.hip) in place of D^-1.
 template <typename T>
-hipError_t smooth(Ctx &L, const T *b, T *x, T *r, T *d, T *q, const double *cf, int m, bool from_zero,
+hipError_t smooth(Ctx &L, const Deferred<T> &b, T *x, T *r, T *d, T *q, const double *cf, int m, bool from_zero,
                   const int32_t *skip, hipStream_t s, bool line = false) {
+  const int64_t ns = L.n_s;
+  const int nlv = node_levels(L), nb = node_blocks(L, nlv);
+  T *bw = b.F != nullptr ? const_cast<T *>(b.y) : nullptr;
   if (line) {
     hipError_t e = hipSuccess;
     if (from_zero) {
-      e = line_cheb0<T>(L, b, r, d, x, cf, skip, s);
+      // the line solves read complete vectors: complete b first (r = b, the rest is overwritten)
+      if (b.F != nullptr) with_levels(nlv, [&](auto lv) { k_cheb0<lv(), T><<<nb, kVecThreads, 0, s>>>(b, bw, r, d, x, Prec<T>::dinv(L), cf, ns, skip); });
+      e = line_cheb0<T>(L, b.y, r, d, x, cf, skip, s);
     } else {
       if ((e = launch_apply(L, Prec<T>::dt, x, q, true, nullptr, skip, s)) != hipSuccess) return e;
-      e = line_cheb1<T>(L, b, q, r, d, x, cf, skip, s);
+      e = line_cheb1<T>(L, b.y, q, r, d, x, cf, skip, s);
     }
     for (int k = 2; k <= m && e == hipSuccess; ++k) {
       if ((e = launch_apply(L, Prec<T>::dt, d, q, true, nullptr, skip, s)) != hipSuccess) return e;
@@ -832,26 +906,26 @@ hipError_t smooth(Ctx &L, const T *b, T *x, T *r, T *d, T *q, const double *cf, 
     return e;
   }
   const T *dinv = Prec<T>::dinv(L);
-  const int64_t n = L.n_v;
   if (from_zero) {
-    k_cheb0<T><<<kVB<T>, kVecThreads, 0, s>>>(b, r, d, x, dinv, cf, n, skip);
+    with_levels(nlv, [&](auto lv) { k_cheb0<lv(), T><<<nb, kVecThreads, 0, s>>>(b, bw, r, d, x, dinv, cf, ns, skip); });
   } else {
-    hipError_t e = launch_apply(L, Prec<T>::dt, x, q, true, nullptr, skip, s);
+    hipError_t e = launch_apply(L, Prec<T>::dt, x, q, true, nullptr, skip, s, nullptr, true);
     if (e != hipSuccess) return e;
-    k_cheb1<T><<<kVB<T>, kVecThreads, 0, s>>>(b, q, r, d, x, dinv, cf, n, skip);
+    with_levels(nlv, [&](auto lv) { k_cheb1<lv(), T><<<nb, kVecThreads, 0, s>>>(b.y, apply_result<T>(L, q), r, d, x, dinv, cf, ns, skip); });
   }
   for (int k = 2; k <= m; ++k) {
-    hipError_t e = launch_apply(L, Prec<T>::dt, d, q, true, nullptr, skip, s);
+    hipError_t e = launch_apply(L, Prec<T>::dt, d, q, true, nullptr, skip, s, nullptr, true);
     if (e != hipSuccess) return e;
-    k_cheb_step<T><<<kVB<T>, kVecThreads, 0, s>>>(r, q, d, x, dinv, cf, k, n, skip);
+    with_levels(nlv, [&](auto lv) { k_cheb_step<lv(), T><<<nb, kVecThreads, 0, s>>>(r, apply_result<T>(L, q), d, x, dinv, cf, k, ns, skip); });
   }
   return hipGetLastError();
 }
 
-// V-cycle on level l (0 = this context) for the right-hand side b, result in x.
+// V-cycle on level l (0 = this context) for the right-hand side b (completed in place where it is
+// deferred), result in x.
 // pre_scaled (level 0, degree 2): d = c0 dinv b is already in place (k_mg_update<T, true>).
 template <typename T>
-hipError_t vcycle(Ctx &c, int l, const T *b, T *x, const int32_t *skip, int m, hipStream_t s,
+hipError_t vcycle(Ctx &c, int l, const Deferred<T> &b, T *x, const int32_t *skip, int m, hipStream_t s,
                   double *dot_partial = nullptr, bool *dot_done = nullptr, bool pre_scaled = false) {
   Ctx &L = l == 0 ? c : *c.mg[l - 1].c;
   T *r, *d, *q;
@@ -870,40 +944,46 @@ hipError_t vcycle(Ctx &c, int l, const T *b, T *x, const int32_t *skip, int m, h
   if (l == last) return smooth<T>(L, b, x, r, d, q, cf, kMgCoarseSteps, true, skip, s, line);
   MgLevel &C = c.mg[l];
   T *bc = Prec<T>::lv(C)[0], *xc = Prec<T>::lv(C)[1];
-  const int64_t n = L.n_v;
+  const int64_t ns = L.n_s;
+  const int nlv = node_levels(L), nb = node_blocks(L, nlv);
   const T *dinv = Prec<T>::dinv(L);
+  Deferred<T> bd;
   hipError_t e = hipSuccess;
+  // y = A v with the assembly left to the reader
+  auto product = [&](const T *v, T *y) {
+    return launch_apply(L, Prec<T>::dt, v, y, true, nullptr, skip, s, nullptr, true);
+  };
   if (m == 2 && !line) {
-    if (!(l == 0 && pre_scaled)) k_scale<T><<<kVB<T>, kVecThreads, 0, s>>>(d, b, dinv, cf, n, skip);
-    if ((e = launch_apply(L, Prec<T>::dt, d, q, true, nullptr, skip, s)) != hipSuccess) return e;
-    k_pre2<T><<<kVB<T>, kVecThreads, 0, s>>>(x, b, q, dinv, cf, n, skip);
-    if ((e = launch_apply(L, Prec<T>::dt, x, q, true, nullptr, skip, s)) != hipSuccess) return e;
-    if ((e = restrict_to<T>(L, *C.c, b, q, bc, skip, s)) != hipSuccess) return e;   // P^T (b - A x)
-    if ((e = vcycle<T>(c, l + 1, bc, xc, skip, m, s)) != hipSuccess) return e;
+    if (!(l == 0 && pre_scaled))
+      with_levels(nlv, [&](auto lv) { k_scale<lv(), T><<<nb, kVecThreads, 0, s>>>(d, b, b.F != nullptr ? const_cast<T *>(b.y) : nullptr, dinv, cf, ns, skip); });
+    if ((e = product(d, q)) != hipSuccess) return e;
+    with_levels(nlv, [&](auto lv) { k_pre2<lv(), T><<<nb, kVecThreads, 0, s>>>(x, b.y, apply_result<T>(L, q), dinv, cf, ns, skip); });
+    if ((e = product(x, q)) != hipSuccess) return e;
+    if ((e = restrict_to<T>(L, *C.c, b.y, apply_result<T>(L, q), bc, bd, skip, s)) != hipSuccess) return e;   // P^T (b - A x)
+    if ((e = vcycle<T>(c, l + 1, bd, xc, skip, m, s)) != hipSuccess) return e;
     if ((e = prolong_to<T>(L, *C.c, xc, x, skip, s)) != hipSuccess) return e;
-    if ((e = launch_apply(L, Prec<T>::dt, x, r, true, nullptr, skip, s)) != hipSuccess) return e;
-    k_post2a<T><<<kVB<T>, kVecThreads, 0, s>>>(d, b, r, dinv, cf, n, skip);
-    if ((e = launch_apply(L, Prec<T>::dt, d, q, true, nullptr, skip, s)) != hipSuccess) return e;
+    if ((e = product(x, q)) != hipSuccess) return e;
+    with_levels(nlv, [&](auto lv) { k_post2a<lv(), T><<<nb, kVecThreads, 0, s>>>(d, b.y, apply_result<T>(L, q), dinv, cf, ns, skip); });
+    if ((e = product(d, q)) != hipSuccess) return e;
     if (dot_partial != nullptr) {
-      k_post2b<T, true><<<kVB<T>, kVecThreads, 0, s>>>(x, b, r, q, dinv, cf, n, skip, dot_partial);
+      with_levels(nlv, [&](auto lv) { k_post2b<lv(), T, true><<<partial_blocks<T>(L), kVecThreads, 0, s>>>(x, b.y, d, apply_result<T>(L, q), dinv, cf, ns, skip, dot_partial); });
       if (dot_done) *dot_done = true;
     } else {
-      k_post2b<T, false><<<kVB<T>, kVecThreads, 0, s>>>(x, b, r, q, dinv, cf, n, skip, nullptr);
+      with_levels(nlv, [&](auto lv) { k_post2b<lv(), T, false><<<nb, kVecThreads, 0, s>>>(x, b.y, d, apply_result<T>(L, q), dinv, cf, ns, skip, nullptr); });
     }
     return hipGetLastError();
   }
   e = smooth<T>(L, b, x, r, d, q, cf, m, true, skip, s, line);
   if (e != hipSuccess) return e;
   // residual of the smoothed x, r - A d, restricted directly
-  e = launch_apply(L, Prec<T>::dt, d, q, true, nullptr, skip, s);
+  if ((e = product(d, q)) != hipSuccess) return e;
+  e = restrict_to<T>(L, *C.c, r, apply_result<T>(L, q), bc, bd, skip, s);
   if (e != hipSuccess) return e;
-  e = restrict_to<T>(L, *C.c, r, q, bc, skip, s);
-  if (e != hipSuccess) return e;
-  e = vcycle<T>(c, l + 1, bc, xc, skip, m, s);
+  e = vcycle<T>(c, l + 1, bd, xc, skip, m, s);
   if (e != hipSuccess) return e;
   e = prolong_to<T>(L, *C.c, xc, x, skip, s);
   if (e != hipSuccess) return e;
-  return smooth<T>(L, b, x, r, d, q, cf, m, false, skip, s, line);
+  return smooth<T>(L, complete<T>(L, b.y), x, r, d, q, cf, m, false, skip, s, line);
 }
 
 // Eigenvalues and eigenvectors of a small symmetric matrix a[n][n] (row-major, destroyed) by
@@ -1260,7 +1340,7 @@ template <typename T>
 hipError_t mg_vcycle(Ctx &c, const T *r, T *z, const int32_t *skip, int smooth_deg, hipStream_t s,
                      double *dot_partial, bool *dot_done, bool pre_scaled) {
   if (dot_done) *dot_done = false;
-  return vcycle<T>(c, 0, r, z, skip, smooth_deg, s, dot_partial, dot_done,
+  return vcycle<T>(c, 0, complete<T>(c, r), z, skip, smooth_deg, s, dot_partial, dot_done,
                    pre_scaled && smooth_deg == 2 && !c.mg.empty() && !c.mg_line);
 }
 template hipError_t mg_vcycle<double>(Ctx &, const double *, double *, const int32_t *, int, hipStream_t, double *,
@@ -1282,46 +1362,60 @@ void mg_set_line(Ctx &c, bool line) {
   for (auto &L : c.mg) L.ev_ok64 = L.ev_ok32 = false;
 }
 
-hipError_t launch_mg_update(Ctx &c, fnpf_dtype dt, void *x, void *r, const void *p, const void *q, double *partial,
-                            PcgScalars *sc, hipStream_t s, int smooth_deg) {
-  const bool pre = mg_prescale(c, smooth_deg);
-  if (dt == FNPF_F64) {
-    if (pre)
-      k_mg_update<double, true><<<kVecBlocks, kVecThreads, 0, s>>>(
-          (double *)x, (double *)r, (const double *)p, (const double *)q, c.n_v, partial, sc,
-          Prec<double>::fv(c)[2], Prec<double>::dinv(c), coef_table<double>(c, 0));
-    else
-      k_mg_update<double, false><<<kVecBlocks, kVecThreads, 0, s>>>((double *)x, (double *)r, (const double *)p,
-                                                                    (const double *)q, c.n_v, partial, sc, nullptr,
-                                                                    nullptr, nullptr);
-  } else {
-    if (pre)
-      k_mg_update<float, true><<<kVB<float>, kVecThreads, 0, s>>>(
-          (float *)x, (float *)r, (const float *)p, (const float *)q, c.n_v, partial, sc, Prec<float>::fv(c)[2],
-          Prec<float>::dinv(c), coef_table<float>(c, 0));
-    else
-      k_mg_update<float, false><<<kVB<float>, kVecThreads, 0, s>>>((float *)x, (float *)r, (const float *)p,
-                                                                   (const float *)q, c.n_v, partial, sc, nullptr,
-                                                                   nullptr, nullptr);
+template <typename T>
+static hipError_t mg_update_impl(Ctx &c, T *x, T *r, const T *p, const T *q, double *partial, int npq, PcgScalars *sc,
+                                 hipStream_t s, bool pre) {
+  const int nb = partial_blocks<T>(c);
+  const Deferred<T> qd = apply_result<T>(c, q);
+  // the partials of r.r go behind those of p.q, which other blocks may still be reading
+  double *rr = partial + npq;
+  const int np = npq <= kFinPartials ? npq : 0;
+  if (np == 0) {
+    hipError_t e = launch_finalize_pq(partial, npq, sc, s);
+    if (e != hipSuccess) return e;
   }
-  k_mg_fin_rr<<<1, kVecThreads, 0, s>>>(partial, dt == FNPF_F64 ? kVB<double> : kVB<float>, sc);
+  with_levels(node_levels(c), [&](auto lv) {
+    if (pre)
+      k_mg_update<lv(), T, true><<<nb, kVecThreads, 0, s>>>(x, r, p, qd, c.n_s, rr, sc, Prec<T>::fv(c)[2],
+                                                            Prec<T>::dinv(c), coef_table<T>(c, 0), partial, np);
+    else
+      k_mg_update<lv(), T, false><<<nb, kVecThreads, 0, s>>>(x, r, p, qd, c.n_s, rr, sc, nullptr, nullptr, nullptr,
+                                                             partial, np);
+  });
+  k_mg_fin_rr<<<1, kVecThreads, 0, s>>>(rr, nb, sc);
+  return hipGetLastError();
+}
+
+hipError_t launch_mg_update(Ctx &c, fnpf_dtype dt, void *x, void *r, const void *p, const void *q, double *partial,
+                            int npq, PcgScalars *sc, hipStream_t s, int smooth_deg) {
+  const bool pre = mg_prescale(c, smooth_deg);
+  if (dt == FNPF_F64)
+    return mg_update_impl<double>(c, (double *)x, (double *)r, (const double *)p, (const double *)q, partial, npq, sc,
+                                  s, pre);
+  return mg_update_impl<float>(c, (float *)x, (float *)r, (const float *)p, (const float *)q, partial, npq, sc, s,
+                               pre);
+}
+
+template <typename T>
+static hipError_t mg_dot_dir_impl(Ctx &c, const T *r, const T *z, T *p, double *partial, PcgScalars *sc, int first,
+                                  hipStream_t s, bool have_partials) {
+  // the V-cycle's last kernel took the partials on its own grid
+  const int nf = (int)std::min<int64_t>((c.n_v + kVecThreads - 1) / kVecThreads, kVB<T>);
+  const int np = have_partials ? partial_blocks<T>(c) : nf;
+  if (!have_partials) k_dot<T><<<nf, kVecThreads, 0, s>>>(r, z, c.n_v, partial, sc);
+  const bool fin = np <= kFinPartials;
+  if (!fin) k_mg_fin_rz<<<1, kVecThreads, 0, s>>>(partial, np, sc, first);
+  k_mg_dir<T><<<nf, kVecThreads, 0, s>>>(p, z, c.n_v, sc, first, partial, fin ? np : 0);
   return hipGetLastError();
 }
 
 hipError_t launch_mg_dot_dir(Ctx &c, fnpf_dtype dt, const void *r, const void *z, void *p, double *partial,
                              PcgScalars *sc, int first, hipStream_t s, bool have_partials) {
-  if (!have_partials) {
-    if (dt == FNPF_F64)
-      k_dot<double><<<kVecBlocks, kVecThreads, 0, s>>>((const double *)r, (const double *)z, c.n_v, partial, sc);
-    else
-      k_dot<float><<<kVB<float>, kVecThreads, 0, s>>>((const float *)r, (const float *)z, c.n_v, partial, sc);
-  }
-  k_mg_fin_rz<<<1, kVecThreads, 0, s>>>(partial, dt == FNPF_F64 ? kVB<double> : kVB<float>, sc, first);
   if (dt == FNPF_F64)
-    k_mg_dir<double><<<kVecBlocks, kVecThreads, 0, s>>>((double *)p, (const double *)z, c.n_v, sc, first);
-  else
-    k_mg_dir<float><<<kVB<float>, kVecThreads, 0, s>>>((float *)p, (const float *)z, c.n_v, sc, first);
-  return hipGetLastError();
+    return mg_dot_dir_impl<double>(c, (const double *)r, (const double *)z, (double *)p, partial, sc, first, s,
+                                   have_partials);
+  return mg_dot_dir_impl<float>(c, (const float *)r, (const float *)z, (float *)p, partial, sc, first, s,
+                                have_partials);
 }
 
 }  // namespace fnpf

@@ -29,13 +29,13 @@ inline std::vector<PartialUse> partial_uses(int64_t colour_blocks, int64_t owner
       {"norm of b (k_bnorm)", v64, 1},
       {"PCG initial residual (k_pcg_init)", v64, 2},
       {"mixed outer residual (k_resid_to32)", v64, 3},
-      {"PCG update (k_pcg_update)", v64, 2},
       {"p-multigrid update and dots, FP64 grid", v64, 2},
       {"p-multigrid update and dots, FP32 grid", v32, 2},
       {"Lanczos and power-iteration dots, FP32 grid", v32, 2},
       {"line-smoother B-norm (k_line_bnorm), FP32 grid", v32, 1},
-      {"apply with dot product, colour schedule", colour_blocks, 1},
-      {"apply with dot product, owner-computes", owner_blocks, 1},
+      // the update after an apply puts its own partials behind the apply's
+      {"apply with dot product, colour schedule, and CG update", colour_blocks + 2 * v32, 1},
+      {"apply with dot product, owner-computes, and CG update", owner_blocks + 2 * v32, 1},
   };
 }
 

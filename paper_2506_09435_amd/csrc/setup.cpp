@@ -402,6 +402,15 @@ std::string build_host_mesh(const fnpf_mesh_desc &m, Ctx &c, std::vector<double>
       c.h_ps_ptr.push_back((int32_t)c.h_ps_slot.size());
     }
     c.n_ps = (int)c.h_ps_node.size();
+    if (dim == 2) {
+      // slices assemble without tiles: their columns' slots are the apply's
+      c.h_tslot = c.h_slot;
+      c.n_tslots = c.n_slots;
+      c.h_tps_node = c.h_ps_node;
+      c.h_tps_ptr = c.h_ps_ptr;
+      c.h_tps_slot = c.h_ps_slot;
+      c.n_tps = c.n_ps;
+    }
 
     // Tile assembly of the 3D owner-computes apply.  A tile is the tile_cols consecutive columns
     // of one workgroup; a node belongs to the tile of its owner column.  In each tile, the first

@@ -34,3 +34,22 @@ def test_split_layers(p, nx, ny, nz):
             err = ((y - ref).double().norm() / ref.double().norm()).item()
             assert err < tol, (dt, mask, err)
             assert torch.equal(y, again)
+
+
+@pytest.mark.parametrize("p,nx,nz", [(4, 8, 2), (4, 120, 3), (4, 20401, 3), (1, 130, 5), (8, 57, 2)])
+def test_slice_columns(p, nx, nz):
+    """The slices' owner-computes apply (one tile, several, ragged chunks) against the colour
+    schedule: same sums, FP64 2e-12 and FP32 2e-6 as above."""
+    wl = configs.small_slice(nx=nx, nz=nz, p=p, lx=0.25 * nx)
+    s = fnpf.setup_workload(wl, fp32=True)
+    g = torch.Generator(device="cuda").manual_seed(6)
+    x = torch.randn(s.ctx.n_v, dtype=torch.float64, device="cuda", generator=g)
+    s.ctx.geom(s.eta0, s.h)
+    for dt, tol in ((torch.float64, 2e-12), (torch.float32, 2e-6)):
+        for mask in (False, True):
+            s.ctx.set_apply_variant(0)
+            y = s.ctx.laplace_apply(x.to(dt), mask_dirichlet=mask)
+            s.ctx.set_apply_variant(7)
+            ref = s.ctx.laplace_apply(x.to(dt), mask_dirichlet=mask)
+            err = ((y - ref).double().norm() / ref.double().norm()).item()
+            assert err < tol, (dt, mask, err)
