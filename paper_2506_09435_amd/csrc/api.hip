@@ -81,6 +81,12 @@ void free_all(Ctx &c) {
   dfree(c.d_eh_nodes);
   dfree(c.d_cols);
   dfree(c.d_slot);
+  dfree(c.d_p1_nb);
+  dfree(c.d_p1_ptr);
+  dfree(c.d_p1_inc);
+  dfree(c.d_p1_map);
+  dfree(c.d_p1_val64);
+  dfree(c.d_p1_val32);
   dfree(c.d_p_slots);
   dfree(c.d_p_lists);
   dfree(c.d_F64);

@@ -83,6 +83,28 @@ __device__ __forceinline__ T list_sum(const Deferred<T> &a, const T *f, int at, 
   return q;
 }
 
+// the assembled value at one node and level
+template <typename T>
+__device__ __forceinline__ T gather_one(const Deferred<T> &a, int64_t i, int64_t n, int64_t n_s, int v) {
+  T q = a.y[i];
+  if (n >= a.n_hi && a.nchunk <= 1) return q;
+  int4 s = make_int4(-1, -1, -1, 0);
+  if (n < a.n_hi) s = a.slots[n];
+  auto add = [&](const T *row) {
+    if (s.x >= 0) q += row[s.x];
+    if (s.y >= 0) q += row[s.y];
+    if (s.z >= 0) q += row[s.z];
+    if (s.w > 0) q = list_sum(a, row, s.w, q);
+  };
+  if (v < a.vend) add(a.F + (int64_t)v * a.n_slots);
+  if (a.nchunk > 1 && v > 0 && v < a.vend && v % a.clev == 0) {
+    const int c = v / a.clev - 1;
+    q += (a.F + (int64_t)(a.nlev + a.nchunk - 1) * a.n_slots)[c * n_s + n];
+    add(a.F + (int64_t)(a.nlev + c) * a.n_slots);
+  }
+  return q;
+}
+
 // For every node n and level v, i = v n_s + n: use(i, load(i), q), q the assembled value of a (the
 // slots in increasing order, then the chunk interface's).  The loads of the next task are issued
 // before the current one is used, and those of the first before the skip flag is tested: on small

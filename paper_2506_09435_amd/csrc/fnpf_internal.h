@@ -303,6 +303,14 @@ struct Ctx {
   double *d_kbe = nullptr, *d_kbp = nullptr, *d_ybe = nullptr, *d_ybp = nullptr;
   double *d_acce = nullptr, *d_accp = nullptr, *d_wbar = nullptr, *d_zero_s = nullptr;
   bool have_adjoint = false;
+  // assembled operator of a degree-1 level that ends a multigrid hierarchy (multigrid.hip): up to
+  // p1_w neighbours per horizontal node (itself among them) on three levels
+  int p1_w = 0;
+  int32_t *d_p1_nb = nullptr;             // [p1_w][n_s] neighbour nodes (padded with the node itself)
+  int32_t *d_p1_ptr = nullptr, *d_p1_inc = nullptr;   // per node its (column, local node) entries
+  uint8_t *d_p1_map = nullptr;            // [n_eh * nh][nh] place of a column's node b among a's neighbours
+  double *d_p1_val64 = nullptr;           // [3][p1_w][n_lev][n_s]
+  float *d_p1_val32 = nullptr;
   // p-multigrid preconditioner (built on first use; the fine level is this context)
   std::vector<MgLevel> mg;
   bool mg_built = false;

@@ -387,6 +387,165 @@ struct L3 { T a, b, c; };
 template <typename T>
 struct L4 { T a, b, c, d; };
 
+// ---- the degree-1 level as an assembled operator ---------------------------------------------
+//
+// The hierarchy ends in kMgCoarseSteps Chebyshev steps on the degree-1 level, which is small (8,000
+// unknowns for the wave of 40 x 40 x 4, p = 5): two launches a step, of 4.1 and 2.9 us, were a third
+// of a solve there.  Assembled after every geometry update (27 entries a row on regular meshes) a
+// step is one launch, and levels of at most 1,024 unknowns take all steps in one workgroup.
+
+// Entry of row (v, n) for its w-th neighbour on levels v - 1, v, v + 1 (blockIdx.y = w, .z = v): the
+// sum over the columns that have both, and the two layers at v, of the element matrix entry
+// sum_q f_q (B^T grad l_row).(B^T grad l_col), collocated at the element's vertices (weights 1,
+// D = [[-1/2, 1/2], [-1/2, 1/2]]); grad l_row is nonzero only at points that share all but one
+// index with the row.
+template <int DIM, typename T>
+__global__ __launch_bounds__(256) void k_p1_matrix(const double *__restrict__ cg, const double *__restrict__ hm,
+                                                   int64_t hstride, const int32_t *__restrict__ ptr,
+                                                   const int32_t *__restrict__ inc,
+                                                   const uint8_t *__restrict__ map, int nz, int64_t n_s,
+                                                   const double *__restrict__ sigma,
+                                                   const double *__restrict__ half_ds, T *__restrict__ val) {
+  constexpr int NH = DIM == 3 ? 4 : 2;
+  const int64_t n = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+  const int w = blockIdx.y, v = blockIdx.z, nlev = gridDim.z;
+  if (n >= n_s) return;
+  double acc[3] = {0.0, 0.0, 0.0};
+  const int pe = ptr[n + 1];
+  for (int p = ptr[n]; p < pe; ++p) {
+    const int o = inc[p], a = o % NH, ai = a & 1, aj = a >> 1;   // o = column NH + a
+    int match = 0;                           // the column's nodes that are this neighbour
+#pragma unroll
+    for (int b = 0; b < NH; ++b) match |= (map[(int64_t)o * NH + b] == w ? 1 : 0) << b;
+    for (; match != 0; match &= match - 1) {
+      const int b = __ffs(match) - 1, bi = b & 1, bj = b >> 1;
+#pragma unroll
+      for (int c = 0; c < NH; ++c) {
+        const int ci = c & 1, cj = c >> 1;
+        const int64_t ho = o - a + c;
+        const double H = cg[ho], Hx = cg[hstride + ho], hx = cg[2 * hstride + ho];
+        double Hy = 0.0, hy = 0.0, A00 = hm[ho], A01 = 0.0, A10 = 0.0, A11 = 0.0, dJ;
+        if constexpr (DIM == 3) {
+          Hy = cg[3 * hstride + ho];
+          hy = cg[4 * hstride + ho];
+          A01 = hm[hstride + ho];
+          A10 = hm[2 * hstride + ho];
+          A11 = hm[3 * hstride + ho];
+          dJ = hm[4 * hstride + ho];
+        } else {
+          dJ = hm[hstride + ho];
+        }
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {        // the row's place in layer l: its bottom or its top
+          const int l = v - k;
+          if (l < 0 || l >= nz) continue;
+          const double zz = half_ds[l] * H, izz = 1.0 / zz, f = dJ * zz;
+#pragma unroll
+          for (int kq = 0; kq < 2; ++kq) {
+            const double sg = sigma[l + kq], zx = sg * Hx - hx, zy = sg * Hy - hy;
+            const double bx = -(zx * A00 + zy * A10) * izz, by = -(zx * A01 + zy * A11) * izz;
+            const double ri = cj == aj && kq == k ? (ai ? 0.5 : -0.5) : 0.0;
+            const double rj = DIM == 3 && ci == ai && kq == k ? (aj ? 0.5 : -0.5) : 0.0;
+            const double rk = c == a ? (k ? 0.5 : -0.5) : 0.0;
+            const double gx = A00 * ri + A10 * rj + bx * rk, gy = A01 * ri + A11 * rj + by * rk, gz = izz * rk;
+#pragma unroll
+            for (int k2 = 0; k2 < 2; ++k2) {
+              const double ti = cj == bj && kq == k2 ? (bi ? 0.5 : -0.5) : 0.0;
+              const double tj = DIM == 3 && ci == bi && kq == k2 ? (bj ? 0.5 : -0.5) : 0.0;
+              const double tk = c == b ? (k2 ? 0.5 : -0.5) : 0.0;
+              const double hx2 = A00 * ti + A10 * tj + bx * tk, hy2 = A01 * ti + A11 * tj + by * tk, hz2 = izz * tk;
+              acc[k2 - k + 1] += f * (gx * hx2 + gy * hy2 + gz * hz2);
+            }
+          }
+        }
+      }
+    }
+  }
+  const int64_t plane = (int64_t)nlev * n_s, i = (int64_t)v * n_s + n;
+#pragma unroll
+  for (int dv = 0; dv < 3; ++dv) val[(dv * (int64_t)gridDim.y + w) * plane + i] = (T)acc[dv];
+}
+
+// One Chebyshev step with it: q = A d, r -= q, d' = c1 d + c2 dinv r, x += d' (d' apart from d, which
+// other rows still read).  W > 0: the number of neighbours as a constant.
+template <int W, typename T>
+__global__ __launch_bounds__(256) void k_p1_step(const T *__restrict__ val, const int32_t *__restrict__ nb, int wn,
+                                                 T *__restrict__ r, const T *__restrict__ d, T *__restrict__ dn,
+                                                 T *__restrict__ x, const T *__restrict__ dinv,
+                                                 const double *__restrict__ cf, int k, int64_t n_s, int nlev,
+                                                 const int32_t *__restrict__ skip) {
+  const int done = skip != nullptr ? *skip : 0;
+  const T c1 = (T)cf[3 + 2 * (k - 2)], c2 = (T)cf[4 + 2 * (k - 2)];
+  const int64_t n = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+  const int v = blockIdx.y;
+  if (n >= n_s) return;
+  const int64_t i = v * n_s + n, plane = (int64_t)nlev * n_s;
+  const int64_t vm = v > 0 ? -n_s : 0, vp = v < nlev - 1 ? n_s : 0;   // the entries there are zero
+  const T ri = r[i], xi = x[i], di = d[i], iv = dinv[i];
+  T q = T(0);
+  auto entry = [&](int w, int wt) {
+    const int64_t j = v * n_s + nb[w * n_s + n];
+    q += val[w * plane + i] * d[j + vm] + val[(wt + w) * plane + i] * d[j] + val[(2 * wt + w) * plane + i] * d[j + vp];
+  };
+  if constexpr (W > 0) {
+#pragma unroll
+    for (int w = 0; w < W; ++w) entry(w, W);
+  } else {
+    for (int w = 0; w < wn; ++w) entry(w, wn);
+  }
+  asm volatile("" ::: "memory");   // the loads stay ahead of the test
+  if (done) return;
+  const T rn = ri - q;
+  const T dd = c1 * di + c2 * iv * rn;
+  r[i] = rn;
+  dn[i] = dd;
+  x[i] = xi + dd;
+}
+
+// All steps, from x = 0, in one workgroup for a level of at most kP1One unknowns: a thread keeps its
+// row of the matrix in registers, d goes through LDS.
+constexpr int kP1One = 1024;
+template <int W, typename T>
+__global__ __launch_bounds__(kP1One) void k_p1_all(Deferred<T> b, T *x, const T *__restrict__ val,
+                                                   const int32_t *__restrict__ nb, const T *__restrict__ dinv,
+                                                   const double *__restrict__ cf, int n_s, int nlev,
+                                                   const int32_t *__restrict__ skip) {
+  __shared__ T sd[kP1One];
+  const int done = skip != nullptr ? *skip : 0;
+  const int i = threadIdx.x, v = i / n_s, n = i - v * n_s;
+  const bool act = v < nlev;
+  const int plane = nlev * n_s;
+  T a[3][W], iv = T(0), bi = T(0);
+  int j[W];
+  const int vm = v > 0 ? -n_s : 0, vp = v < nlev - 1 ? n_s : 0;
+#pragma unroll
+  for (int w = 0; w < W; ++w) {
+    j[w] = act ? v * n_s + nb[w * n_s + n] : 0;
+#pragma unroll
+    for (int dv = 0; dv < 3; ++dv) a[dv][w] = act ? val[(dv * W + w) * plane + i] : T(0);
+  }
+  if (act) {
+    iv = dinv[i];
+    bi = gather_one(b, i, n, n_s, v);
+  }
+  if (done) return;
+  T r = bi, d = (T)cf[0] * iv * bi, xi = d;
+  for (int k = 2; k <= kMgCoarseSteps; ++k) {
+    sd[i] = d;
+    __syncthreads();
+    T q = T(0);
+    if (act) {
+#pragma unroll
+      for (int w = 0; w < W; ++w) q += a[0][w] * sd[j[w] + vm] + a[1][w] * sd[j[w]] + a[2][w] * sd[j[w] + vp];
+    }
+    r -= q;
+    d = (T)cf[3 + 2 * (k - 2)] * d + (T)cf[4 + 2 * (k - 2)] * iv * r;
+    xi += d;
+    __syncthreads();
+  }
+  if (act) x[i] = xi;
+}
+
 // first Chebyshev step from x = 0: r = b, d = c dinv b, x = d; a deferred b is completed in bw
 template <int LV, typename T>
 __global__ __launch_bounds__(kVecThreads) void k_cheb0(Deferred<T> b, T *bw, T *r, T *d, T *x, const T *dinv,
@@ -921,6 +1080,93 @@ hipError_t smooth(Ctx &L, const Deferred<T> &b, T *x, T *r, T *d, T *q, const do
   return hipGetLastError();
 }
 
+template <typename T>
+T *&p1_values(Ctx &c);
+template <>
+double *&p1_values<double>(Ctx &c) { return c.d_p1_val64; }
+template <>
+float *&p1_values<float>(Ctx &c) { return c.d_p1_val32; }
+
+// Levels whose assembled operator stays within the 256 MB cache with room to spare: a row is read
+// whole at every step (216 bytes in FP64), so beyond it the matrix-free apply moves less.
+constexpr size_t kP1MaxBytes = size_t(96) << 20;
+
+// Neighbour lists of a degree-1 level (host, once).
+fnpf_status p1_build(Ctx &c) {
+  const int nh = c.nh;
+  std::vector<std::vector<int32_t>> nb(c.n_s);
+  std::vector<int32_t> ptr(c.n_s + 1, 0), inc;
+  for (int32_t id : c.h_eh_nodes) ptr[id + 1]++;
+  for (int64_t n = 0; n < c.n_s; ++n) {
+    ptr[n + 1] += ptr[n];
+    nb[n].push_back((int32_t)n);
+  }
+  inc.resize(c.h_eh_nodes.size());
+  std::vector<int32_t> fill(ptr.begin(), ptr.end() - 1);
+  std::vector<uint8_t> map(c.h_eh_nodes.size() * nh);
+  size_t w = 1;
+  for (size_t o = 0; o < c.h_eh_nodes.size(); ++o) {
+    const int32_t n = c.h_eh_nodes[o];
+    inc[fill[n]++] = (int32_t)o;
+    for (int b = 0; b < nh; ++b) {
+      const int32_t m = c.h_eh_nodes[o / nh * nh + b];
+      const auto at = std::find(nb[n].begin(), nb[n].end(), m);
+      const size_t k = at - nb[n].begin();
+      if (at == nb[n].end()) nb[n].push_back(m);
+      w = std::max(w, nb[n].size());
+      if (k > 255) return FNPF_ERR_ARG;
+      map[o * nh + b] = (uint8_t)k;
+    }
+  }
+  std::vector<int32_t> list(w * c.n_s);
+  for (size_t k = 0; k < w; ++k)
+    for (int64_t n = 0; n < c.n_s; ++n) list[k * c.n_s + n] = k < nb[n].size() ? nb[n][k] : (int32_t)n;
+  auto up = [](auto **d, const auto &h) {
+    if (dalloc_t(d, h.size()) != hipSuccess) return false;
+    return hipMemcpy(*d, h.data(), h.size() * sizeof(h[0]), hipMemcpyHostToDevice) == hipSuccess;
+  };
+  if (!up(&c.d_p1_nb, list) || !up(&c.d_p1_ptr, ptr) || !up(&c.d_p1_inc, inc) || !up(&c.d_p1_map, map))
+    return FNPF_ERR_ALLOC;
+  c.p1_w = (int)w;
+  return FNPF_OK;
+}
+
+// the assembled operator of the level's current geometry
+template <typename T>
+hipError_t p1_assemble(Ctx &c, hipStream_t s) {
+  if (p1_values<T>(c) == nullptr) return hipSuccess;
+  const int64_t hs = (int64_t)c.n_eh * c.nh;
+  const dim3 nb((unsigned)((c.n_s + 255) / 256), c.p1_w, c.nz + 1);
+  auto kern = c.dim == 3 ? k_p1_matrix<3, T> : k_p1_matrix<2, T>;
+  kern<<<nb, 256, 0, s>>>(c.d_cg64, c.d_hm, hs, c.d_p1_ptr, c.d_p1_inc, c.d_p1_map, c.nz, c.n_s, c.d_sigma,
+                          c.d_half_ds, p1_values<T>(c));
+  return hipGetLastError();
+}
+
+// kMgCoarseSteps Chebyshev steps from zero with it (r, d, d2: work vectors)
+template <typename T>
+hipError_t p1_smooth(Ctx &L, const Deferred<T> &b, T *x, T *r, T *d, T *d2, const double *cf, const int32_t *skip,
+                     hipStream_t s) {
+  const T *dinv = Prec<T>::dinv(L), *val = p1_values<T>(L);
+  const int nlev = L.nz + 1;
+  if (L.n_v <= kP1One && (L.p1_w == 3 || L.p1_w == 9)) {
+    auto kern = L.p1_w == 3 ? k_p1_all<3, T> : k_p1_all<9, T>;
+    kern<<<1, (unsigned)((L.n_v + 63) / 64 * 64), 0, s>>>(b, x, val, L.d_p1_nb, dinv, cf, (int)L.n_s, nlev, skip);
+    return hipGetLastError();
+  }
+  const int nlv = node_levels(L);
+  with_levels(nlv, [&](auto lv) {
+    k_cheb0<lv(), T><<<node_blocks(L, nlv), kVecThreads, 0, s>>>(b, nullptr, r, d, x, dinv, cf, L.n_s, skip);
+  });
+  const dim3 nb((unsigned)((L.n_s + 255) / 256), nlev);
+  auto kern = L.p1_w == 3 ? k_p1_step<3, T> : L.p1_w == 9 ? k_p1_step<9, T> : k_p1_step<0, T>;
+  for (int k = 2; k <= kMgCoarseSteps; ++k) {
+    kern<<<nb, 256, 0, s>>>(val, L.d_p1_nb, L.p1_w, r, d, d2, x, dinv, cf, k, L.n_s, nlev, skip);
+    std::swap(d, d2);
+  }
+  return hipGetLastError();
+}
+
 // V-cycle on level l (0 = this context) for the right-hand side b (completed in place where it is
 // deferred), result in x.
 // pre_scaled (level 0, degree 2): d = c0 dinv b is already in place (k_mg_update<T, true>).
@@ -941,6 +1187,7 @@ hipError_t vcycle(Ctx &c, int l, const Deferred<T> &b, T *x, const int32_t *skip
   const double *cf = coef_table<T>(c, l);
   const int last = (int)c.mg.size();
   const bool line = c.mg_line;
+  if (l == last && !line && p1_values<T>(L) != nullptr) return p1_smooth<T>(L, b, x, r, d, q, cf, skip, s);
   if (l == last) return smooth<T>(L, b, x, r, d, q, cf, kMgCoarseSteps, true, skip, s, line);
   MgLevel &C = c.mg[l];
   T *bc = Prec<T>::lv(C)[0], *xc = Prec<T>::lv(C)[1];
@@ -1229,6 +1476,10 @@ fnpf_status mg_build(Ctx &c) {
     c.mg.push_back(L);
     F = c.mg.back().c;
   }
+  if (!c.mg.empty() && (size_t)27 * c.mg.back().c->n_v * sizeof(float) <= kP1MaxBytes) {
+    const fnpf_status st = p1_build(*c.mg.back().c);
+    if (st != FNPF_OK && st != FNPF_ERR_ARG) return st;   // ARG: a node with too many neighbours stays matrix-free
+  }
   if (dalloc_t(&c.d_mgc, (size_t)2 * (c.mg.size() + 1) * kMgCoef) != hipSuccess) return FNPF_ERR_ALLOC;
   if (dalloc_t(&c.d_mg_lz, (size_t)kLzScalars) != hipSuccess) return FNPF_ERR_ALLOC;
   if (dalloc_t(&c.d_mg_lam, (size_t)2 * (c.mg.size() + 1)) != hipSuccess) return FNPF_ERR_ALLOC;
@@ -1290,6 +1541,11 @@ fnpf_status mg_refresh(Ctx &c, hipStream_t s) {
       if (dalloc_t(&Prec<T>::ev(L), L.c->n_v) != hipSuccess) return FNPF_ERR_ALLOC;
       if (sizeof(T) == 4 && ctx_ensure32(*L.c) != FNPF_OK) return FNPF_ERR_ALLOC;
     }
+    if (!c.mg.empty()) {
+      Ctx &L = *c.mg.back().c;
+      const size_t n = (size_t)3 * L.p1_w * L.n_v;
+      if (n > 0 && n * sizeof(T) <= kP1MaxBytes && dalloc_t(&p1_values<T>(L), n) != hipSuccess) return FNPF_ERR_ALLOC;
+    }
   }
   if (!Prec<T>::stale(c)) return FNPF_OK;
   Ctx *F = &c;
@@ -1300,6 +1556,7 @@ fnpf_status mg_refresh(Ctx &c, hipStream_t s) {
     if (st != FNPF_OK) return st;
     F = L.c;
   }
+  if (!c.mg.empty() && !c.mg_line && p1_assemble<T>(*c.mg.back().c, s) != hipSuccess) return FNPF_ERR_HIP;
   if (c.mg_line) {
     // the vertical line blocks of every level from its current geometry, factored
     if (line_setup(c, s) != hipSuccess) return FNPF_ERR_HIP;
