@@ -283,7 +283,7 @@ hipError_t stage_rhs(Ctx &c, const double *eta, const double *phs, const double 
   if (!consistent_surface(c)) return launch_rhs(c, eta, phs, w, a, s);
   hipError_t e = launch_sq_rhs(c, eta, phs, w, c.d_sq_b, s);
   if (e != hipSuccess) return e;
-  e = sq_solve(c, c.d_sq_b, c.d_sq_x, s);
+  e = sq_solve(c, c.d_sq_b, c.d_sq_x, true, s);
   if (e != hipSuccess) return e;
   return launch_sq_stage(a, c.d_sq_x, c.n_s, s);
 }
@@ -296,7 +296,7 @@ hipError_t stage_rhs_vjp(Ctx &c, const double *eta, const double *phs, const dou
   // the fixed-length Chebyshev solve is a symmetric map, so bbar = S kbar
   hipError_t e = launch_sq_pack(kbe, kbp, c.d_sq_b, c.n_s, s);
   if (e != hipSuccess) return e;
-  e = sq_solve(c, c.d_sq_b, c.d_sq_x, s);
+  e = sq_solve(c, c.d_sq_b, c.d_sq_x, false, s);
   if (e != hipSuccess) return e;
   return launch_sq_rhs_vjp(c, eta, phs, w, c.d_sq_x, eta_bar, phis_bar, w_bar, s);
 }

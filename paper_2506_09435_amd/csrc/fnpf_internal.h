@@ -131,7 +131,7 @@ void sq_free(Ctx &c);
 hipError_t launch_sq_rhs(Ctx &c, const double *eta, const double *phs, const double *w, double *b, hipStream_t s);
 hipError_t launch_sq_rhs_vjp(Ctx &c, const double *eta, const double *phs, const double *w, const double *bbar,
                              double *eta_bar, double *phi_bar, double *w_bar, hipStream_t s);
-hipError_t sq_solve(Ctx &c, const double *b, double *x, hipStream_t s);
+hipError_t sq_solve(Ctx &c, double *b, double *x, bool b_slots, hipStream_t s);
 hipError_t launch_sq_stage(const RkStageArgs &a, const double *k2, int64_t n_s, hipStream_t s);
 hipError_t launch_sq_pack(const double *a, const double *b, double *out, int64_t n_s, hipStream_t s);
 // modal filter (forward: out = W (M x M) in, out != in; transpose: in_bar += (M x M)^T W out_bar)
@@ -348,7 +348,8 @@ struct Ctx {
   double sq_lo = 0.0, sq_hi = 0.0;        // Chebyshev interval of M_L^{-1} M
   double *d_sq_B = nullptr, *d_sq_Bd = nullptr;   // [nq][p+1] Lagrange values / derivatives at Gauss points
   double *d_sq_met = nullptr;             // [5 | 2][n_eh * nq^(dim-1)]: J^{-1} entries, W det J
-  double *d_sq_b = nullptr, *d_sq_x = nullptr, *d_sq_r = nullptr, *d_sq_d = nullptr, *d_sq_ad = nullptr;  // [2][n_s]
+  double *d_sq_b = nullptr, *d_sq_x = nullptr, *d_sq_d = nullptr, *d_sq_ad = nullptr;  // [2][n_s]
+  double *d_sq_F = nullptr;               // [2][n_slots] face slots of the quadrature and the mass product
   double *d_sq_scr = nullptr;             // [3][n_s] VJP accumulation
   // modal filter of the surface fields (cutoff < 0: off)
   int filter_cutoff = -1, filter_order = 0;

@@ -13,9 +13,9 @@
 // solve has a fixed length, needs no reductions and is a symmetric linear map of b (its VJP is
 // the same solve).
 //
-// Elements are processed up to four per workgroup (one wave each), colour by colour (columns of
-// one colour share no surface node), accumulating shared nodes in colour order like the other
-// surface kernels.
+// Assembly: a column stores the surface nodes it owns and writes its other contributions to face
+// slots (one per column and node, numbered by the set-up), which the vector kernel that follows adds;
+// the VJP's quadrature kernel accumulates colour by colour.
 
 #include <hip/hip_runtime.h>
 
@@ -24,6 +24,7 @@
 #include <cstring>
 #include <vector>
 
+#include "deferred.h"
 #include "fnpf_internal.h"
 #include "stage_update.h"
 
@@ -53,27 +54,27 @@ struct Carve {
   }
 };
 
-// Every kernel below handles epb elements per block, tpe = 256 / epb threads per element, each
+// The quadrature kernels handle epb elements per block, tpe = 256 / epb threads per element, each
 // element with its own LDS region of `per` doubles after the shared tables.  Groups without an
-// element (the ragged end of a colour) take part in the barriers only.
+// element (the ragged end) take part in the barriers only.
 
-// Forward: b_k, b_d (colour-accumulated, final at the last writer).
+// Forward: b_k, b_d at the owned nodes, the other contributions in the face slots Fk, Fd.
 template <int P, int DIM>
 __global__ __launch_bounds__(kSqThreads) void k_sq_rhs(const double *__restrict__ eta, const double *__restrict__ phs,
                                                        const double *__restrict__ wv,
                                                        const int32_t *__restrict__ eh_nodes,
-                                                       const uint8_t *__restrict__ flags,
-                                                       const int32_t *__restrict__ cols, int count, int epb, int per,
+                                                       const int32_t *__restrict__ slot, int count, int epb, int per,
                                                        const double *__restrict__ Bg,
                                                        const double *__restrict__ Bdg, int nq,
                                                        const double *__restrict__ met, int64_t mstride, double g,
-                                                       double *__restrict__ bk, double *__restrict__ bd) {
+                                                       double *__restrict__ bk, double *__restrict__ bd,
+                                                       double *__restrict__ Fk, double *__restrict__ Fd) {
   constexpr int N1 = P + 1, NH = DIM == 3 ? N1 * N1 : N1;
   extern __shared__ double lds[];
   const int tpe = kSqThreads / epb, grp = threadIdx.x / tpe, tid = threadIdx.x - grp * tpe;
   const int ci = blockIdx.x * epb + grp;
   const bool act = ci < count;
-  const int col = act ? cols[ci] : 0;
+  const int col = act ? ci : 0;
   const int nqd = DIM == 3 ? nq * nq : nq;
   double *sB = lds, *sBd = lds + nq * N1;
   Carve cv{lds + 2 * nq * N1 + grp * per};
@@ -162,10 +163,9 @@ __global__ __launch_bounds__(kSqThreads) void k_sq_rhs(const double *__restrict_
         a1 += b * Ud[j * nq + qx];
       }
       const int64_t o = (int64_t)col * NH + t;
-      const int hn = eh_nodes[o];
-      const uint8_t fl = flags[o];
-      acc_colour(bk, hn, a0, fl);
-      acc_colour(bd, hn, a1, fl);
+      const int hn = eh_nodes[o], sl = slot[o];
+      (sl < 0 ? bk + hn : Fk + sl)[0] = a0;
+      (sl < 0 ? bd + hn : Fd + sl)[0] = a1;
     }
   } else {
     for (int q = tid; act && q < nq; q += tpe) {
@@ -192,120 +192,127 @@ __global__ __launch_bounds__(kSqThreads) void k_sq_rhs(const double *__restrict_
         a1 += sB[q * N1 + i] * Qd[q];
       }
       const int64_t o = (int64_t)col * NH + i;
-      const int hn = eh_nodes[o];
-      const uint8_t fl = flags[o];
-      acc_colour(bk, hn, a0, fl);
-      acc_colour(bd, hn, a1, fl);
+      const int hn = eh_nodes[o], sl = slot[o];
+      (sl < 0 ? bk + hn : Fk + sl)[0] = a0;
+      (sl < 0 ? bd + hn : Fd + sl)[0] = a1;
     }
   }
 }
 
-// y = M x for two fields stored [2][n_s] (consistent surface mass, W det at the Gauss points).
-template <int P, int DIM>
-__global__ __launch_bounds__(kSqThreads) void k_sq_mass(const double *__restrict__ x, double *__restrict__ y,
-                                                        int64_t n_s, const int32_t *__restrict__ eh_nodes,
-                                                        const uint8_t *__restrict__ flags,
-                                                        const int32_t *__restrict__ cols, int count, int epb,
-                                                        int per, const double *__restrict__ Bg, int nq,
-                                                        const double *__restrict__ wdet) {
-  constexpr int N1 = P + 1, NH = DIM == 3 ? N1 * N1 : N1;
+// y = M x for two fields stored [2][n_s] (consistent surface mass, W det at the Gauss points): the
+// owned nodes' sums in y, the others in the face slots F [2][n_slots].
+// 3D: `lanes` = 2 max(P + 1, nq) threads an element.  A thread owns a line of one field at a time,
+// its values in registers and the 1D tables as uniform scalars: a xi-line of nodes (interpolated to
+// nq points, into LDS), an eta-line of points (interpolated, times W det, tested against the basis:
+// nothing of it leaves the registers), a xi-line again.  LDS then carries four values a line point
+// instead of two operands for every multiply-add, which bound the thread-per-point form: on the sea's
+// surface (256 x 128, p = 6, nq = 9) four colour launches of 14.4 us, now one of 23.9 for 79 MB of
+// fields, W det, ids and slots (3.3 TB/s).
+template <int P>
+__global__ __launch_bounds__(kSqThreads) void k_sq_mass3(const double *__restrict__ x, double *__restrict__ y,
+                                                         double *__restrict__ F, int64_t n_s, int64_t n_slots,
+                                                         const int32_t *__restrict__ eh_nodes,
+                                                         const int32_t *__restrict__ slot, int n_eh, int lanes,
+                                                         const double *__restrict__ B, int nq,
+                                                         const double *__restrict__ wdet) {
+  constexpr int N1 = P + 1, NH = N1 * N1;
   extern __shared__ double lds[];
-  const int tpe = kSqThreads / epb, grp = threadIdx.x / tpe, tid = threadIdx.x - grp * tpe;
-  const int ci = blockIdx.x * epb + grp;
-  const bool act = ci < count;
-  const int col = act ? cols[ci] : 0;
-  const int nqd = DIM == 3 ? nq * nq : nq;
-  double *sB = lds;
-  Carve cv{lds + nq * N1 + grp * per};
-  double *u0 = cv.take(NH), *u1 = cv.take(NH);
-  double *Q0 = cv.take(nqd), *Q1 = cv.take(nqd);
-  for (int k = threadIdx.x; k < nq * N1; k += kSqThreads) sB[k] = Bg[k];
-  for (int t = tid; act && t < NH; t += tpe) {
-    const int hn = eh_nodes[(int64_t)col * NH + t];
-    u0[t] = x[hn];
-    u1[t] = x[n_s + hn];
+  const int epb = kSqThreads / lanes, grp = threadIdx.x / lanes, ln = threadIdx.x - grp * lanes;
+  const int64_t col = (int64_t)blockIdx.x * epb + grp;
+  const bool act = grp < epb && col < n_eh;
+  double *T = lds + (grp < epb ? grp : 0) * 2 * N1 * nq;   // [2][N1][nq]
+  const bool xi = act && ln < 2 * N1;
+  double *row = T + (xi ? ln : 0) * nq;   // the thread's xi-line (field ln / N1, node row ln % N1)
+  const int64_t o = xi ? col * NH + (ln % N1) * N1 : 0;
+  const int f = ln / N1;
+  int id[N1];
+  if (xi) {
+    double u[N1];
+#pragma unroll
+    for (int i = 0; i < N1; ++i) id[i] = eh_nodes[o + i];
+#pragma unroll
+    for (int i = 0; i < N1; ++i) u[i] = x[f * n_s + id[i]];
+    for (int q = 0; q < nq; ++q) {
+      double a = 0.0;
+#pragma unroll
+      for (int i = 0; i < N1; ++i) a += B[q * N1 + i] * u[i];
+      row[q] = a;
+    }
   }
   __syncthreads();
-  const int64_t mb = (int64_t)col * nqd;
-  if constexpr (DIM == 3) {
-    double *T0 = cv.take(N1 * nq), *T1 = cv.take(N1 * nq);
-    for (int k = tid; act && k < N1 * nq; k += tpe) {
-      const int j = k / nq, qx = k - j * nq;
-      double a0 = 0, a1 = 0;
+  if (act && ln < 2 * nq) {
+    const int g = ln / nq, qx = ln - g * nq;
+    double *p = T + g * N1 * nq + qx;
+    const double *wd = wdet + col * nq * nq + qx;
+    double t[N1], r[N1];
 #pragma unroll
-      for (int i = 0; i < N1; ++i) {
-        const double b = sB[qx * N1 + i];
-        a0 += b * u0[j * N1 + i];
-        a1 += b * u1[j * N1 + i];
-      }
-      T0[k] = a0;
-      T1[k] = a1;
+    for (int j = 0; j < N1; ++j) {
+      t[j] = p[j * nq];
+      r[j] = 0.0;
     }
-    __syncthreads();
-    for (int k = tid; act && k < nqd; k += tpe) {
-      const int qy = k / nq, qx = k - qy * nq;
-      double a0 = 0, a1 = 0;
+    for (int q = 0; q < nq; ++q) {
+      double a = 0.0;
 #pragma unroll
-      for (int j = 0; j < N1; ++j) {
-        const double b = sB[qy * N1 + j];
-        a0 += b * T0[j * nq + qx];
-        a1 += b * T1[j * nq + qx];
-      }
-      const double wd = wdet[mb + k];
-      Q0[k] = wd * a0;
-      Q1[k] = wd * a1;
-    }
-    __syncthreads();
-    for (int k = tid; act && k < N1 * nq; k += tpe) {
-      const int j = k / nq, qx = k - j * nq;
-      double a0 = 0, a1 = 0;
-      for (int qy = 0; qy < nq; ++qy) {
-        const double b = sB[qy * N1 + j];
-        a0 += b * Q0[qy * nq + qx];
-        a1 += b * Q1[qy * nq + qx];
-      }
-      T0[k] = a0;   // T is free again after the barrier above
-      T1[k] = a1;
-    }
-    __syncthreads();
-    for (int t = tid; act && t < NH; t += tpe) {
-      const int j = t / N1, i = t - j * N1;
-      double a0 = 0, a1 = 0;
-      for (int qx = 0; qx < nq; ++qx) {
-        const double b = sB[qx * N1 + i];
-        a0 += b * T0[j * nq + qx];
-        a1 += b * T1[j * nq + qx];
-      }
-      const int64_t o = (int64_t)col * NH + t;
-      const int hn = eh_nodes[o];
-      const uint8_t fl = flags[o];
-      acc_colour(y, hn, a0, fl);
-      acc_colour(y + n_s, hn, a1, fl);
-    }
-  } else {
-    for (int q = tid; act && q < nq; q += tpe) {
-      double a0 = 0, a1 = 0;
+      for (int j = 0; j < N1; ++j) a += B[q * N1 + j] * t[j];
+      a *= wd[q * nq];
 #pragma unroll
-      for (int i = 0; i < N1; ++i) {
-        a0 += sB[q * N1 + i] * u0[i];
-        a1 += sB[q * N1 + i] * u1[i];
-      }
-      Q0[q] = wdet[mb + q] * a0;
-      Q1[q] = wdet[mb + q] * a1;
+      for (int j = 0; j < N1; ++j) r[j] += B[q * N1 + j] * a;
     }
-    __syncthreads();
-    for (int i = tid; act && i < N1; i += tpe) {
-      double a0 = 0, a1 = 0;
-      for (int q = 0; q < nq; ++q) {
-        a0 += sB[q * N1 + i] * Q0[q];
-        a1 += sB[q * N1 + i] * Q1[q];
-      }
-      const int64_t o = (int64_t)col * NH + i;
-      const int hn = eh_nodes[o];
-      const uint8_t fl = flags[o];
-      acc_colour(y, hn, a0, fl);
-      acc_colour(y + n_s, hn, a1, fl);
+#pragma unroll
+    for (int j = 0; j < N1; ++j) p[j * nq] = r[j];
+  }
+  __syncthreads();
+  if (xi) {
+    double r[N1];
+#pragma unroll
+    for (int i = 0; i < N1; ++i) r[i] = 0.0;
+    for (int q = 0; q < nq; ++q) {
+      const double a = row[q];
+#pragma unroll
+      for (int i = 0; i < N1; ++i) r[i] += B[q * N1 + i] * a;
     }
+#pragma unroll
+    for (int i = 0; i < N1; ++i) {
+      const int sl = slot[o + i];
+      (sl < 0 ? y + f * n_s + id[i] : F + f * n_slots + sl)[0] = r[i];
+    }
+  }
+}
+
+// the same on the intervals of a slice's surface: a thread takes one element and field
+template <int P>
+__global__ __launch_bounds__(kSqThreads) void k_sq_mass2(const double *__restrict__ x, double *__restrict__ y,
+                                                         double *__restrict__ F, int64_t n_s, int64_t n_slots,
+                                                         const int32_t *__restrict__ eh_nodes,
+                                                         const int32_t *__restrict__ slot, int n_eh,
+                                                         const double *__restrict__ B, int nq,
+                                                         const double *__restrict__ wdet) {
+  constexpr int N1 = P + 1;
+  const int64_t k = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+  if (k >= 2 * (int64_t)n_eh) return;
+  const int f = (int)(k & 1);
+  const int64_t col = k >> 1;
+  double u[N1], r[N1];
+  int id[N1];
+#pragma unroll
+  for (int i = 0; i < N1; ++i) id[i] = eh_nodes[col * N1 + i];
+#pragma unroll
+  for (int i = 0; i < N1; ++i) {
+    u[i] = x[f * n_s + id[i]];
+    r[i] = 0.0;
+  }
+  for (int q = 0; q < nq; ++q) {
+    double a = 0.0;
+#pragma unroll
+    for (int i = 0; i < N1; ++i) a += B[q * N1 + i] * u[i];
+    a *= wdet[col * nq + q];
+#pragma unroll
+    for (int i = 0; i < N1; ++i) r[i] += B[q * N1 + i] * a;
+  }
+#pragma unroll
+  for (int i = 0; i < N1; ++i) {
+    const int sl = slot[col * N1 + i];
+    (sl < 0 ? y + f * n_s + id[i] : F + f * n_slots + sl)[0] = r[i];
   }
 }
 
@@ -497,34 +504,54 @@ __global__ __launch_bounds__(kSqThreads) void k_sq_rhs_vjp(
   }
 }
 
-// Chebyshev vector kernels on [2][n_s]; ml = lumped surface mass [n_s].
-__global__ void k_sq_init(const double *__restrict__ b, const double *__restrict__ ml, double *__restrict__ x,
-                          int64_t n_s) {
-  for (int64_t k = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; k < 2 * n_s; k += (int64_t)gridDim.x * blockDim.x)
-    x[k] = b[k] / ml[k < n_s ? k : k - n_s];
+// Chebyshev vector kernels on two fields [2][n_s]; ml = lumped surface mass [n_s].  A thread takes one
+// node and both fields; v: a vector whose face slots are still to be added.
+__device__ __forceinline__ void sq_gather(const Deferred<double> &v, int64_t n, int64_t n_s, double &a, double &b) {
+  a = v.y[n];
+  b = v.y[n_s + n];
+  if (n >= v.n_hi) return;
+  const int4 s = v.slots[n];
+  const double *f = v.F, *g = v.F + v.n_slots;
+  if (s.x >= 0) a += f[s.x], b += g[s.x];
+  if (s.y >= 0) a += f[s.y], b += g[s.y];
+  if (s.z >= 0) a += f[s.z], b += g[s.z];
+  if (s.w > 0) a = list_sum(v, f, s.w, a), b = list_sum(v, g, s.w, b);
 }
 
-__global__ void k_sq_start(const double *__restrict__ b, const double *__restrict__ ax, const double *__restrict__ ml,
-                           double inv_theta, double *__restrict__ r, double *__restrict__ d, int64_t n_s) {
-  for (int64_t k = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; k < 2 * n_s;
-       k += (int64_t)gridDim.x * blockDim.x) {
-    const double rr = b[k] - ax[k];
-    r[k] = rr;
-    d[k] = inv_theta * rr / ml[k < n_s ? k : k - n_s];
+// x = b / ml; a deferred b is completed in bw
+__global__ __launch_bounds__(256) void k_sq_init(Deferred<double> b, double *bw, const double *__restrict__ ml,
+                                                 double *x, int64_t n_s) {
+  const int64_t n = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+  if (n >= n_s) return;
+  double u, v;
+  const double m = ml[n];
+  sq_gather(b, n, n_s, u, v);
+  if (bw != nullptr) {
+    bw[n] = u;
+    bw[n_s + n] = v;
   }
+  x[n] = u / m;
+  x[n_s + n] = v / m;
 }
 
-__global__ void k_sq_cheb(double *__restrict__ x, double *__restrict__ r, double *__restrict__ d,
-                          const double *__restrict__ ad, const double *__restrict__ ml, double c1, double c2,
-                          int64_t n_s) {
-  for (int64_t k = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; k < 2 * n_s;
-       k += (int64_t)gridDim.x * blockDim.x) {
-    const double dk = d[k];
-    x[k] += dk;
-    const double rr = r[k] - ad[k];
-    r[k] = rr;
-    d[k] = c1 * dk + c2 * rr / ml[k < n_s ? k : k - n_s];
+// One Chebyshev step in the form that needs no residual or direction in memory:
+// x_{k+1} = x_k + c1 (x_k - x_{k-1}) + c2 (b - M x_k) / ml, x_{k+1} over x_{k-1} (c1 = 0: not read)
+// Bound by its 125 MB on the sea's surface (1.18 M nodes): 20.8 us, 6 TB/s with the last level cache's
+// help; the form with residual and direction in memory and the sums complete took 24.7.
+__global__ __launch_bounds__(256) void k_sq_cheb(const double *__restrict__ x, double *xo, Deferred<double> mx,
+                                                 const double *__restrict__ b, const double *__restrict__ ml,
+                                                 double c1, double c2, int64_t n_s) {
+  const int64_t n = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+  if (n >= n_s) return;
+  const double m = ml[n], b0 = b[n], b1 = b[n_s + n], x0 = x[n], x1 = x[n_s + n];
+  double p0 = 0.0, p1 = 0.0, y0, y1;
+  if (c1 != 0.0) {
+    p0 = c1 * (x0 - xo[n]);
+    p1 = c1 * (x1 - xo[n_s + n]);
   }
+  sq_gather(mx, n, n_s, y0, y1);
+  xo[n] = x0 + (p0 + c2 * ((b0 - y0) / m));
+  xo[n_s + n] = x1 + (p1 + c2 * ((b1 - y1) / m));
 }
 
 __global__ void k_sq_stage(RkStageArgs a, const double *__restrict__ k2, int64_t n_s) {
@@ -564,11 +591,6 @@ SqLds lds_rhs(const Ctx &c) {
   const int nqd = c.dim == 3 ? nq * nq : nq;
   return {2 * nq * n1, 3 * nh + 2 * nqd + (c.dim == 3 ? 7 * n1 * nq : 0)};
 }
-SqLds lds_mass(const Ctx &c) {
-  const int n1 = c.p + 1, nq = c.sq_nq, nh = c.nh;
-  const int nqd = c.dim == 3 ? nq * nq : nq;
-  return {nq * n1, 2 * nh + 2 * nqd + (c.dim == 3 ? 2 * n1 * nq : 0)};
-}
 SqLds lds_vjp(const Ctx &c) {
   const int n1 = c.p + 1, nq = c.sq_nq, nh = c.nh;
   const int nqd = c.dim == 3 ? nq * nq : nq;
@@ -588,17 +610,26 @@ SqLaunch sq_launch(const SqLds &l) {
   return {1, l.per, (size_t)(l.table + l.per) * sizeof(double)};
 }
 
+// two fields y [2][n_s] whose other contributions are in the face slots d_sq_F [2][n_slots]
+Deferred<double> sq_deferred(const Ctx &c, const double *y) {
+  Deferred<double> d;
+  d.y = y;
+  d.F = c.d_sq_F;
+  d.slots = c.d_p_slots;
+  d.lists = c.d_p_lists;
+  d.n_hi = c.p_n_hi;
+  d.n_slots = c.n_slots;
+  return d;
+}
+
 template <int P, int DIM>
 hipError_t sq_rhs_impl(Ctx &c, const double *eta, const double *phs, const double *w, double *b, hipStream_t s) {
   const int64_t ms = (int64_t)c.n_eh * (c.dim == 3 ? c.sq_nq * c.sq_nq : c.sq_nq);
   const SqLaunch L = sq_launch(lds_rhs(c));
-  for (const auto &cr : c.colours) {
-    if (cr.count == 0) continue;
-    const int nb = (cr.count + L.epb - 1) / L.epb;
-    k_sq_rhs<P, DIM><<<nb, kSqThreads, L.bytes, s>>>(eta, phs, w, c.d_eh_nodes, c.d_flags, c.d_cols + cr.offset,
-                                                      cr.count, L.epb, L.per, c.d_sq_B, c.d_sq_Bd, c.sq_nq,
-                                                      c.d_sq_met, ms, c.g, b, b + c.n_s);
-  }
+  const int nb = (c.n_eh + L.epb - 1) / L.epb;
+  k_sq_rhs<P, DIM><<<nb, kSqThreads, L.bytes, s>>>(eta, phs, w, c.d_eh_nodes, c.d_slot, c.n_eh, L.epb, L.per, c.d_sq_B,
+                                                    c.d_sq_Bd, c.sq_nq, c.d_sq_met, ms, c.g, b, b + c.n_s, c.d_sq_F,
+                                                    c.d_sq_F + c.n_slots);
   return hipGetLastError();
 }
 
@@ -606,12 +637,16 @@ template <int P, int DIM>
 hipError_t sq_mass_impl(Ctx &c, const double *x, double *y, hipStream_t s) {
   const int64_t ms = (int64_t)c.n_eh * (c.dim == 3 ? c.sq_nq * c.sq_nq : c.sq_nq);
   const double *wdet = c.d_sq_met + (c.dim == 3 ? 4 : 1) * ms;
-  const SqLaunch L = sq_launch(lds_mass(c));
-  for (const auto &cr : c.colours) {
-    if (cr.count == 0) continue;
-    const int nb = (cr.count + L.epb - 1) / L.epb;
-    k_sq_mass<P, DIM><<<nb, kSqThreads, L.bytes, s>>>(x, y, c.n_s, c.d_eh_nodes, c.d_flags, c.d_cols + cr.offset,
-                                                       cr.count, L.epb, L.per, c.d_sq_B, c.sq_nq, wdet);
+  if constexpr (DIM == 3) {
+    const int lanes = 2 * std::max(c.p + 1, c.sq_nq), epb = kSqThreads / lanes;
+    const size_t bytes = (size_t)epb * 2 * (c.p + 1) * c.sq_nq * sizeof(double);
+    k_sq_mass3<P><<<(c.n_eh + epb - 1) / epb, kSqThreads, bytes, s>>>(x, y, c.d_sq_F, c.n_s, c.n_slots, c.d_eh_nodes,
+                                                                       c.d_slot, c.n_eh, lanes, c.d_sq_B, c.sq_nq,
+                                                                       wdet);
+  } else {
+    const int64_t n = 2 * (int64_t)c.n_eh;
+    k_sq_mass2<P><<<(unsigned)((n + kSqThreads - 1) / kSqThreads), kSqThreads, 0, s>>>(
+        x, y, c.d_sq_F, c.n_s, c.n_slots, c.d_eh_nodes, c.d_slot, c.n_eh, c.d_sq_B, c.sq_nq, wdet);
   }
   return hipGetLastError();
 }
@@ -695,24 +730,27 @@ hipError_t launch_sq_rhs_vjp(Ctx &c, const double *eta, const double *phs, const
   return hipSuccess;
 }
 
-// x = M^{-1} b for two fields [2][n_s] by the fixed-length preconditioned Chebyshev iteration.
-// Uses c.d_sq_r, d_sq_d, d_sq_ad as work vectors; b and x must not overlap them.
-hipError_t sq_solve(Ctx &c, const double *b, double *x, hipStream_t s) {
+// x = M^{-1} b for two fields [2][n_s] by the fixed-length preconditioned Chebyshev iteration.  b_slots:
+// b's face slots (launch_sq_rhs) are still to be added; b is then completed in place.  Uses d_sq_d and
+// d_sq_ad as work vectors; b and x must not overlap them.
+hipError_t sq_solve(Ctx &c, double *b, double *x, bool b_slots, hipStream_t s) {
   const int64_t ns = c.n_s;
-  const int nb = vec_blocks(2 * ns);
+  const unsigned nb = (unsigned)((ns + 255) / 256);
   const double theta = 0.5 * (c.sq_hi + c.sq_lo), delta = 0.5 * (c.sq_hi - c.sq_lo);
   const double sigma = theta / delta;
-  k_sq_init<<<nb, 256, 0, s>>>(b, c.d_mlump_s, x, ns);
-  hipError_t e = sq_mass(c, x, c.d_sq_ad, s);
-  if (e != hipSuccess) return e;
-  k_sq_start<<<nb, 256, 0, s>>>(b, c.d_sq_ad, c.d_mlump_s, 1.0 / theta, c.d_sq_r, c.d_sq_d, ns);
-  double rho = 1.0 / sigma;
+  double *cur = (c.sq_iters & 1) ? c.d_sq_d : x, *oth = (c.sq_iters & 1) ? x : c.d_sq_d;   // x_K lands in x
+  Deferred<double> bd = sq_deferred(c, b);
+  if (!b_slots) bd.n_hi = 0;
+  k_sq_init<<<nb, 256, 0, s>>>(bd, b_slots ? b : nullptr, c.d_mlump_s, cur, ns);
+  double rho = 1.0 / sigma, c1 = 0.0, c2 = 1.0 / theta;
   for (int k = 0; k < c.sq_iters; ++k) {
-    e = sq_mass(c, c.d_sq_d, c.d_sq_ad, s);
+    const hipError_t e = sq_mass(c, cur, c.d_sq_ad, s);
     if (e != hipSuccess) return e;
+    k_sq_cheb<<<nb, 256, 0, s>>>(cur, oth, sq_deferred(c, c.d_sq_ad), b, c.d_mlump_s, c1, c2, ns);
+    std::swap(cur, oth);
     const double rho_n = 1.0 / (2.0 * sigma - rho);
-    k_sq_cheb<<<nb, 256, 0, s>>>(x, c.d_sq_r, c.d_sq_d, c.d_sq_ad, c.d_mlump_s, rho_n * rho, 2.0 * rho_n / delta,
-                                  ns);
+    c1 = rho_n * rho;
+    c2 = 2.0 * rho_n / delta;
     rho = rho_n;
   }
   return hipGetLastError();
@@ -730,7 +768,7 @@ hipError_t launch_sq_pack(const double *a, const double *b, double *out, int64_t
 
 void sq_free(Ctx &c) {
   double **bufs[] = {&c.d_sq_B, &c.d_sq_Bd, &c.d_sq_met, &c.d_sq_b, &c.d_sq_x,
-                     &c.d_sq_r, &c.d_sq_d,  &c.d_sq_ad,  &c.d_sq_scr};
+                     &c.d_sq_F, &c.d_sq_d,  &c.d_sq_ad,  &c.d_sq_scr};
   for (double **p : bufs) {
     if (*p) (void)hipFree(*p);
     *p = nullptr;
@@ -813,10 +851,12 @@ const char *sq_setup(Ctx &c, int nq) {
     return hipMemcpy(*d, h.data(), h.size() * sizeof(double), hipMemcpyHostToDevice) == hipSuccess;
   };
   if (!up(&c.d_sq_B, B) || !up(&c.d_sq_Bd, Bd) || !up(&c.d_sq_met, met)) return "surface quadrature: allocation";
-  double **vecs[] = {&c.d_sq_b, &c.d_sq_x, &c.d_sq_r, &c.d_sq_d, &c.d_sq_ad};
+  double **vecs[] = {&c.d_sq_b, &c.d_sq_x, &c.d_sq_d, &c.d_sq_ad};
   for (double **v : vecs)
     if (hipMalloc(v, 2 * c.n_s * sizeof(double)) != hipSuccess) return "surface quadrature: allocation";
   if (hipMalloc(&c.d_sq_scr, 3 * c.n_s * sizeof(double)) != hipSuccess) return "surface quadrature: allocation";
+  if (hipMalloc(&c.d_sq_F, 2 * std::max<int64_t>(c.n_slots, 1) * sizeof(double)) != hipSuccess)
+    return "surface quadrature: allocation";
   c.sq_lo = lo;
   c.sq_hi = hi;
   const double kappa = hi / lo;
