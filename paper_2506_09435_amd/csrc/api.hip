@@ -106,7 +106,6 @@ void free_all(Ctx &c) {
   dfree(c.d_hm);
   dfree(c.d_sigma);
   dfree(c.d_layer_s);
-  dfree(c.d_mlump_w);
   dfree(c.d_mlump_s);
   dfree(c.d_G64);
   dfree(c.d_G32);
@@ -137,9 +136,8 @@ void free_all(Ctx &c) {
   dfree(c.d_w);
   dfree(c.d_geoH);
   dfree(c.d_geoh);
-  dfree(c.d_wnum);
-  dfree(c.d_nk);
-  dfree(c.d_nd);
+  dfree(c.d_sk);
+  dfree(c.d_sF);
   dfree(c.d_partial);
   dfree(c.d_mg_scal);
   dfree(c.d_lb64);
@@ -659,10 +657,10 @@ fnpf_status fnpf_create(const fnpf_mesh_desc *m, fnpf_ctx *out) {
   fnpf_ctx_s *h = new (std::nothrow) fnpf_ctx_s();
   if (!h) return FNPF_ERR_ALLOC;
   Ctx &c = h->c;
-  std::vector<double> hm, mw, ms;
+  std::vector<double> hm, ms;
   std::vector<uint8_t> flags;
   std::vector<int32_t> cols;
-  std::string e = build_host_mesh(*m, c, hm, flags, cols, mw, ms);
+  std::string e = build_host_mesh(*m, c, hm, flags, cols, ms);
   if (!e.empty()) {
     g_create_error = e;
     delete h;
@@ -771,7 +769,6 @@ fnpf_status fnpf_create(const fnpf_mesh_desc *m, fnpf_ctx *out) {
   UP(c.d_hm, hm.data(), hm.size());
   UP(c.d_sigma, c.h_sigma.data(), c.h_sigma.size());
   UP(c.d_layer_s, c.h_layer_s.data(), c.h_layer_s.size());
-  UP(c.d_mlump_w, mw.data(), mw.size());
   UP(c.d_mlump_s, ms.data(), ms.size());
   AL(c.d_cg64, (size_t)c.ncg * c.n_eh * c.nh);
   UP(c.d_half_ds, c.h_half_ds.data(), c.h_half_ds.size());
@@ -791,9 +788,8 @@ fnpf_status fnpf_create(const fnpf_mesh_desc *m, fnpf_ctx *out) {
   AL(c.d_w, c.n_s);
   AL(c.d_geoH, c.n_s);
   AL(c.d_geoh, c.n_s);
-  AL(c.d_wnum, c.n_s);
-  AL(c.d_nk, c.n_s);
-  AL(c.d_nd, c.n_s);
+  AL(c.d_sk, 2 * c.n_s);
+  AL(c.d_sF, 3 * std::max<int64_t>(c.n_slots, 1));
   {
     const auto uses = partial_uses(c.max_colour_blocks, owner_apply_blocks(c));
     c.n_partial = (int)partial_capacity(uses);

@@ -61,6 +61,18 @@ Deferred<T> complete(const Ctx &c, const T *y) {
   return d;
 }
 
+// two surface fields y [2][n_s]: the owned columns' values, the others in the slots c.d_sF [2][n_slots]
+inline Deferred<double> surface_result(const Ctx &c, const double *y) {
+  Deferred<double> d;
+  d.y = y;
+  d.F = c.d_sF;
+  d.slots = c.d_p_slots;
+  d.lists = c.d_p_lists;
+  d.n_hi = c.p_n_hi;
+  d.n_slots = c.n_slots;
+  return d;
+}
+
 // Grid-stride vector kernels over (levels, node): a task is 256 nodes at LV levels, a thread's LV
 // values being in flight together.
 inline int64_t node_tasks(const Ctx &c, int lv) { return (c.n_s + 255) / 256 * ((c.p * c.nz + lv) / lv); }
@@ -81,6 +93,19 @@ template <typename T>
 __device__ __forceinline__ T list_sum(const Deferred<T> &a, const T *f, int at, T q) {
   for (int k = 1; k <= a.lists[at]; ++k) q += f[a.lists[at + k]];
   return q;
+}
+
+// both fields of a surface_result at node n (nodes from n_hi on are complete)
+__device__ __forceinline__ void gather_pair(const Deferred<double> &v, int64_t n, int64_t n_s, double &a, double &b) {
+  a = v.y[n];
+  b = v.y[n_s + n];
+  if (n >= v.n_hi) return;
+  const int4 s = v.slots[n];
+  const double *f = v.F, *g = v.F + v.n_slots;
+  if (s.x >= 0) a += f[s.x], b += g[s.x];
+  if (s.y >= 0) a += f[s.y], b += g[s.y];
+  if (s.z >= 0) a += f[s.z], b += g[s.z];
+  if (s.w > 0) a = list_sum(v, f, s.w, a), b = list_sum(v, g, s.w, b);
 }
 
 // the assembled value at one node and level

@@ -207,7 +207,6 @@ struct Ctx {
   double *d_hm = nullptr;                 // [ncomp][n_eh*nh]
   double *d_sigma = nullptr;              // [p nz + 1]
   double *d_layer_s = nullptr;            // [nz + 1]
-  double *d_mlump_w = nullptr;            // [n_s] sum_e w_i w_j w_p det J_h (w recovery denominator)
   double *d_mlump_s = nullptr;            // [n_s] sum_e w_i w_j det J_h (surface mass)
   // apply variant: 0 fused geometry (factors recomputed in registers), 1 stored factors,
   // 2 fused geometry, unrolled schedule; the schedule of 0 is refined by the fields below
@@ -281,7 +280,8 @@ struct Ctx {
   double *d_acc_e = nullptr, *d_acc_p = nullptr;
   double *d_w = nullptr;                  // recovered w at the surface
   double *d_geoH = nullptr, *d_geoh = nullptr;    // eta + h and h of the last fnpf_geom
-  double *d_wnum = nullptr, *d_nk = nullptr, *d_nd = nullptr;  // surface scatter scratch
+  double *d_sk = nullptr;   // [2][n_s] surface right-hand sides, owned contributions
+  double *d_sF = nullptr;   // [3][n_slots] face slots of the surface kernels
   double *d_partial = nullptr;
   int n_partial = 0;                       // capacity: partial_capacity(partial_uses(...))
   double *d_mg_scal = nullptr;             // [4] power-iteration scalars of the p-multigrid refresh
@@ -349,7 +349,6 @@ struct Ctx {
   double *d_sq_B = nullptr, *d_sq_Bd = nullptr;   // [nq][p+1] Lagrange values / derivatives at Gauss points
   double *d_sq_met = nullptr;             // [5 | 2][n_eh * nq^(dim-1)]: J^{-1} entries, W det J
   double *d_sq_b = nullptr, *d_sq_x = nullptr, *d_sq_d = nullptr, *d_sq_ad = nullptr;  // [2][n_s]
-  double *d_sq_F = nullptr;               // [2][n_slots] face slots of the quadrature and the mass product
   double *d_sq_scr = nullptr;             // [3][n_s] VJP accumulation
   // modal filter of the surface fields (cutoff < 0: off)
   int filter_cutoff = -1, filter_order = 0;
@@ -425,6 +424,6 @@ void gll_host(int p, double *x, double *w, double *D);
 std::string coarse_numbering(const Ctx &f, int pc, std::vector<int32_t> &nodes, int64_t &n_s);
 std::string surface_interp_weights(const Ctx &c, int32_t n_pts, const double *pts, int32_t *node, double *w);
 std::string build_host_mesh(const fnpf_mesh_desc &m, Ctx &c, std::vector<double> &hm, std::vector<uint8_t> &flags,
-                            std::vector<int32_t> &cols, std::vector<double> &mlump_w, std::vector<double> &mlump_s);
+                            std::vector<int32_t> &cols, std::vector<double> &mlump_s);
 
 }  // namespace fnpf

@@ -21,6 +21,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include "deferred.h"
 #include "fnpf_internal.h"
 #include "stage_update.h"
 
@@ -1770,50 +1771,40 @@ __global__ __launch_bounds__(256) void k_neumann(const double *__restrict__ qv, 
 
 // ---------------------------------------------------------------------------------------------
 // Vertical velocity at the free surface (Steps 4.4-4.5): lumped-GLL L2 projection of dphi/dz.
-// For extruded elements d/dz = (1/z_zeta) d/dzeta and det J = det J_h z_zeta, and z_zeta at a
-// surface node is the same in every adjacent top element, so
-//   w_n = sum_e w_i w_j w_p det J_h (dphi/dzeta)_e / (z_zeta sum_e w_i w_j w_p det J_h).
+// For extruded elements d/dz = (1/z_zeta) d/dzeta and det J = det J_h z_zeta, and both z_zeta and
+// dphi/dzeta at a surface node are the same in every adjacent top element, so the weights
+// w_i w_j w_p det J_h of numerator and denominator cancel: w_n = (dphi/dzeta)_n / (z_zeta)_n, node by
+// node.  One launch that reads the top layer's P + 1 rows and H, 87 MB on the sea's surface (256 x 128
+// columns, p = 6): 20.3 us; assembled over the columns, colour by colour, it was 58 us.
 // ---------------------------------------------------------------------------------------------
-template <int P, int DIM>
-__global__ __launch_bounds__(256) void k_wsurf(const double *__restrict__ phi, const int32_t *__restrict__ eh_nodes,
-                                               const uint8_t *__restrict__ flags, const int32_t *__restrict__ cols,
-                                               int ncols, int nz, int64_t n_s, const double *__restrict__ hm,
-                                               int64_t hstride, const double *__restrict__ Hg,
-                                               const double *__restrict__ mlump, double half_ds,
-                                               double *__restrict__ wnum, double *__restrict__ w) {
-  using S = Sh<P, DIM>;
-  constexpr int N1 = S::N1, NH = S::NH, CPB = S::CPB;
-  const int lc = threadIdx.x / NH;
-  const int t = threadIdx.x - lc * NH;
-  const int i = t % N1, j = t / N1;
-  const int ci = blockIdx.x * CPB + lc;
-  if (ci >= ncols) return;
-  const int col = cols[ci];
-  const int hn = eh_nodes[(int64_t)col * NH + t];
-  const uint8_t fl = flags[(int64_t)col * NH + t];
-  const int64_t ho = (int64_t)col * NH + t;
-  const int v0 = (nz - 1) * P;
+template <int P>
+__global__ __launch_bounds__(256) void k_wsurf(const double *__restrict__ phi, int nz, int64_t n_s,
+                                               const double *__restrict__ Hg, double half_ds,
+                                               double *__restrict__ w) {
+  const int64_t n = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (n >= n_s) return;
+  const double *f = phi + (int64_t)(nz - 1) * P * n_s + n;
   double dz = 0.0;
 #pragma unroll
-  for (int m = 0; m < N1; ++m) dz += dmat<double>(P, P, m) * phi[(int64_t)(v0 + m) * n_s + hn];
-  const double det = DIM == 3 ? hm[4 * hstride + ho] : hm[1 * hstride + ho];
-  const double wq = (DIM == 3 ? wgt(P, i) * wgt(P, j) : wgt(P, i)) * wgt(P, P);
-  const double num = scatter(wnum, hn, wq * det * dz, fl);
-  if (fl & kLast) w[hn] = num / (half_ds * Hg[hn] * mlump[hn]);
+  for (int m = 0; m <= P; ++m) dz += dmat<double>(P, P, m) * f[m * n_s];
+  w[n] = dz / (half_ds * Hg[n]);
 }
 
 // ---------------------------------------------------------------------------------------------
 // Free-surface right-hand side (Step 4.6, Eqs. 2-3, lumped surface mass; linear potential flow:
 // their linear terms only), fused with the ERK4 stage update (Sec. 3.2) and, after the last
-// stage, the relaxation zones (Sec. 3.3).
+// stage, the relaxation zones (Sec. 3.3).  k_rhs: the columns' sums, owned nodes in nk [2][n_s],
+// the others in face slots F [2][n_slots]; k_rhs_stage completes them node by node.  Two launches and
+// 50 us on the sea's surface (256 x 128 columns, p = 6), most of it the 64 MB of column metrics;
+// read-add-write colour by colour took four launches and 70 us.
 // ---------------------------------------------------------------------------------------------
 template <int P, int DIM>
 __global__ __launch_bounds__(256) void k_rhs(const double *__restrict__ eta, const double *__restrict__ phs,
                                              const double *__restrict__ wv, const int32_t *__restrict__ eh_nodes,
-                                             const uint8_t *__restrict__ flags, const int32_t *__restrict__ cols,
-                                             int ncols, const double *__restrict__ hm, int64_t hstride,
-                                             const double *__restrict__ mlump_s, double g, double *__restrict__ nk,
-                                             double *__restrict__ nd, RkStageArgs a) {
+                                             const int32_t *__restrict__ slot, int ncols,
+                                             const double *__restrict__ hm, int64_t hstride, double g,
+                                             double *__restrict__ nk, int64_t n_s, double *__restrict__ F,
+                                             int64_t n_slots, bool linear) {
   using S = Sh<P, DIM>;
   constexpr int N1 = S::N1, NH = S::NH, CPB = S::CPB;
   __shared__ double se[CPB * NH];
@@ -1823,10 +1814,9 @@ __global__ __launch_bounds__(256) void k_rhs(const double *__restrict__ eta, con
   const int i = t % N1, j = t / N1;
   const int ci = blockIdx.x * CPB + lc;
   const bool active = ci < ncols;
-  const int col = active ? cols[ci] : 0;
-  const int hn = active ? eh_nodes[(int64_t)col * NH + t] : 0;
-  const uint8_t fl = active ? flags[(int64_t)col * NH + t] : 0;
-  const int64_t ho = (int64_t)col * NH + t;
+  const int64_t ho = (int64_t)ci * NH + t;
+  const int hn = active ? eh_nodes[ho] : 0;
+  const int sl = active ? slot[ho] : 0;
   const double en = active ? eta[hn] : 0.0;
   const double pn = active ? phs[hn] : 0.0;
   se[lc * NH + t] = en;
@@ -1862,13 +1852,21 @@ __global__ __launch_bounds__(256) void k_rhs(const double *__restrict__ eta, con
   }
   const double w = wv[hn];
   const double ee = ex * ex + ey * ey;
-  const double Ek = a.linear ? w : -(ex * px + ey * py) + w * (1.0 + ee);
-  const double Ed = a.linear ? -g * en : -g * en - 0.5 * (px * px + py * py) + 0.5 * w * w * (1.0 + ee);
+  const double Ek = linear ? w : -(ex * px + ey * py) + w * (1.0 + ee);
+  const double Ed = linear ? -g * en : -g * en - 0.5 * (px * px + py * py) + 0.5 * w * w * (1.0 + ee);
   const double ms = ws * det;
-  const double sk = scatter(nk, hn, ms * Ek, fl);
-  const double sd = scatter(nd, hn, ms * Ed, fl);
-  if (!(fl & kLast)) return;
-  stage_update(a, hn, sk / mlump_s[hn], sd / mlump_s[hn]);
+  (sl < 0 ? nk + hn : F + sl)[0] = ms * Ek;
+  (sl < 0 ? nk + n_s + hn : F + n_slots + sl)[0] = ms * Ed;
+}
+
+__global__ __launch_bounds__(256) void k_rhs_stage(Deferred<double> k2, const double *__restrict__ mlump_s,
+                                                   int64_t n_s, RkStageArgs a) {
+  const int64_t n = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (n >= n_s) return;
+  double ke, kp;
+  const double m = mlump_s[n];
+  gather_pair(k2, n, n_s, ke, kp);
+  stage_update(a, n, ke / m, kp / m);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -2093,27 +2091,11 @@ hipError_t launch_neumann(Ctx &c, const double *q, double *f, hipStream_t s) {
   return hipSuccess;
 }
 
-template <int P, int DIM>
-static hipError_t wsurf_impl(Ctx &c, const double *phi, double *w, hipStream_t s) {
-  using S = Sh<P, DIM>;
-  const int64_t hs = (int64_t)c.n_eh * c.nh;
-  const double half_ds = 0.5 * (c.h_layer_s[c.nz] - c.h_layer_s[c.nz - 1]);
-  for (const auto &cr : c.colours) {
-    if (cr.count == 0) continue;
-    const int nb = (cr.count + S::CPB - 1) / S::CPB;
-    k_wsurf<P, DIM><<<nb, S::NT, 0, s>>>(phi, c.d_eh_nodes, c.d_flags, c.d_cols + cr.offset, cr.count, c.nz, c.n_s,
-                                         c.d_hm, hs, c.d_geoH, c.d_mlump_w, half_ds, c.d_wnum, w);
-  }
-  return hipGetLastError();
-}
-
 hipError_t launch_wsurf(Ctx &c, const double *phi, double *w, hipStream_t s) {
-  if (c.dim == 3) {
-    FNPF_DISPATCH(3, c.p, return (wsurf_impl<P_, 3>(c, phi, w, s)));
-  } else {
-    FNPF_DISPATCH(2, c.p, return (wsurf_impl<P_, 2>(c, phi, w, s)));
-  }
-  return hipSuccess;
+  const double half_ds = 0.5 * (c.h_layer_s[c.nz] - c.h_layer_s[c.nz - 1]);
+  const unsigned nb = (unsigned)((c.n_s + 255) / 256);
+  FNPF_DISPATCH(0, c.p, (k_wsurf<P_><<<nb, 256, 0, s>>>(phi, c.nz, c.n_s, c.d_geoH, half_ds, w)));
+  return hipGetLastError();
 }
 
 template <int P, int DIM>
@@ -2121,12 +2103,9 @@ static hipError_t rhs_impl(Ctx &c, const double *eta, const double *phs, const d
                            hipStream_t s) {
   using S = Sh<P, DIM>;
   const int64_t hs = (int64_t)c.n_eh * c.nh;
-  for (const auto &cr : c.colours) {
-    if (cr.count == 0) continue;
-    const int nb = (cr.count + S::CPB - 1) / S::CPB;
-    k_rhs<P, DIM><<<nb, S::NT, 0, s>>>(eta, phs, w, c.d_eh_nodes, c.d_flags, c.d_cols + cr.offset, cr.count, c.d_hm,
-                                       hs, c.d_mlump_s, c.g, c.d_nk, c.d_nd, a);
-  }
+  k_rhs<P, DIM><<<(c.n_eh + S::CPB - 1) / S::CPB, S::NT, 0, s>>>(eta, phs, w, c.d_eh_nodes, c.d_slot, c.n_eh, c.d_hm,
+                                                                  hs, c.g, c.d_sk, c.n_s, c.d_sF, c.n_slots, a.linear);
+  k_rhs_stage<<<(unsigned)((c.n_s + 255) / 256), 256, 0, s>>>(surface_result(c, c.d_sk), c.d_mlump_s, c.n_s, a);
   return hipGetLastError();
 }
 

@@ -505,19 +505,7 @@ __global__ __launch_bounds__(kSqThreads) void k_sq_rhs_vjp(
 }
 
 // Chebyshev vector kernels on two fields [2][n_s]; ml = lumped surface mass [n_s].  A thread takes one
-// node and both fields; v: a vector whose face slots are still to be added.
-__device__ __forceinline__ void sq_gather(const Deferred<double> &v, int64_t n, int64_t n_s, double &a, double &b) {
-  a = v.y[n];
-  b = v.y[n_s + n];
-  if (n >= v.n_hi) return;
-  const int4 s = v.slots[n];
-  const double *f = v.F, *g = v.F + v.n_slots;
-  if (s.x >= 0) a += f[s.x], b += g[s.x];
-  if (s.y >= 0) a += f[s.y], b += g[s.y];
-  if (s.z >= 0) a += f[s.z], b += g[s.z];
-  if (s.w > 0) a = list_sum(v, f, s.w, a), b = list_sum(v, g, s.w, b);
-}
-
+// node and both fields.
 // x = b / ml; a deferred b is completed in bw
 __global__ __launch_bounds__(256) void k_sq_init(Deferred<double> b, double *bw, const double *__restrict__ ml,
                                                  double *x, int64_t n_s) {
@@ -525,7 +513,7 @@ __global__ __launch_bounds__(256) void k_sq_init(Deferred<double> b, double *bw,
   if (n >= n_s) return;
   double u, v;
   const double m = ml[n];
-  sq_gather(b, n, n_s, u, v);
+  gather_pair(b, n, n_s, u, v);
   if (bw != nullptr) {
     bw[n] = u;
     bw[n_s + n] = v;
@@ -549,7 +537,7 @@ __global__ __launch_bounds__(256) void k_sq_cheb(const double *__restrict__ x, d
     p0 = c1 * (x0 - xo[n]);
     p1 = c1 * (x1 - xo[n_s + n]);
   }
-  sq_gather(mx, n, n_s, y0, y1);
+  gather_pair(mx, n, n_s, y0, y1);
   xo[n] = x0 + (p0 + c2 * ((b0 - y0) / m));
   xo[n_s + n] = x1 + (p1 + c2 * ((b1 - y1) / m));
 }
@@ -610,26 +598,14 @@ SqLaunch sq_launch(const SqLds &l) {
   return {1, l.per, (size_t)(l.table + l.per) * sizeof(double)};
 }
 
-// two fields y [2][n_s] whose other contributions are in the face slots d_sq_F [2][n_slots]
-Deferred<double> sq_deferred(const Ctx &c, const double *y) {
-  Deferred<double> d;
-  d.y = y;
-  d.F = c.d_sq_F;
-  d.slots = c.d_p_slots;
-  d.lists = c.d_p_lists;
-  d.n_hi = c.p_n_hi;
-  d.n_slots = c.n_slots;
-  return d;
-}
-
 template <int P, int DIM>
 hipError_t sq_rhs_impl(Ctx &c, const double *eta, const double *phs, const double *w, double *b, hipStream_t s) {
   const int64_t ms = (int64_t)c.n_eh * (c.dim == 3 ? c.sq_nq * c.sq_nq : c.sq_nq);
   const SqLaunch L = sq_launch(lds_rhs(c));
   const int nb = (c.n_eh + L.epb - 1) / L.epb;
   k_sq_rhs<P, DIM><<<nb, kSqThreads, L.bytes, s>>>(eta, phs, w, c.d_eh_nodes, c.d_slot, c.n_eh, L.epb, L.per, c.d_sq_B,
-                                                    c.d_sq_Bd, c.sq_nq, c.d_sq_met, ms, c.g, b, b + c.n_s, c.d_sq_F,
-                                                    c.d_sq_F + c.n_slots);
+                                                    c.d_sq_Bd, c.sq_nq, c.d_sq_met, ms, c.g, b, b + c.n_s, c.d_sF,
+                                                    c.d_sF + c.n_slots);
   return hipGetLastError();
 }
 
@@ -640,13 +616,13 @@ hipError_t sq_mass_impl(Ctx &c, const double *x, double *y, hipStream_t s) {
   if constexpr (DIM == 3) {
     const int lanes = 2 * std::max(c.p + 1, c.sq_nq), epb = kSqThreads / lanes;
     const size_t bytes = (size_t)epb * 2 * (c.p + 1) * c.sq_nq * sizeof(double);
-    k_sq_mass3<P><<<(c.n_eh + epb - 1) / epb, kSqThreads, bytes, s>>>(x, y, c.d_sq_F, c.n_s, c.n_slots, c.d_eh_nodes,
+    k_sq_mass3<P><<<(c.n_eh + epb - 1) / epb, kSqThreads, bytes, s>>>(x, y, c.d_sF, c.n_s, c.n_slots, c.d_eh_nodes,
                                                                        c.d_slot, c.n_eh, lanes, c.d_sq_B, c.sq_nq,
                                                                        wdet);
   } else {
     const int64_t n = 2 * (int64_t)c.n_eh;
     k_sq_mass2<P><<<(unsigned)((n + kSqThreads - 1) / kSqThreads), kSqThreads, 0, s>>>(
-        x, y, c.d_sq_F, c.n_s, c.n_slots, c.d_eh_nodes, c.d_slot, c.n_eh, c.d_sq_B, c.sq_nq, wdet);
+        x, y, c.d_sF, c.n_s, c.n_slots, c.d_eh_nodes, c.d_slot, c.n_eh, c.d_sq_B, c.sq_nq, wdet);
   }
   return hipGetLastError();
 }
@@ -739,14 +715,14 @@ hipError_t sq_solve(Ctx &c, double *b, double *x, bool b_slots, hipStream_t s) {
   const double theta = 0.5 * (c.sq_hi + c.sq_lo), delta = 0.5 * (c.sq_hi - c.sq_lo);
   const double sigma = theta / delta;
   double *cur = (c.sq_iters & 1) ? c.d_sq_d : x, *oth = (c.sq_iters & 1) ? x : c.d_sq_d;   // x_K lands in x
-  Deferred<double> bd = sq_deferred(c, b);
+  Deferred<double> bd = surface_result(c, b);
   if (!b_slots) bd.n_hi = 0;
   k_sq_init<<<nb, 256, 0, s>>>(bd, b_slots ? b : nullptr, c.d_mlump_s, cur, ns);
   double rho = 1.0 / sigma, c1 = 0.0, c2 = 1.0 / theta;
   for (int k = 0; k < c.sq_iters; ++k) {
     const hipError_t e = sq_mass(c, cur, c.d_sq_ad, s);
     if (e != hipSuccess) return e;
-    k_sq_cheb<<<nb, 256, 0, s>>>(cur, oth, sq_deferred(c, c.d_sq_ad), b, c.d_mlump_s, c1, c2, ns);
+    k_sq_cheb<<<nb, 256, 0, s>>>(cur, oth, surface_result(c, c.d_sq_ad), b, c.d_mlump_s, c1, c2, ns);
     std::swap(cur, oth);
     const double rho_n = 1.0 / (2.0 * sigma - rho);
     c1 = rho_n * rho;
@@ -768,7 +744,7 @@ hipError_t launch_sq_pack(const double *a, const double *b, double *out, int64_t
 
 void sq_free(Ctx &c) {
   double **bufs[] = {&c.d_sq_B, &c.d_sq_Bd, &c.d_sq_met, &c.d_sq_b, &c.d_sq_x,
-                     &c.d_sq_F, &c.d_sq_d,  &c.d_sq_ad,  &c.d_sq_scr};
+                     &c.d_sq_d, &c.d_sq_ad, &c.d_sq_scr};
   for (double **p : bufs) {
     if (*p) (void)hipFree(*p);
     *p = nullptr;
@@ -855,8 +831,6 @@ const char *sq_setup(Ctx &c, int nq) {
   for (double **v : vecs)
     if (hipMalloc(v, 2 * c.n_s * sizeof(double)) != hipSuccess) return "surface quadrature: allocation";
   if (hipMalloc(&c.d_sq_scr, 3 * c.n_s * sizeof(double)) != hipSuccess) return "surface quadrature: allocation";
-  if (hipMalloc(&c.d_sq_F, 2 * std::max<int64_t>(c.n_slots, 1) * sizeof(double)) != hipSuccess)
-    return "surface quadrature: allocation";
   c.sq_lo = lo;
   c.sq_hi = hi;
   const double kappa = hi / lo;
