@@ -1091,6 +1091,27 @@ float *&p1_values<float>(Ctx &c) { return c.d_p1_val32; }
 // whole at every step (216 bytes in FP64), so beyond it the matrix-free apply moves less.
 constexpr size_t kP1MaxBytes = size_t(96) << 20;
 
+// Rows are padded with zero entries to a width that the kernels know at compile time, so that all
+// loads of a row are in flight together: slices, quadrilaterals four to a node, five and six to a
+// node.  On the tank around a cylinder (2,922 x 5 rows, at most 11 neighbours) a step takes 4.4 us,
+// with the width as an argument 6.2 us.
+constexpr int kP1Widths[] = {3, 9, 11, 13};
+static size_t p1_width(size_t w) {
+  for (const int k : kP1Widths)
+    if (w <= (size_t)k) return k;
+  return w;
+}
+template <typename F>
+void with_p1_width(int w, F f) {
+  switch (w) {
+    case 3: f(std::integral_constant<int, 3>()); break;
+    case 9: f(std::integral_constant<int, 9>()); break;
+    case 11: f(std::integral_constant<int, 11>()); break;
+    case 13: f(std::integral_constant<int, 13>()); break;
+    default: f(std::integral_constant<int, 0>()); break;
+  }
+}
+
 // Neighbour lists of a degree-1 level (host, once).
 fnpf_status p1_build(Ctx &c) {
   const int nh = c.nh;
@@ -1118,6 +1139,7 @@ fnpf_status p1_build(Ctx &c) {
       map[o * nh + b] = (uint8_t)k;
     }
   }
+  w = p1_width(w);
   std::vector<int32_t> list(w * c.n_s);
   for (size_t k = 0; k < w; ++k)
     for (int64_t n = 0; n < c.n_s; ++n) list[k * c.n_s + n] = k < nb[n].size() ? nb[n][k] : (int32_t)n;
@@ -1149,9 +1171,12 @@ hipError_t p1_smooth(Ctx &L, const Deferred<T> &b, T *x, T *r, T *d, T *d2, cons
                      hipStream_t s) {
   const T *dinv = Prec<T>::dinv(L), *val = p1_values<T>(L);
   const int nlev = L.nz + 1;
-  if (L.n_v <= kP1One && (L.p1_w == 3 || L.p1_w == 9)) {
-    auto kern = L.p1_w == 3 ? k_p1_all<3, T> : k_p1_all<9, T>;
-    kern<<<1, (unsigned)((L.n_v + 63) / 64 * 64), 0, s>>>(b, x, val, L.d_p1_nb, dinv, cf, (int)L.n_s, nlev, skip);
+  if (L.n_v <= kP1One && L.p1_w <= kP1Widths[2]) {   // (13 entries in FP64 do not fit its registers)
+    with_p1_width(L.p1_w, [&](auto w) {
+      if constexpr (w() > 0 && w() <= kP1Widths[2])
+        k_p1_all<w(), T><<<1, (unsigned)((L.n_v + 63) / 64 * 64), 0, s>>>(b, x, val, L.d_p1_nb, dinv, cf, (int)L.n_s,
+                                                                          nlev, skip);
+    });
     return hipGetLastError();
   }
   const int nlv = node_levels(L);
@@ -1159,9 +1184,10 @@ hipError_t p1_smooth(Ctx &L, const Deferred<T> &b, T *x, T *r, T *d, T *d2, cons
     k_cheb0<lv(), T><<<node_blocks(L, nlv), kVecThreads, 0, s>>>(b, nullptr, r, d, x, dinv, cf, L.n_s, skip);
   });
   const dim3 nb((unsigned)((L.n_s + 255) / 256), nlev);
-  auto kern = L.p1_w == 3 ? k_p1_step<3, T> : L.p1_w == 9 ? k_p1_step<9, T> : k_p1_step<0, T>;
   for (int k = 2; k <= kMgCoarseSteps; ++k) {
-    kern<<<nb, 256, 0, s>>>(val, L.d_p1_nb, L.p1_w, r, d, d2, x, dinv, cf, k, L.n_s, nlev, skip);
+    with_p1_width(L.p1_w, [&](auto w) {
+      k_p1_step<w(), T><<<nb, 256, 0, s>>>(val, L.d_p1_nb, L.p1_w, r, d, d2, x, dinv, cf, k, L.n_s, nlev, skip);
+    });
     std::swap(d, d2);
   }
   return hipGetLastError();
