@@ -95,6 +95,9 @@ hipError_t launch_geom(Ctx &c, const double *eta, const double *h, bool store_G,
 hipError_t ensure_diag(Ctx &c, hipStream_t s);
 hipError_t launch_apply(Ctx &c, fnpf_dtype dt, const void *x, void *y, bool mask, double *partial,
                         const int32_t *skip, hipStream_t s, void *face_scratch = nullptr, bool defer = false);
+bool apply_restrict_active(const Ctx &F);
+hipError_t launch_apply_restrict(Ctx &F, Ctx &C, fnpf_dtype dt, const void *x, const void *b, void *bc, void *Fc,
+                                 int lpc, const int32_t *skip, hipStream_t s);
 hipError_t launch_neumann(Ctx &c, const double *q, double *f, hipStream_t s);
 hipError_t launch_wsurf(Ctx &c, const double *phi, double *w, hipStream_t s);
 struct RkStageArgs {
@@ -306,6 +309,8 @@ struct Ctx {
   // assembled operator of a degree-1 level that ends a multigrid hierarchy (multigrid.hip): up to
   // p1_w neighbours per horizontal node (itself among them) on three levels
   int p1_w = 0;
+  const double *d_ip64 = nullptr;         // [p + 1][p / 2 + 1] coarse basis at the nodes (not owned)
+  const float *d_ip32 = nullptr;
   int32_t *d_p1_nb = nullptr;             // [p1_w][n_s] neighbour nodes (padded with the node itself)
   int32_t *d_p1_ptr = nullptr, *d_p1_inc = nullptr;   // per node its (column, local node) entries
   uint8_t *d_p1_map = nullptr;            // [n_eh * nh][nh] place of a column's node b among a's neighbours

@@ -945,15 +945,25 @@ hipError_t surf_impl(Ctx &F, Ctx &C, double *Hc, double *hc, hipStream_t s) {
   return hipGetLastError();
 }
 
-// b_c = P^T (r_f - q_f), its assembly left to the reader
+// b_c = P^T (r_f - A x), its assembly left to the reader (q: work vector for A x)
 template <typename T>
-hipError_t restrict_to(Ctx &F, Ctx &C, const T *rf, const Deferred<T> &qf, T *bc, Deferred<T> &out, const int32_t *skip,
+hipError_t restrict_to(Ctx &F, Ctx &C, const T *rf, const T *x, T *q, T *bc, Deferred<T> &out, const int32_t *skip,
                        hipStream_t s) {
   T *Fc = face_buffer<T>(C);
-  if (F.dim == 3) {
-    MG_DISPATCH(3, F.p, { hipError_t e = (restrict_impl<PF_, 3, T>(F, C, rf, qf, bc, Fc, skip, s)); if (e != hipSuccess) return e; });
-  } else {
-    MG_DISPATCH(2, F.p, { hipError_t e = (restrict_impl<PF_, 2, T>(F, C, rf, qf, bc, Fc, skip, s)); if (e != hipSuccess) return e; });
+  const int lpc = transfer_lpc(F, C);
+  hipError_t er;
+  if (apply_restrict_active(F))
+    er = launch_apply_restrict(F, C, Prec<T>::dt, x, rf, bc, Fc, lpc, skip, s);
+  else
+    er = launch_apply(F, Prec<T>::dt, x, q, true, nullptr, skip, s, nullptr, true);
+  if (er != hipSuccess) return er;
+  const Deferred<T> qf = apply_result<T>(F, q);
+  if (!apply_restrict_active(F)) {
+    if (F.dim == 3) {
+      MG_DISPATCH(3, F.p, { hipError_t e = (restrict_impl<PF_, 3, T>(F, C, rf, qf, bc, Fc, skip, s)); if (e != hipSuccess) return e; });
+    } else {
+      MG_DISPATCH(2, F.p, { hipError_t e = (restrict_impl<PF_, 2, T>(F, C, rf, qf, bc, Fc, skip, s)); if (e != hipSuccess) return e; });
+    }
   }
   out = complete<T>(C, bc);
   out.F = Fc;
@@ -962,7 +972,6 @@ hipError_t restrict_to(Ctx &F, Ctx &C, const T *rf, const Deferred<T> &qf, T *bc
   out.n_hi = C.p_n_hi;
   out.n_slots = C.n_slots;
   out.vend = out.nlev - 1;
-  const int lpc = transfer_lpc(F, C);
   out.clev = lpc * C.p;
   out.nchunk = (F.nz + lpc - 1) / lpc;
   return hipSuccess;
@@ -1231,8 +1240,7 @@ hipError_t vcycle(Ctx &c, int l, const Deferred<T> &b, T *x, const int32_t *skip
       with_levels(nlv, [&](auto lv) { k_scale<lv(), T><<<nb, kVecThreads, 0, s>>>(d, b, b.F != nullptr ? const_cast<T *>(b.y) : nullptr, dinv, cf, ns, skip); });
     if ((e = product(d, q)) != hipSuccess) return e;
     with_levels(nlv, [&](auto lv) { k_pre2<lv(), T><<<nb, kVecThreads, 0, s>>>(x, b.y, apply_result<T>(L, q), dinv, cf, ns, skip); });
-    if ((e = product(x, q)) != hipSuccess) return e;
-    if ((e = restrict_to<T>(L, *C.c, b.y, apply_result<T>(L, q), bc, bd, skip, s)) != hipSuccess) return e;   // P^T (b - A x)
+    if ((e = restrict_to<T>(L, *C.c, b.y, x, q, bc, bd, skip, s)) != hipSuccess) return e;
     if ((e = vcycle<T>(c, l + 1, bd, xc, skip, m, s)) != hipSuccess) return e;
     if ((e = prolong_to<T>(L, *C.c, xc, x, skip, s)) != hipSuccess) return e;
     if ((e = product(x, q)) != hipSuccess) return e;
@@ -1249,8 +1257,7 @@ hipError_t vcycle(Ctx &c, int l, const Deferred<T> &b, T *x, const int32_t *skip
   e = smooth<T>(L, b, x, r, d, q, cf, m, true, skip, s, line);
   if (e != hipSuccess) return e;
   // residual of the smoothed x, r - A d, restricted directly
-  if ((e = product(d, q)) != hipSuccess) return e;
-  e = restrict_to<T>(L, *C.c, r, apply_result<T>(L, q), bc, bd, skip, s);
+  e = restrict_to<T>(L, *C.c, r, d, q, bc, bd, skip, s);
   if (e != hipSuccess) return e;
   e = vcycle<T>(c, l + 1, bd, xc, skip, m, s);
   if (e != hipSuccess) return e;
@@ -1510,6 +1517,16 @@ fnpf_status mg_build(Ctx &c) {
   if (dalloc_t(&c.d_mg_lz, (size_t)kLzScalars) != hipSuccess) return FNPF_ERR_ALLOC;
   if (dalloc_t(&c.d_mg_lam, (size_t)2 * (c.mg.size() + 1)) != hipSuccess) return FNPF_ERR_ALLOC;
   if (hipMemset(c.d_mg_lam, 0, sizeof(double) * 2 * (c.mg.size() + 1)) != hipSuccess) return FNPF_ERR_HIP;
+  void *ip64 = nullptr, *ip32 = nullptr;
+  if (hipGetSymbolAddress(&ip64, HIP_SYMBOL(c_IP64)) != hipSuccess ||
+      hipGetSymbolAddress(&ip32, HIP_SYMBOL(c_IP32)) != hipSuccess)
+    return FNPF_ERR_HIP;
+  auto tables = [&](Ctx &L) {
+    L.d_ip64 = (const double *)ip64 + L.p * kMaxN1 * kMaxN1;
+    L.d_ip32 = (const float *)ip32 + L.p * kMaxN1 * kMaxN1;
+  };
+  tables(c);
+  for (auto &L : c.mg) tables(*L.c);
   c.mg_built = true;
   c.mg_stale64 = c.mg_stale32 = true;
   return FNPF_OK;
