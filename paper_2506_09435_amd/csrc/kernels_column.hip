@@ -1298,16 +1298,16 @@ __global__ __launch_bounds__(256) void k_geom(const double *__restrict__ eta, co
   // The diagonal at node (i, j, k) of an element, collocated quadrature:
   //   sum_m D[m][i]^2 G_xx(m, j, k) + sum_m D[m][j]^2 G_yy(i, m, k) + sum_m D[m][k]^2 G_zz(i, j, m)
   //   + 2 (D_ii D_jj G_xy + D_ii D_kk G_xz + D_jj D_kk G_yz)(i, j, k).
-  // sA holds G_xx at the element's points (plane k, row j, entry i at k NH + j N1 + i) and then, in
-  // place, its xi-line sums; sB the same for G_yy along eta-lines; the zeta sums use the thread's
-  // own vertical line in registers.  sX: the partners' values at shared nodes (OWN) and, before
-  // the layer loop, the surface H and h of the block's columns.
-  constexpr int NX0 = 2 * CPB * NH, NX1 = OWN ? N1 * XM : 0;
-  // sB's plane stride padded as the apply's eta-line array: SB = N1 (mod 64), so the 64 lanes of
-  // a wave reading their eta-lines start in distinct banks (degrees < 4: N1 mod 16)
-  constexpr int SB = DIM == 3 ? eta_plane_stride(P) : NH;
-  __shared__ double sA[CPB * NP];
-  __shared__ double sB[DIM == 3 ? CPB * N1 * SB : 1];
+  // In extruded columns G_xx, G_yy and G_xy separate into w_k half_ds[l] times a function of (i, j),
+  // so their part of it is base(i, j) w_k half_ds[l], one set of line sums per column (sA, sB); the
+  // zeta sums use the thread's own vertical line in registers.  sX: the surface H and h of the
+  // block's columns, then the partners' values at shared nodes (OWN), of two layers in turn, so that
+  // one barrier a layer separates writes and reads.  Bound by memory: on the sea of 256 x 128 x 6
+  // elements, p = 6, 204 us for some 560 MB (inverses, face layout, column data); with line sums at
+  // every level of every layer 327 us.
+  constexpr int NX0 = 2 * CPB * NH, NX1 = OWN ? 2 * N1 * XM : 0;
+  __shared__ double sA[CPB * NH];
+  __shared__ double sB[DIM == 3 ? CPB * NH : 1];
   __shared__ double sX[NX0 > NX1 ? NX0 : NX1];
   double *sH = sX, *sh = sX + CPB * NH;
 
@@ -1410,9 +1410,6 @@ __global__ __launch_bounds__(256) void k_geom(const double *__restrict__ eta, co
   }
   const double wh = DIM == 3 ? wgt(P, i) * wgt(P, j) : wgt(P, i);
   const double Dii = dmat<double>(P, i, i), Djj = DIM == 3 ? dmat<double>(P, j, j) : 0.0;
-  double *Ab = sA + lc * NP;
-  double *Bb = sB + (DIM == 3 ? lc * N1 * SB : 0);
-
   // 3D: the horizontal part of J^-T grad(.) picks up b2 = -(J_h^-T grad z) / z_zeta, and
   // grad z = sigma grad H - grad h is linear in sigma along the line: b2 = (sigma a0 + b0) / z_zeta
   // with a0, b0 per column node; the products of A in the factors are per column node as well
@@ -1421,10 +1418,23 @@ __global__ __launch_bounds__(256) void k_geom(const double *__restrict__ eta, co
   const double c00 = A00 * A00 + A01 * A01, c11 = A10 * A10 + A11 * A11, c01 = A00 * A10 + A01 * A11;
   const double whd = wh * detJh;
 
+  // base(i, j): see above
+  const double whH = wh * detJh * Hn;
+  sA[lc * NH + t] = whH * (DIM == 3 ? c00 : A00 * A00);
+  if constexpr (DIM == 3) sB[lc * NH + t] = whH * c11;
+  __syncthreads();
+  double base = DIM == 3 ? 2.0 * (Dii * Djj * (whH * c01)) : 0.0;
+#pragma unroll
+  for (int m = 0; m < N1; ++m) {
+    base += c_DSQ64[P * kDStride + m * N1 + i] * sA[lc * NH + j * N1 + m];
+    if constexpr (DIM == 3) base += c_DSQ64[P * kDStride + m * N1 + j] * sB[lc * NH + m * N1 + i];
+  }
+
   double carry = 0.0;
   const int64_t e0 = (int64_t)col * nz;
   for (int l = 0; l < nz; ++l) {
-    const double zz = 0.5 * (layer_s[l + 1] - layer_s[l]) * Hn;   // z_zeta (sigma-linear per layer)
+    const double hds = 0.5 * (layer_s[l + 1] - layer_s[l]);
+    const double zz = hds * Hn;   // z_zeta (sigma-linear per layer)
     const double izz = 1.0 / zz;
     const double ax = ax0 * izz, bx = bx0 * izz, ay = ay0 * izz, by = by0 * izz, izz2 = izz * izz;
     const double fzl = whd * zz;   // the point's factor w_i w_j w_k det J is w_k fzl
@@ -1439,10 +1449,10 @@ __global__ __launch_bounds__(256) void k_geom(const double *__restrict__ eta, co
         const double f = wgt(P, k) * fzl;
         const double b2x = sg * ax + bx;
         const double b2y = sg * ay + by;
-        const double g00 = f * c00;
-        const double g11 = f * c11;
         const double g22 = f * (b2x * b2x + b2y * b2y + izz2);
         if (SG && active && Ge64) {
+          const double g00 = f * c00;
+          const double g11 = f * c11;
           const double g01 = f * c01;
           const double g02 = f * (A00 * b2x + A01 * b2y);
           const double g12 = f * (A10 * b2x + A11 * b2y);
@@ -1461,17 +1471,15 @@ __global__ __launch_bounds__(256) void k_geom(const double *__restrict__ eta, co
             Ge32[5 * NP + q] = (float)g22;
           }
         }
-        Ab[q] = g00;
-        Bb[k * SB + t] = g11;
         gz[k] = g22;
       } else {
         const double zx = -hx + sg * Hx;
         const double f = wh * wgt(P, k) * detJh * zz;
         const double b1x = -zx * A00 * izz;
         const double b1z = izz;
-        const double g00 = f * A00 * A00;
         const double g11 = f * (b1x * b1x + b1z * b1z);
         if (SG && active && Ge64) {
+          const double g00 = f * A00 * A00;
           const double g01 = f * A00 * b1x;
           Ge64[0 * NP + q] = g00;
           Ge64[1 * NP + q] = g01;
@@ -1482,101 +1490,69 @@ __global__ __launch_bounds__(256) void k_geom(const double *__restrict__ eta, co
             Ge32[2 * NP + q] = (float)g11;
           }
         }
-        Ab[q] = g00;
         gz[k] = g11;
       }
     }
-    __syncthreads();
-    // line sums in place: the thread's xi-line (j = a, k = b) and, in 3D, eta-line (i = a,
-    // k = b), t = b N1 + a; out_r = sum_m D[m][r]^2 in_m (even-odd form up to degree 6)
-    {
-      auto line_sum = [&](const double(&in)[N1], double(&out)[N1]) {
-        if constexpr (P <= 6) {
-          line_sq_eo<P>(in, out, sqeo_ptr(P, in[0]));
-        } else {
-          const double *Q = dsq_ptr(P, in[0]);
+    // the node's diagonal at each level of the layer element: zeta sums out_r = sum_m D[m][r]^2 in_m
+    // (even-odd form up to degree 6), the horizontal part, and at the element's bottom and top (D_kk
+    // vanishes elsewhere) the cross terms
+    double d[N1];
+    if constexpr (P <= 6) {
+      line_sq_eo<P>(gz, d, sqeo_ptr(P, gz[0]));
+    } else {
 #pragma unroll
-          for (int r = 0; r < N1; ++r) {
-            double a = 0.0;
+      for (int r = 0; r < N1; ++r) {
+        const double *Q = dsq_ptr(P, r > 0 ? d[r - 1] : gz[0]);   // the table's columns one after the other
+        double a = 0.0;
 #pragma unroll
-            for (int m = 0; m < N1; ++m) a += Q[m * N1 + r] * in[m];
-            out[r] = a;
-          }
-        }
-      };
-      double in[N1], out[N1];
-#pragma unroll
-      for (int m = 0; m < N1; ++m) in[m] = Ab[t * N1 + m];
-      line_sum(in, out);
-#pragma unroll
-      for (int r = 0; r < N1; ++r) Ab[t * N1 + r] = out[r];
-      if constexpr (DIM == 3) {
-        const int eb = (t / N1) * SB + t % N1;
-#pragma unroll
-        for (int m = 0; m < N1; ++m) in[m] = Bb[eb + m * N1];
-        line_sum(in, out);
-#pragma unroll
-        for (int r = 0; r < N1; ++r) Bb[eb + r * N1] = out[r];
+        for (int m = 0; m < N1; ++m) a += Q[m * N1 + r] * gz[m];
+        d[r] = a;
       }
     }
-    __syncthreads();
-    // the node's diagonal at each level of the layer element, one level at a time; the node's own
-    // entry of sA (read here by this thread only) then holds its value for the tile assembly
-    const int kh = (l == nz - 1) ? N1 : P;   // levels stored by this layer (the top one by the next)
-    double top = 0.0;
-#pragma unroll 1
+    const double bl = base * hds;
+#pragma unroll
     for (int k = 0; k < N1; ++k) {
-      double d = Ab[k * NH + t];
-      if constexpr (DIM == 3) d += Bb[k * SB + t];
-      const double *Qk = dsq_ptr(P, d) + k;
-#pragma unroll
-      for (int m = 0; m < N1; ++m) d += Qk[m * N1] * gz[m];
-      const double Dkk = dmat<double>(P, k, k);
-      const double sg = sigma[l * P + k];
-      if constexpr (DIM == 3) {
-        const double f = wgt(P, k) * fzl;
-        const double f01 = f * c01;
-        if (Dkk != 0.0) {   // uniform: D_kk vanishes except at the element's bottom and top levels
-          const double b2x = sg * ax + bx;
-          const double b2y = sg * ay + by;
-          const double f02 = f * (A00 * b2x + A01 * b2y);
-          const double f12 = f * (A10 * b2x + A11 * b2y);
-          d += 2.0 * (Dii * Djj * f01 + Dii * Dkk * f02 + Djj * Dkk * f12);
+      d[k] += wgt(P, k) * bl;
+      if (k == 0 || k == P) {
+        const double Dkk = dmat<double>(P, k, k), sg = sigma[l * P + k], f = wgt(P, k) * fzl;
+        if constexpr (DIM == 3) {
+          const double b2x = sg * ax + bx, b2y = sg * ay + by;
+          d[k] += 2.0 * Dkk * (Dii * (f * (A00 * b2x + A01 * b2y)) + Djj * (f * (A10 * b2x + A11 * b2y)));
         } else {
-          d += 2.0 * (Dii * Djj * f01);
+          const double b1x = -(-hx + sg * Hx) * A00 * izz;
+          d[k] += 2.0 * Dii * Dkk * (f * A00 * b1x);
         }
-      } else {
-        const double zx = -hx + sg * Hx;
-        const double f = wh * wgt(P, k) * detJh * zz;
-        const double b1x = -zx * A00 * izz;
-        const double c01 = f * A00 * b1x;
-        d += 2.0 * Dii * Dkk * c01;
       }
-      if (k == 0) d += carry;
-      if (k == P) top = d;
-      if (k < kh) {
-        if constexpr (OWN) {
-          if (xw >= 0)
-            sX[k * XM + xw] = d;
-          else
-            Ab[k * NH + t] = d;
-        } else if (active) {
-          const int v = l * P + k;
-          const int64_t idx = (int64_t)v * n_s + hn;
-          const double val = scatter(diag, idx, d, fl);
-          if (fl & kLast) {
-            const double di = (v == P * nz) ? 0.0 : recip(val);
-            dinv[idx] = di;
-            if (dinv32) dinv32[idx] = (float)di;
+    }
+    d[0] += carry;
+    carry = d[P];
+    const int kh = (l == nz - 1) ? N1 : P;   // levels stored by this layer (the top one by the next)
+    if constexpr (!OWN) {
+      if (active) {
+#pragma unroll
+        for (int k = 0; k < N1; ++k) {
+          if (k < kh) {
+            const int v = l * P + k;
+            const int64_t idx = (int64_t)v * n_s + hn;
+            const double val = scatter(diag, idx, d[k], fl);
+            if (fl & kLast) {
+              const double di = (v == P * nz) ? 0.0 : recip(val);
+              dinv[idx] = di;
+              if (dinv32) dinv32[idx] = (float)di;
+            }
           }
         }
       }
     }
-    carry = top;
     if constexpr (OWN) {
+      double *sx = sX + (l & 1) * (N1 * XM);
+      if (xw >= 0) {
+#pragma unroll
+        for (int k = 0; k < N1; ++k)
+          if (k < kh) sx[k * XM + xw] = d[k];
+      }
       __syncthreads();
-      // representatives add their partners' values and store (the next writes to sX follow the
-      // next layer's first barrier; sA's own entries are rewritten by this thread only)
+      // representatives add their partners' values and store
       // the per-thread conditions are re-derived here from one opaque word, so the compiler does
       // not keep a 64-bit lane mask per condition live across the layer loop (which spilled
       // scalar registers to vector lanes)
@@ -1587,8 +1563,8 @@ __global__ __launch_bounds__(256) void k_geom(const double *__restrict__ eta, co
         for (int k = 0; k < N1; ++k) {
           if (k < kh) {
             // partners' entries read unconditionally at clamped (valid) places, then selected
-            const double p0 = sX[k * XM + xc0], p1 = sX[k * XM + xc1], p2 = sX[k * XM + xc2];
-            double a = Ab[k * NH + t];
+            const double p0 = sx[k * XM + xc0], p1 = sx[k * XM + xc1], p2 = sx[k * XM + xc2];
+            double a = d[k];
             a += (sm & kSmX0) ? p0 : 0.0;
             a += (sm & kSmX1) ? p1 : 0.0;
             a += (sm & kSmX2) ? p2 : 0.0;
