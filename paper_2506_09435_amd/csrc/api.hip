@@ -657,10 +657,10 @@ fnpf_status fnpf_create(const fnpf_mesh_desc *m, fnpf_ctx *out) {
   fnpf_ctx_s *h = new (std::nothrow) fnpf_ctx_s();
   if (!h) return FNPF_ERR_ALLOC;
   Ctx &c = h->c;
-  std::vector<double> hm, ms;
+  std::vector<double> hm, mw, ms;
   std::vector<uint8_t> flags;
   std::vector<int32_t> cols;
-  std::string e = build_host_mesh(*m, c, hm, flags, cols, ms);
+  std::string e = build_host_mesh(*m, c, hm, flags, cols, mw, ms);
   if (!e.empty()) {
     g_create_error = e;
     delete h;

@@ -429,6 +429,6 @@ void gll_host(int p, double *x, double *w, double *D);
 std::string coarse_numbering(const Ctx &f, int pc, std::vector<int32_t> &nodes, int64_t &n_s);
 std::string surface_interp_weights(const Ctx &c, int32_t n_pts, const double *pts, int32_t *node, double *w);
 std::string build_host_mesh(const fnpf_mesh_desc &m, Ctx &c, std::vector<double> &hm, std::vector<uint8_t> &flags,
-                            std::vector<int32_t> &cols, std::vector<double> &mlump_s);
+                            std::vector<int32_t> &cols, std::vector<double> &mlump_w, std::vector<double> &mlump_s);
 
 }  // namespace fnpf

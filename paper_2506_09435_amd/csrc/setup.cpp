@@ -151,7 +151,7 @@ Pt edge_point(Pt a, Pt b, const double *arc, double t) {
 }  // namespace
 
 std::string build_host_mesh(const fnpf_mesh_desc &m, Ctx &c, std::vector<double> &hm, std::vector<uint8_t> &flags,
-                            std::vector<int32_t> &cols, std::vector<double> &mlump_s) {
+                            std::vector<int32_t> &cols, std::vector<double> &mlump_w, std::vector<double> &mlump_s) {
   char buf[256];
   const int dim = m.dim, p = m.p, n1 = p + 1;
   const int nh = dim == 3 ? n1 * n1 : n1;
@@ -258,8 +258,9 @@ std::string build_host_mesh(const fnpf_mesh_desc &m, Ctx &c, std::vector<double>
       }
   }
   c.h_xh = xh;
-  // horizontal metrics and lumped mass
+  // horizontal metrics and lumped masses
   hm.assign((size_t)ncomp * n_eh * nh, 0.0);
+  mlump_w.assign(n_s, 0.0);
   mlump_s.assign(n_s, 0.0);
   const int64_t stride = n_eh * nh;
   for (int64_t e = 0; e < n_eh; ++e) {
@@ -307,6 +308,7 @@ std::string build_host_mesh(const fnpf_mesh_desc &m, Ctx &c, std::vector<double>
       }
       int32_t id = m.eh_nodes[o];
       mlump_s[id] += ws * det;
+      mlump_w[id] += ws * w[p] * det;
     }
   }
 
