@@ -774,6 +774,7 @@ struct RestrictArgs {
   const uint8_t *flags = nullptr;
   int64_t n_s = 0, n_slots = 0;
 };
+struct NoRestrict {};   // the other forms' kernels carry no such argument
 template <int P, typename T, bool MASK, bool DOT, bool OWN = false, bool SPLIT = false, bool RES = false>
 __global__ __launch_bounds__(256) void k_apply_lines(const T *__restrict__ x, T *__restrict__ y,
                                                      const T *__restrict__ cg, const T *__restrict__ hmT,
@@ -787,7 +788,7 @@ __global__ __launch_bounds__(256) void k_apply_lines(const T *__restrict__ x, T 
                                                      const int32_t *__restrict__ slot = nullptr,
                                                      int64_t n_slots = 0,
                                                      const int16_t *__restrict__ xch = nullptr, int lpc = 0,
-                                                     RestrictArgs<T> ra = {}) {
+                                                     std::conditional_t<RES, RestrictArgs<T>, NoRestrict> ra = {}) {
   using S = Sh<P, 3>;
   constexpr int N1 = S::N1, NH = S::NH, NP = S::NP, CPB = S::CPB;
   constexpr GllTab<P> gll{};
@@ -2048,7 +2049,7 @@ static hipError_t apply_impl(Ctx &c, const T *x, T *y, const T *G, double *parti
                                           : k_apply_lines<P, T, MASK, DOT, true, false>;
           kern<<<owner_apply_blocks(c), S::NT, 0, s>>>(
               x, y, cg, hmT, hs, sig, hds, c.d_eh_nodes, c.d_flags, nullptr, c.n_eh, c.nz, c.n_s,
-              DOT ? partial : nullptr, skip, F, c.d_tslot, c.n_tslots, c.d_xch, c.lpc, RestrictArgs<T>{});
+              DOT ? partial : nullptr, skip, F, c.d_tslot, c.n_tslots, c.d_xch, c.lpc, NoRestrict{});
         } else {
           k_apply_fused2<P, DIM, T, MASK, DOT, true><<<dim3(owner_tiles(c.n_eh, c.nh), owner_chunks(c)), S::NT, 0, s>>>(
               x, y, cg, hmT, hs, sig, hds, c.d_eh_nodes, c.d_flags, nullptr, c.n_eh, c.nz, c.n_s,
