@@ -34,7 +34,9 @@
  *   - Every call returns a status and never aborts or throws across the ABI.
  *     Argument validation happens before any HIP call.  fnpf_last_error
  *     returns a message for the last failing call on a context.
- *   - A context is not thread-safe; distinct contexts are independent.
+ *   - A context is not thread-safe; distinct contexts are independent.  Calls
+ *     on one context share its workspaces: enqueue them on one stream, or
+ *     order the streams by events.
  */
 #ifndef FNPF_H
 #define FNPF_H

@@ -789,7 +789,7 @@ fnpf_status fnpf_create(const fnpf_mesh_desc *m, fnpf_ctx *out) {
   AL(c.d_geoH, c.n_s);
   AL(c.d_geoh, c.n_s);
   AL(c.d_sk, 2 * c.n_s);
-  AL(c.d_sF, 3 * std::max<int64_t>(c.n_slots, 1));
+  AL(c.d_sF, kSlotRows * std::max<int64_t>(c.n_slots, 1));
   {
     const auto uses = partial_uses(c.max_colour_blocks, owner_apply_blocks(c));
     c.n_partial = (int)partial_capacity(uses);

@@ -183,6 +183,9 @@ struct MgLevel {
   bool ev_ok64 = false, ev_ok32 = false;
 };
 
+// rows of Ctx::d_sF: the RHS (lumped or consistent, with its mass solves), its VJP, the geometry's VJP
+constexpr int kSlotsRhsVjp = 2, kSlotsGeomVjp = 5, kSlotRows = 7;
+
 struct Ctx {
   // mesh
   int dim = 3, p = 1, nz = 1, n_eh = 0;
@@ -284,7 +287,7 @@ struct Ctx {
   double *d_w = nullptr;                  // recovered w at the surface
   double *d_geoH = nullptr, *d_geoh = nullptr;    // eta + h and h of the last fnpf_geom
   double *d_sk = nullptr;   // [2][n_s] surface right-hand sides, owned contributions
-  double *d_sF = nullptr;   // [3][n_slots] face slots of the surface kernels
+  double *d_sF = nullptr;   // [kSlotRows][n_slots] face slots of the surface kernels, rows of its own each
   double *d_partial = nullptr;
   int n_partial = 0;                       // capacity: partial_capacity(partial_uses(...))
   double *d_mg_scal = nullptr;             // [4] power-iteration scalars of the p-multigrid refresh
