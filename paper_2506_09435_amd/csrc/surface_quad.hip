@@ -384,8 +384,20 @@ __global__ __launch_bounds__(kSqThreads) void k_sq_rhs_vjp(
     Qpx[k] = A00 * gpx + A01 * gpy;
     Qpy[k] = A10 * gpx + A11 * gpy;
   };
-  double r_e = 0, r_p = 0, r_w = 0;
-  int t_out = -1;
+  // node t's sums, assembled
+  auto put = [&](int t, double r_e, double r_p, double r_w) {
+    const int64_t o = (int64_t)col * NH + t;
+    const int hn = eh_nodes[o];
+    const uint8_t fl = flags[o];
+    const double se_ = acc_colour(scr, hn, r_e, fl);
+    const double sp_ = acc_colour(scr + n_s, hn, r_p, fl);
+    const double sw_ = acc_colour(scr + 2 * n_s, hn, r_w, fl);
+    if (fl & kLast) {
+      eta_bar[hn] += se_;
+      phi_bar[hn] += sp_;
+      w_bar[hn] += sw_;
+    }
+  };
   if constexpr (DIM == 3) {
     double *Te = cv.take(N1 * nq), *Ted = cv.take(N1 * nq), *Tp = cv.take(N1 * nq), *Tpd = cv.take(N1 * nq),
            *Tw = cv.take(N1 * nq), *Tk = cv.take(N1 * nq), *Td = cv.take(N1 * nq);
@@ -452,8 +464,10 @@ __global__ __launch_bounds__(kSqThreads) void k_sq_rhs_vjp(
       Uw[k] = a4;
     }
     __syncthreads();
-    if (act && tid < NH) {
-      const int j = tid / N1, i = tid - j * N1;
+    // an element has more nodes than threads at degree 8 with four elements a block
+    for (int t = tid; act && t < NH; t += tpe) {
+      const int j = t / N1, i = t - j * N1;
+      double r_e = 0, r_p = 0, r_w = 0;
       for (int qx = 0; qx < nq; ++qx) {
         const double b = sB[qx * N1 + i], bdx = sBd[qx * N1 + i];
         const int o = j * nq + qx;
@@ -461,7 +475,7 @@ __global__ __launch_bounds__(kSqThreads) void k_sq_rhs_vjp(
         r_p += b * Uap[o] + bdx * Ubp[o];
         r_w += b * Uw[o];
       }
-      t_out = tid;
+      put(t, r_e, r_p, r_w);
     }
   } else {
     for (int q = tid; act && q < nq; q += tpe) {
@@ -479,27 +493,15 @@ __global__ __launch_bounds__(kSqThreads) void k_sq_rhs_vjp(
       point(q, ev, exi, 0.0, pxi, 0.0, w, kb, db);
     }
     __syncthreads();
-    if (act && tid < NH) {
+    for (int t = tid; act && t < NH; t += tpe) {
+      double r_e = 0, r_p = 0, r_w = 0;
       for (int q = 0; q < nq; ++q) {
-        const double b = sB[q * N1 + tid], bdx = sBd[q * N1 + tid];
+        const double b = sB[q * N1 + t], bdx = sBd[q * N1 + t];
         r_e += b * Qe[q] + bdx * Qex[q];
         r_p += bdx * Qpx[q];
         r_w += b * Qw[q];
       }
-      t_out = tid;
-    }
-  }
-  if (t_out >= 0) {
-    const int64_t o = (int64_t)col * NH + t_out;
-    const int hn = eh_nodes[o];
-    const uint8_t fl = flags[o];
-    const double se_ = acc_colour(scr, hn, r_e, fl);
-    const double sp_ = acc_colour(scr + n_s, hn, r_p, fl);
-    const double sw_ = acc_colour(scr + 2 * n_s, hn, r_w, fl);
-    if (fl & kLast) {
-      eta_bar[hn] += se_;
-      phi_bar[hn] += sp_;
-      w_bar[hn] += sw_;
+      put(t, r_e, r_p, r_w);
     }
   }
 }
