@@ -318,11 +318,13 @@ int apply_blocks(const Ctx &c) {
 // Diagonal scaling of the preconditioner choice: the Jacobi inverse (1), or the mask of the
 // non-surface unknowns (0: none; 2: the first direction before the multigrid one replaces it).
 fnpf_status ensure_mask(Ctx &c, hipStream_t s) {
-  if (c.d_mask) return FNPF_OK;
-  HIPCHK(dalloc(&c.d_mask, c.n_v));
-  HIPCHK(launch_fill(c.d_mask, 1.0, c.n_v, s));
-  HIPCHK(launch_fill(c.d_mask + (c.n_v - c.n_s), 0.0, c.n_s, s));
-  if (c.want32) {
+  if (!c.d_mask) {
+    HIPCHK(dalloc(&c.d_mask, c.n_v));
+    HIPCHK(launch_fill(c.d_mask, 1.0, c.n_v, s));
+    HIPCHK(launch_fill(c.d_mask + (c.n_v - c.n_s), 0.0, c.n_s, s));
+  }
+  // the FP32 path may have been enabled after an FP64 solve
+  if (c.want32 && !c.d_mask32) {
     HIPCHK(dalloc(&c.d_mask32, c.n_v));
     HIPCHK(launch_cast_f32(c.d_mask, c.d_mask32, c.n_v, s));
   }
