@@ -164,15 +164,17 @@ __global__ __launch_bounds__(kVecThreads) void k_pcg_update(T *x, T *r, const T 
                                                             int64_t n_s, double *partial, PcgScalars *sc,
                                                             const double *pq, int np) {
   const int dn = sc->done;
-  const double rz = sc->rz2, alpha = sc->alpha;
+  const double rz = sc->rz2;
+  double alpha = sc->alpha;
   const PartialLoads<1> pv(pq, np);
+  bool live = dn == 0;
   T a = T(0);
   double v[2] = {0.0, 0.0};
   for_nodes<LV>(q, n_s, [&](int64_t i) { return PcgLoads<T>{x[i], r[i], p[i], dinv[i]}; },
             [&] {
-              if (dn) return false;
-              a = (T)(np > 0 ? cg_alpha(pv, rz, sc) : alpha);
-              return true;
+              if (np > 0) live = cg_alpha(pv, dn != 0, rz, sc, alpha);
+              a = (T)alpha;
+              return live;
             },
             [&](int64_t i, const PcgLoads<T> &l, T qi) {
               x[i] = l.x + a * l.p;
@@ -182,7 +184,7 @@ __global__ __launch_bounds__(kVecThreads) void k_pcg_update(T *x, T *r, const T 
               v[0] += (double)ri * (double)zi;
               v[1] += (double)ri * (double)ri;
             });
-  if (dn) return;
+  if (!live) return;
   block_partials<2>(v, partial);
 }
 
@@ -241,14 +243,14 @@ __global__ __launch_bounds__(kVecThreads) void k_pcg_dir(T *p, const T *r, const
     dv = reinterpret_cast<const V *>(dinv)[c];
   }
   asm volatile("" ::: "memory");   // the first loads stay ahead of the test
-  if (dn) return;
   double beta;
   if (np > 0) {
     double s[2];
-    sums.sums(s);
+    if (sums.sums(s, dn != 0)) return;
     beta = s[0] / rz;
     if (blockIdx.x == 0 && threadIdx.x == 0) pcg_store(sc, s[0], s[1], beta);
   } else {
+    if (dn) return;
     beta = beta0;
   }
   const T b = (T)beta;

@@ -657,15 +657,17 @@ __global__ __launch_bounds__(kVecThreads) void k_mg_update(T *x, T *r, const T *
                                                            const double *cf, const double *pq, int np) {
   const T c0 = SCALE ? (T)cf[0] : T(0);
   const int dn = sc->done;
-  const double rz = sc->rz2, alpha = sc->alpha;
+  const double rz = sc->rz2;
+  double alpha = sc->alpha;
   const PartialLoads<1> pv(pq, np);
+  bool live = dn == 0;
   T a = T(0);
   double v[1] = {0.0};
   for_nodes<LV>(q, n_s, [&](int64_t i) { return L4<T>{x[i], r[i], p[i], SCALE ? dinv[i] : T(0)}; },
             [&] {
-              if (dn) return false;
-              a = (T)(np > 0 ? cg_alpha(pv, rz, sc) : alpha);
-              return true;
+              if (np > 0) live = cg_alpha(pv, dn != 0, rz, sc, alpha);
+              a = (T)alpha;
+              return live;
             },
             [&](int64_t i, const L4<T> &l, T qi) {
               x[i] = l.a + a * l.c;
@@ -674,7 +676,7 @@ __global__ __launch_bounds__(kVecThreads) void k_mg_update(T *x, T *r, const T *
               if constexpr (SCALE) d[i] = c0 * l.d * ri;
               v[0] += (double)ri * (double)ri;
             });
-  if (dn) return;
+  if (!live) return;
   block_partials<1>(v, partial);
 }
 
@@ -737,14 +739,14 @@ __global__ __launch_bounds__(kVecThreads) void k_mg_dir(T *p, const T *z, int64_
     if (!first) p0 = p[i];
   }
   asm volatile("" ::: "memory");   // the first loads stay ahead of the test
-  if (dn) return;
   double beta;
   if (np > 0) {
     double s[1];
-    pv.sums(s);
+    if (pv.sums(s, dn != 0)) return;
     beta = first ? 0.0 : s[0] / rz;
     if (blockIdx.x == 0 && threadIdx.x == 0) cg_store_rz(sc, s[0], beta);
   } else {
+    if (dn) return;
     beta = beta0;
   }
   const T b = (T)beta;

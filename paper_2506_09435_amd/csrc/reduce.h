@@ -42,12 +42,15 @@ __device__ __forceinline__ void block_partials(double (&v)[NS], double *partial)
   }
 }
 
-// Fixed-order sum of per-thread values over the block; every thread gets it.
+// Fixed-order sum of per-thread values over the block; every thread gets it, and whether any wave's flag
+// was set.
 template <int NS>
-__device__ __forceinline__ void block_total(const double (&a)[NS], double (&out)[NS]) {
+__device__ __forceinline__ bool block_total(const double (&a)[NS], double (&out)[NS], bool flag = false) {
   constexpr int NW = kVecThreads / 64;
   __shared__ double s[NS][NW];
+  __shared__ int any[NW];
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  if (lane == 0) any[wv] = flag ? 1 : 0;
 #pragma unroll
   for (int k = 0; k < NS; ++k) {
     const double r = wsum(a[k]);
@@ -59,6 +62,9 @@ __device__ __forceinline__ void block_total(const double (&a)[NS], double (&out)
     out[k] = 0.0;
     for (int w = 0; w < NW; ++w) out[k] += s[k][w];
   }
+  int f = 0;
+  for (int w = 0; w < NW; ++w) f |= any[w];
+  return f != 0;
 }
 
 // Fixed-order sum of np partial tuples (stride NS) by one block; every thread gets it.
@@ -92,7 +98,8 @@ struct PartialLoads {
       }
     }
   }
-  __device__ __forceinline__ void sums(double (&out)[NS]) const {
+  // true: one of the block's waves has seen the solve end (ended)
+  __device__ __forceinline__ bool sums(double (&out)[NS], bool ended) const {
     double a[NS];
 #pragma unroll
     for (int k = 0; k < NS; ++k) {
@@ -100,7 +107,7 @@ struct PartialLoads {
 #pragma unroll
       for (int m = 0; m < N; ++m) a[k] += v[m][k];
     }
-    block_total<NS>(a, out);
+    return block_total<NS>(a, out, ended);
   }
 };
 
@@ -120,13 +127,18 @@ __device__ __forceinline__ double cg_set_alpha(PcgScalars *sc, double pq, double
   return alpha;
 }
 
-// the same by a whole grid: every block sums the partials of p.Ap, the first one stores.  (On a
-// breakdown a late block may already see `done`: alpha is 0, so nothing is lost.)
-__device__ __forceinline__ double cg_alpha(const PartialLoads<1> &pq, double rz, PcgScalars *sc) {
+// The same by a whole grid: every block sums the partials of p.Ap, the first one stores.  False where
+// nothing may be updated: on a breakdown, which leaves x at its last iterate, and where the solve has
+// ended.  `ended` is the done flag as this wave read it: the first block may set it while the waves of
+// another one start, some before and some after, so all of them go through the sum and leave together if
+// one has seen it (a wave that left alone would leave its part of the sum unwritten).
+__device__ __forceinline__ bool cg_alpha(const PartialLoads<1> &pq, bool ended, double rz, PcgScalars *sc,
+                                         double &alpha) {
   double s[1];
-  pq.sums(s);
+  if (pq.sums(s, ended)) return false;
   if (blockIdx.x == 0 && threadIdx.x == 0) cg_set_alpha(sc, s[0], rz);
-  return (s[0] > 0.0 && s[0] <= 1e300) ? rz / s[0] : 0.0;
+  alpha = rz / s[0];
+  return s[0] > 0.0 && s[0] <= 1e300;
 }
 
 }  // namespace fnpf
