@@ -36,7 +36,12 @@
  *     returns a message for the last failing call on a context.
  *   - A context is not thread-safe; distinct contexts are independent.  Calls
  *     on one context share its workspaces: enqueue them on one stream, or
- *     order the streams by events.
+ *     order the streams by events.  Free of workspaces, so that they may
+ *     overlap on several streams (and be captured and replayed beside others)
+ *     under one geometry: fnpf_w_surface and its VJP, fnpf_rhs_vjp without
+ *     surface quadrature, fnpf_geom_vjp and fnpf_neumann_load.  (The first
+ *     stream that makes such a call takes a shorter path; results differ
+ *     between the paths by the order of the sums at shared nodes only.)
  */
 #ifndef FNPF_H
 #define FNPF_H

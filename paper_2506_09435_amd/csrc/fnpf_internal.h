@@ -183,6 +183,12 @@ struct MgLevel {
   bool ev_ok64 = false, ev_ok32 = false;
 };
 
+// Whether a call on stream s may leave contributions in the context's slots (d_sF of the VJPs): true on
+// the first stream that asks, outside capture.  Calls that need no other workspace may overlap on several
+// streams of one context, and so may replays of what was captured; all but that stream's calls, which
+// follow one another, assemble colour by colour and keep nothing in the context.
+bool slots_usable(Ctx &c, hipStream_t s);
+
 // rows of Ctx::d_sF: the RHS (lumped or consistent, with its mass solves), its VJP, the geometry's VJP
 constexpr int kSlotsRhsVjp = 2, kSlotsGeomVjp = 5, kSlotRows = 7;
 
@@ -288,6 +294,8 @@ struct Ctx {
   double *d_geoH = nullptr, *d_geoh = nullptr;    // eta + h and h of the last fnpf_geom
   double *d_sk = nullptr;   // [2][n_s] surface right-hand sides, owned contributions
   double *d_sF = nullptr;   // [kSlotRows][n_slots] face slots of the surface kernels, rows of its own each
+  hipStream_t slot_stream = nullptr;       // slots_usable: the stream that has the slots
+  bool have_slot_stream = false;
   double *d_partial = nullptr;
   int n_partial = 0;                       // capacity: partial_capacity(partial_uses(...))
   double *d_mg_scal = nullptr;             // [4] power-iteration scalars of the p-multigrid refresh

@@ -1219,6 +1219,23 @@ bool owner_apply_active(const Ctx &c) {
   return c.n_v * 8 < lim && (int64_t)(c.p * c.nz + 1) * std::max(c.n_slots, c.n_tslots) * 8 < lim;
 }
 
+bool slots_usable(Ctx &c, hipStream_t s) {
+  if (s == hipStreamPerThread) return false;   // one handle for the streams of all threads
+  if (s != nullptr) {                          // (the null stream cannot be captured)
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &cap) != hipSuccess) {
+      (void)hipGetLastError();
+      return false;
+    }
+    if (cap != hipStreamCaptureStatusNone) return false;
+  }
+  if (!c.have_slot_stream) {
+    c.slot_stream = s;
+    c.have_slot_stream = true;
+  }
+  return s == c.slot_stream;
+}
+
 // Layers per block of the owner-computes apply.  A block walks its layers one after the other, so a
 // mesh with too few tiles to fill the chip splits its layers over several blocks, at the price of
 // one more value per node at every chunk interface.  The line: as many chunks as still leave all
