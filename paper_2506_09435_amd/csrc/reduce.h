@@ -103,9 +103,9 @@ struct PartialLoads {
     double a[NS];
 #pragma unroll
     for (int k = 0; k < NS; ++k) {
-      a[k] = 0.0;
+      a[k] = v[0][k];   // (0 + v[0] would be formed, and the load waited for, ahead of the other loads)
 #pragma unroll
-      for (int m = 0; m < N; ++m) a[k] += v[m][k];
+      for (int m = 1; m < N; ++m) a[k] += v[m][k];
     }
     return block_total<NS>(a, out, ended);
   }
