@@ -39,7 +39,8 @@
  *     order the streams by events.  Free of workspaces, so that they may
  *     overlap on several streams (and be captured and replayed beside others)
  *     under one geometry: fnpf_w_surface and its VJP, fnpf_rhs_vjp without
- *     surface quadrature, fnpf_geom_vjp and fnpf_neumann_load.  (The first
+ *     surface quadrature, fnpf_geom_vjp, fnpf_neumann_load, and on slices
+ *     both forms of fnpf_laplace_apply.  (The first
  *     stream that makes such a call takes a shorter path; results differ
  *     between the paths by the order of the sums at shared nodes only.)
  */
@@ -229,7 +230,8 @@ fnpf_status fnpf_surface_interp_weights(fnpf_ctx ctx, int32_t n_pts, const doubl
  *     of 6 while n_v * sizeof(element) stays below 4 GiB, else to that of
  *     7; the result is the same.  Small meshes split the layers over several
  *     workgroups.  2D: the same assembly column by column (the schedule of
- *     7 when the face slots exceed 128 MiB);
+ *     7 when the face slots exceed 128 MiB, and for applies that may overlap
+ *     with others of the context: see above);
  *   1 stored factors: fnpf_geom stores G (6 or 3 per point, FP64 and FP32)
  *     and the apply streams it from HBM;
  *   6 fused geometry, line schedule with colour assembly (3D): in the
@@ -278,6 +280,7 @@ fnpf_status fnpf_laplace_apply(fnpf_ctx ctx, fnpf_dtype dtype, const void *x, vo
  * on a GPU uses that GPU's one array: calls that overlap on a GPU (other streams, other
  * contexts, other host threads) race and must be serialised by the caller.  The slots are
  * written before they are read within each call, so nothing carries over between calls.
+ * Slices use none of it: there the call is fnpf_laplace_apply.
  * Errors: ARG when the face slots, at least (p nz + 1) * n_tile_slots elements of the dtype, exceed the
  * array (then use fnpf_laplace_apply); as fnpf_laplace_apply otherwise. */
 fnpf_status fnpf_laplace_apply_noalloc(fnpf_ctx ctx, fnpf_dtype dtype, const void *x, void *y,

@@ -91,6 +91,8 @@ void free_all(Ctx &c) {
   dfree(c.d_p_lists);
   dfree(c.d_F64);
   dfree(c.d_F32);
+  dfree(c.d_aF64);
+  dfree(c.d_aF32);
   dfree(c.d_tslot);
   dfree(c.d_xch);
   dfree(c.d_tps_node);
@@ -200,6 +202,7 @@ fnpf_status ensure32(Ctx &c) {
   HIPCHK(dalloc(&c.d_q32, c.n_v));
   HIPCHK(dalloc(&c.d_d32, c.n_v));
   HIPCHK(dalloc(&c.d_F32, c.n_F));
+  if (c.d_aF64) HIPCHK(dalloc(&c.d_aF32, face_buffer_elements(c, c.n_tslots)));
   c.want32 = true;
   c.have_geom32 = false;
   return FNPF_OK;
@@ -792,6 +795,7 @@ fnpf_status fnpf_create(const fnpf_mesh_desc *m, fnpf_ctx *out) {
   AL(c.d_geoh, c.n_s);
   AL(c.d_sk, 2 * c.n_s);
   AL(c.d_sF, kSlotRows * std::max<int64_t>(c.n_slots, 1));
+  if (c.dim == 2 && owner_apply_active(c)) AL(c.d_aF64, face_buffer_elements(c, c.n_tslots));
   {
     const auto uses = partial_uses(c.max_colour_blocks, owner_apply_blocks(c));
     c.n_partial = (int)partial_capacity(uses);
@@ -910,6 +914,14 @@ fnpf_status fnpf_export_geometry(fnpf_ctx ctx, fnpf_dtype dtype, void *G, double
   return FNPF_OK;
 }
 
+// A slice's apply as the public calls make it: with slots of its own where they are this call's to use,
+// else (and on the schedules that need none) colour by colour.
+static hipError_t slice_apply(Ctx &c, fnpf_dtype dtype, const void *x, void *y, bool mask, hipStream_t s) {
+  const bool own = owner_apply_active(c) && slots_usable(c, s);
+  void *F = dtype == FNPF_F64 ? (void *)c.d_aF64 : (void *)c.d_aF32;
+  return launch_apply(c, dtype, x, y, mask, nullptr, nullptr, s, own ? F : nullptr, false, !own);
+}
+
 fnpf_status fnpf_laplace_apply(fnpf_ctx ctx, fnpf_dtype dtype, const void *x, void *y, int32_t mask, void *stream) {
   if (!ctx) return FNPF_ERR_ARG;
   Ctx &c = ctx->c;
@@ -919,7 +931,10 @@ fnpf_status fnpf_laplace_apply(fnpf_ctx ctx, fnpf_dtype dtype, const void *x, vo
   if (!c.have_geom) return fail(&c, FNPF_ERR_STATE, "fnpf_laplace_apply before fnpf_geom");
   if (dtype == FNPF_F32 && !c.have_geom32)
     return fail(&c, FNPF_ERR_STATE, "no FP32 factors: call fnpf_enable_fp32, then fnpf_geom");
-  HIPCHK(launch_apply(c, dtype, x, y, mask != 0, nullptr, nullptr, (hipStream_t)stream));
+  if (c.dim == 2)
+    HIPCHK(slice_apply(c, dtype, x, y, mask != 0, (hipStream_t)stream));
+  else
+    HIPCHK(launch_apply(c, dtype, x, y, mask != 0, nullptr, nullptr, (hipStream_t)stream));
   return FNPF_OK;
 }
 
@@ -933,6 +948,10 @@ fnpf_status fnpf_laplace_apply_noalloc(fnpf_ctx ctx, fnpf_dtype dtype, const voi
   if (!c.have_geom) return fail(&c, FNPF_ERR_STATE, "fnpf_laplace_apply_noalloc before fnpf_geom");
   if (dtype == FNPF_F32 && !c.have_geom32)
     return fail(&c, FNPF_ERR_STATE, "no FP32 factors: call fnpf_enable_fp32, then fnpf_geom");
+  if (c.dim == 2) {   // needs none of the scratch
+    HIPCHK(slice_apply(c, dtype, x, y, mask != 0, (hipStream_t)stream));
+    return FNPF_OK;
+  }
   // only the owner-computes schedule uses face slots; the others need no scratch
   const size_t word = dtype == FNPF_F64 ? sizeof(double) : sizeof(float);
   const size_t need = owner_apply_active(c) ? face_buffer_elements(c, c.n_tslots) * word : 0;

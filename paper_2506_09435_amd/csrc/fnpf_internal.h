@@ -94,7 +94,8 @@ hipError_t launch_geom(Ctx &c, const double *eta, const double *h, bool store_G,
 // geometry update did not store it
 hipError_t ensure_diag(Ctx &c, hipStream_t s);
 hipError_t launch_apply(Ctx &c, fnpf_dtype dt, const void *x, void *y, bool mask, double *partial,
-                        const int32_t *skip, hipStream_t s, void *face_scratch = nullptr, bool defer = false);
+                        const int32_t *skip, hipStream_t s, void *face_scratch = nullptr, bool defer = false,
+                        bool colour = false);
 bool apply_restrict_active(const Ctx &F);
 hipError_t launch_apply_restrict(Ctx &F, Ctx &C, fnpf_dtype dt, const void *x, const void *b, void *bc, void *Fc,
                                  int lpc, const int32_t *skip, hipStream_t s);
@@ -183,7 +184,8 @@ struct MgLevel {
   bool ev_ok64 = false, ev_ok32 = false;
 };
 
-// Whether a call on stream s may leave contributions in the context's slots (d_sF of the VJPs): true on
+// Whether a call on stream s may leave contributions in the context's slots (d_sF of the VJPs, d_aF64 and
+// d_aF32 of a slice's apply): true on
 // the first stream that asks, outside capture.  Calls that need no other workspace may overlap on several
 // streams of one context, and so may replays of what was captured; all but that stream's calls, which
 // follow one another, assemble colour by colour and keep nothing in the context.
@@ -293,6 +295,8 @@ struct Ctx {
   double *d_w = nullptr;                  // recovered w at the surface
   double *d_geoH = nullptr, *d_geoh = nullptr;    // eta + h and h of the last fnpf_geom
   double *d_sk = nullptr;   // [2][n_s] surface right-hand sides, owned contributions
+  double *d_aF64 = nullptr; // slices: face slots of the public apply, apart from the solves'
+  float *d_aF32 = nullptr;
   double *d_sF = nullptr;   // [kSlotRows][n_slots] face slots of the surface kernels, rows of its own each
   hipStream_t slot_stream = nullptr;       // slots_usable: the stream that has the slots
   bool have_slot_stream = false;

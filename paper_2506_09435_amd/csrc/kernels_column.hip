@@ -1147,7 +1147,8 @@ __global__ __launch_bounds__(256) void k_apply_lines(const T *__restrict__ x, T 
 
 // Second pass of the owner-computes apply: y[v][n] += the face slots of the other tiles at node n
 // (in increasing slot order), for every node level v; with the layers split into chunks of lpc,
-// also the lower chunk's value Z at the chunk interfaces, and its face slots (rows nlev.. of F).
+// also the lower chunk's value Z at the chunk interfaces, and its face slots (rows nlev.. of F), each
+// added to the upper chunk's value of the same column first, as a column that is not split adds them.
 // Blocks below nba: a thread takes one node with slots and a chunk of kFaceLevels levels, with all
 // its loads issued before the sums, and each XCD walks a contiguous range of nodes of one level
 // chunk (the slots of neighbouring tiles then meet in the same L2).  The other blocks: one chunk
@@ -1185,26 +1186,27 @@ __global__ __launch_bounds__(256) void k_apply_faces(T *__restrict__ y, const T 
   if (k >= n_ps) return;
   const int64_t n = ps_node[k];
   const int a = ps_ptr[k], b = ps_ptr[k + 1];
+  // chunk below the interface at level v, -1 at other levels
+  auto below = [&](int v) {
+    const int c = v / clev - 1;
+    return nchunk > 1 && v > 0 && v < nlev - 1 && v == (c + 1) * clev ? c : -1;
+  };
   T acc[LC];
 #pragma unroll
-  for (int u = 0; u < LC; ++u) acc[u] = (v0 + u < vend) ? y[(v0 + u) * n_s + n] : T(0);
+  for (int u = 0; u < LC; ++u) {
+    acc[u] = (v0 + u < vend) ? y[(v0 + u) * n_s + n] : T(0);
+    if (const int c = below(v0 + u); c >= 0) acc[u] += Z[c * n_s + n];
+  }
   for (int q = a; q < b; ++q) {
     const int64_t sl = ps_slot[q];
     T f[LC];
 #pragma unroll
-    for (int u = 0; u < LC; ++u) f[u] = (v0 + u < vend) ? F[(v0 + u) * n_slots + sl] : T(0);
+    for (int u = 0; u < LC; ++u) {
+      f[u] = (v0 + u < vend) ? F[(v0 + u) * n_slots + sl] : T(0);
+      if (const int c = below(v0 + u); c >= 0) f[u] += F[(nlev + c) * n_slots + sl];
+    }
 #pragma unroll
     for (int u = 0; u < LC; ++u) acc[u] += f[u];
-  }
-  if (nchunk > 1) {
-#pragma unroll
-    for (int u = 0; u < LC; ++u) {
-      const int v = v0 + u, c = v / clev - 1;
-      if (v > 0 && v < nlev - 1 && v == (c + 1) * clev) {
-        acc[u] += Z[c * n_s + n];
-        for (int q = a; q < b; ++q) acc[u] += F[(nlev + c) * n_slots + ps_slot[q]];
-      }
-    }
   }
 #pragma unroll
   for (int u = 0; u < LC; ++u)
@@ -1213,7 +1215,7 @@ __global__ __launch_bounds__(256) void k_apply_faces(T *__restrict__ y, const T 
 
 bool owner_apply_active(const Ctx &c) {
   if (c.apply_variant != 0 || !c.apply_owner) return false;
-  // slices: while their slots fit the allocation-free apply's scratch, so that it has the same result
+  // slices: while their slots stay small (a second buffer of them is kept for the public apply)
   if (c.dim == 2) return face_buffer_elements(c, c.n_tslots) * sizeof(double) <= noalloc_scratch_bytes();
   const int64_t lim = int64_t(1) << 32;
   return c.n_v * 8 < lim && (int64_t)(c.p * c.nz + 1) * std::max(c.n_slots, c.n_tslots) * 8 < lim;
@@ -2034,7 +2036,7 @@ hipError_t ensure_diag(Ctx &c, hipStream_t s) {
 
 template <int P, int DIM, typename T, bool MASK, bool DOT>
 static hipError_t apply_impl(Ctx &c, const T *x, T *y, const T *G, double *partial, const int32_t *skip,
-                             hipStream_t s, T *face_scratch, bool defer) {
+                             hipStream_t s, T *face_scratch, bool defer, bool colour) {
   using S = Sh<P, DIM>;
   const int64_t hs = (int64_t)c.n_eh * c.nh;
   const bool fused = c.apply_variant == 0;
@@ -2055,7 +2057,7 @@ static hipError_t apply_impl(Ctx &c, const T *x, T *y, const T *G, double *parti
     if (cr.count == 0) continue;
     const int nb = (cr.count + S::CPB - 1) / S::CPB;
     if (fused) {
-      if (owner_apply_active(c)) {
+      if (owner_apply_active(c) && !colour) {
         T *F = face_scratch;
         if (F == nullptr) {
           if constexpr (sizeof(T) == 8) F = (T *)c.d_F64; else F = (T *)c.d_F32;
@@ -2099,22 +2101,22 @@ static hipError_t apply_impl(Ctx &c, const T *x, T *y, const T *G, double *parti
 
 template <int P, int DIM>
 static hipError_t apply_dispatch(Ctx &c, fnpf_dtype dt, const void *x, void *y, bool mask, double *partial,
-                                 const int32_t *skip, hipStream_t s, void *fs, bool defer) {
+                                 const int32_t *skip, hipStream_t s, void *fs, bool defer, bool colour) {
   const bool dot = partial != nullptr;
   if (dt == FNPF_F64) {
     const double *xx = (const double *)x;
     double *yy = (double *)y;
     double *F = (double *)fs;
-    if (!mask) return apply_impl<P, DIM, double, false, false>(c, xx, yy, c.d_G64, nullptr, skip, s, F, defer);
-    if (!dot) return apply_impl<P, DIM, double, true, false>(c, xx, yy, c.d_G64, nullptr, skip, s, F, defer);
-    return apply_impl<P, DIM, double, true, true>(c, xx, yy, c.d_G64, partial, skip, s, F, defer);
+    if (!mask) return apply_impl<P, DIM, double, false, false>(c, xx, yy, c.d_G64, nullptr, skip, s, F, defer, colour);
+    if (!dot) return apply_impl<P, DIM, double, true, false>(c, xx, yy, c.d_G64, nullptr, skip, s, F, defer, colour);
+    return apply_impl<P, DIM, double, true, true>(c, xx, yy, c.d_G64, partial, skip, s, F, defer, colour);
   }
   const float *xx = (const float *)x;
   float *yy = (float *)y;
   float *F = (float *)fs;
-  if (!mask) return apply_impl<P, DIM, float, false, false>(c, xx, yy, c.d_G32, nullptr, skip, s, F, defer);
-  if (!dot) return apply_impl<P, DIM, float, true, false>(c, xx, yy, c.d_G32, nullptr, skip, s, F, defer);
-  return apply_impl<P, DIM, float, true, true>(c, xx, yy, c.d_G32, partial, skip, s, F, defer);
+  if (!mask) return apply_impl<P, DIM, float, false, false>(c, xx, yy, c.d_G32, nullptr, skip, s, F, defer, colour);
+  if (!dot) return apply_impl<P, DIM, float, true, false>(c, xx, yy, c.d_G32, nullptr, skip, s, F, defer, colour);
+  return apply_impl<P, DIM, float, true, true>(c, xx, yy, c.d_G32, partial, skip, s, F, defer, colour);
 }
 
 // The restricted residual P^T (b - A x) of level F on the next coarser level C by the apply itself
@@ -2169,17 +2171,20 @@ hipError_t launch_apply_restrict(Ctx &F, Ctx &C, fnpf_dtype dt, const void *x, c
 
 // defer: leave the owner-computes apply's face pass to the reader (deferred.h, apply_result).
 // face_scratch: device memory for the face slots in place of the context's own (nullptr: the
-// context's); it must hold (p nz + 1) * n_tslots elements of the apply's precision
+// context's); it must hold face_buffer_elements(c, c.n_tslots) elements of the apply's precision.
+// colour: the colour schedule, which needs none, also where the owner-computes one is active
 hipError_t launch_apply(Ctx &c, fnpf_dtype dt, const void *x, void *y, bool mask, double *partial,
-                        const int32_t *skip, hipStream_t s, void *face_scratch, bool defer) {
+                        const int32_t *skip, hipStream_t s, void *face_scratch, bool defer, bool colour) {
   // one partial per block of every launch when the dot product is fused
   if (partial != nullptr &&
       !partials_fit(c.n_partial, owner_apply_active(c) ? owner_apply_blocks(c) : c.max_colour_blocks, 1))
     return hipErrorInvalidValue;
   if (c.dim == 3) {
-    FNPF_DISPATCH(3, c.p, return (apply_dispatch<P_, 3>(c, dt, x, y, mask, partial, skip, s, face_scratch, defer)));
+    FNPF_DISPATCH(3, c.p,
+                  return (apply_dispatch<P_, 3>(c, dt, x, y, mask, partial, skip, s, face_scratch, defer, colour)));
   } else {
-    FNPF_DISPATCH(2, c.p, return (apply_dispatch<P_, 2>(c, dt, x, y, mask, partial, skip, s, face_scratch, defer)));
+    FNPF_DISPATCH(2, c.p,
+                  return (apply_dispatch<P_, 2>(c, dt, x, y, mask, partial, skip, s, face_scratch, defer, colour)));
   }
   return hipSuccess;
 }

@@ -1,10 +1,12 @@
 """Calls that need no workspace of the context, overlapping on two streams and replayed from a graph beside
-direct calls (the surface VJPs of the lumped form, the geometry's VJP).
+direct calls (the surface VJPs of the lumped form, the geometry's VJP, the apply on slices).
 
-The reference is the same calls one after the other on a context of their own.  Shared nodes sum at most
+The VJPs' reference is the same calls one after the other on a context of their own.  Shared nodes sum at most
 a few contributions in another order, over REPS accumulations: 1e-13 relative L2 per call bounds it, the
-checks take 1e-12.
+checks take 1e-12.  A slice's node has two columns, so its applies are equal bit by bit.
 """
+
+import ctypes as C
 
 import pytest
 
@@ -92,3 +94,47 @@ def test_captured_vjps_beside_direct_ones(name, same):
             vjps(s, d[0])
         torch.cuda.synchronize()
         assert close(d[0]["bars"], ref[0]) and close(d[1]["bars"], ref[1])
+
+
+SLICES = [(200, 3, 4), (90, 7, 2), (130, 4, 1), (60, 5, 8), (300, 2, 5)]
+
+
+def apply_noalloc(ctx, x, y):
+    dt = fnpf.F64 if x.dtype == torch.float64 else fnpf.F32
+    assert fnpf.lib().fnpf_laplace_apply_noalloc(ctx._h, dt, C.c_void_p(x.data_ptr()), C.c_void_p(y.data_ptr()), 0,
+                                                 C.c_void_p(torch.cuda.current_stream().cuda_stream)) == 0
+
+
+@pytest.mark.parametrize("nx,nz,p", SLICES)
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
+def test_slice_applies_overlap(nx, nz, p, dtype):
+    # layers in one block and split, several tiles; both forms of the call, on the context's first stream,
+    # on another one beside it and beside a solve, and from a graph: bitwise the same
+    wl = configs.small_slice(nx=nx, nz=nz, p=p)
+    s = fnpf.setup_workload(wl, fp32=True)
+    s.ctx.geom(s.eta0, s.h)
+    g = torch.Generator(device="cuda").manual_seed(p)
+    x = [torch.randn(s.ctx.n_v, dtype=torch.float64, device="cuda", generator=g).to(dtype) for _ in range(2)]
+    ref = [s.ctx.laplace_apply(v) for v in x]      # the default stream is the first
+    torch.cuda.synchronize()
+    other = torch.cuda.Stream()
+    y = [torch.full_like(v, float("nan")) for v in x]
+    z = torch.full_like(x[0], float("nan"))
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=torch.cuda.Stream()):
+        apply_noalloc(s.ctx, x[1], z)
+    for _ in range(REPS):
+        with torch.cuda.stream(other):
+            s.ctx.laplace_apply(x[1], y[1])
+        apply_noalloc(s.ctx, x[0], y[0])
+        with torch.cuda.stream(other):
+            graph.replay()
+    torch.cuda.synchronize()
+    assert torch.equal(y[0], ref[0]) and torch.equal(y[1], ref[1]) and torch.equal(z, ref[1])
+    phi, info = s.ctx.solve(s.phi0, opts=fnpf.default_opts(rtol=1e-11))
+    with torch.cuda.stream(other):
+        for _ in range(REPS):
+            s.ctx.laplace_apply(x[1], y[1])
+    phi2, _ = s.ctx.solve(s.phi0, opts=fnpf.default_opts(rtol=1e-11))
+    torch.cuda.synchronize()
+    assert info["status"] == "OK" and torch.equal(phi, phi2) and torch.equal(y[1], ref[1])
