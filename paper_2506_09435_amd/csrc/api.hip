@@ -6,6 +6,7 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
+#include <exception>
 #include <new>
 #include <string>
 #include <vector>
@@ -34,6 +35,14 @@ fnpf_status hipfail(Ctx *c, hipError_t e, const char *where) {
   if (c) c->err = std::string(where) + ": " + hipGetErrorString(e);
   return FNPF_ERR_HIP;
 }
+
+// what an entry point that builds host tables makes of an exception (short enough to need no memory)
+constexpr char kNoMemory[] = "out of memory";
+
+fnpf_status caught(fnpf_ctx ctx);
+
+#define FNPF_CATCH(ctx) \
+  catch (const std::exception &) { return caught(ctx); }
 
 #define HIPCHK(expr)                                 \
   do {                                               \
@@ -578,6 +587,11 @@ fnpf_status flat_geometry(Ctx &c, const double *h, hipStream_t s) {
   return FNPF_OK;
 }
 
+fnpf_status caught(fnpf_ctx ctx) {
+  ctx->c.err = kNoMemory;
+  return FNPF_ERR_ALLOC;
+}
+
 }  // namespace
 
 namespace fnpf {
@@ -638,37 +652,14 @@ fnpf_status fnpf_gll(int32_t p, double *nodes, double *weights, double *D) {
   return FNPF_OK;
 }
 
-fnpf_status fnpf_create(const fnpf_mesh_desc *m, fnpf_ctx *out) {
-  g_create_error.clear();
-  if (!out) {
-    g_create_error = "out is NULL";
-    return FNPF_ERR_ARG;
-  }
-  *out = nullptr;
-  if (!m) {
-    g_create_error = "mesh is NULL";
-    return FNPF_ERR_ARG;
-  }
-  if ((m->dim != 2 && m->dim != 3) || m->p < 1 || m->p > kMaxP || m->nz < 1 || m->n_eh < 1 || m->n_s < 1 ||
-      !m->eh_nodes || !m->eh_corner || !(m->g > 0.0)) {
-    g_create_error = "invalid mesh header (dim 2|3, 1 <= p <= 8, nz >= 1, n_eh >= 1, n_s >= 1, g > 0, "
-                     "eh_nodes and eh_corner required)";
-    return FNPF_ERR_ARG;
-  }
-  if (m->dim == 2 && m->eh_arc) {
-    g_create_error = "eh_arc is only meaningful for dim 3";
-    return FNPF_ERR_ARG;
-  }
-  fnpf_ctx_s *h = new (std::nothrow) fnpf_ctx_s();
-  if (!h) return FNPF_ERR_ALLOC;
-  Ctx &c = h->c;
+// the context of a mesh; what was allocated before a failure is left to the caller
+static fnpf_status create_context(const fnpf_mesh_desc *m, Ctx &c) {
   std::vector<double> hm, mw, ms;
   std::vector<uint8_t> flags;
   std::vector<int32_t> cols;
   std::string e = build_host_mesh(*m, c, hm, flags, cols, mw, ms);
   if (!e.empty()) {
     g_create_error = e;
-    delete h;
     return FNPF_ERR_ARG;
   }
   c.h_hm = hm;
@@ -687,8 +678,6 @@ fnpf_status fnpf_create(const fnpf_mesh_desc *m, fnpf_ctx *out) {
   hipError_t he = hipGetDevice(&c.device);
   auto bad = [&](hipError_t err) {
     g_create_error = std::string("HIP error during create: ") + hipGetErrorString(err);
-    free_all(c);
-    delete h;
     return err == hipErrorOutOfMemory ? FNPF_ERR_ALLOC : FNPF_ERR_HIP;
   };
   if (he != hipSuccess) return bad(he);
@@ -802,8 +791,6 @@ fnpf_status fnpf_create(const fnpf_mesh_desc *m, fnpf_ctx *out) {
     const std::string le = partial_layout_error(uses, c.n_partial);
     if (!le.empty()) {
       g_create_error = le;
-      free_all(c);
-      delete h;
       return FNPF_ERR_ARG;
     }
   }
@@ -819,6 +806,48 @@ fnpf_status fnpf_create(const fnpf_mesh_desc *m, fnpf_ctx *out) {
   if ((he = hipMemset(c.d_phi, 0, c.n_v * sizeof(double))) != hipSuccess) return bad(he);
   if ((he = hipMemset(c.d_sc, 0, 2 * sizeof(PcgScalars))) != hipSuccess) return bad(he);
   if ((he = hipDeviceSynchronize()) != hipSuccess) return bad(he);
+  return FNPF_OK;
+}
+
+fnpf_status fnpf_create(const fnpf_mesh_desc *m, fnpf_ctx *out) {
+  g_create_error.clear();
+  if (!out) {
+    g_create_error = "out is NULL";
+    return FNPF_ERR_ARG;
+  }
+  *out = nullptr;
+  if (!m) {
+    g_create_error = "mesh is NULL";
+    return FNPF_ERR_ARG;
+  }
+  if ((m->dim != 2 && m->dim != 3) || m->p < 1 || m->p > kMaxP || m->nz < 1 || m->n_eh < 1 || m->n_s < 1 ||
+      !m->eh_nodes || !m->eh_corner || !(m->g > 0.0)) {
+    g_create_error = "invalid mesh header (dim 2|3, 1 <= p <= 8, nz >= 1, n_eh >= 1, n_s >= 1, g > 0, "
+                     "eh_nodes and eh_corner required)";
+    return FNPF_ERR_ARG;
+  }
+  if (m->dim == 2 && m->eh_arc) {
+    g_create_error = "eh_arc is only meaningful for dim 3";
+    return FNPF_ERR_ARG;
+  }
+  if ((int64_t)m->p * m->nz >= INT32_MAX || m->n_s > (int64_t)m->n_eh * (m->p + 1) * (m->dim == 3 ? m->p + 1 : 1)) {
+    g_create_error = "invalid mesh header (too many node levels, or more horizontal nodes than the elements use)";
+    return FNPF_ERR_ARG;
+  }
+  fnpf_ctx_s *h = new (std::nothrow) fnpf_ctx_s();
+  if (!h) return FNPF_ERR_ALLOC;
+  fnpf_status st;
+  try {
+    st = create_context(m, h->c);
+  } catch (const std::exception &) {
+    g_create_error = kNoMemory;
+    st = FNPF_ERR_ALLOC;
+  }
+  if (st != FNPF_OK) {
+    free_all(h->c);
+    delete h;
+    return st;
+  }
   *out = h;
   return FNPF_OK;
 }
@@ -840,7 +869,7 @@ fnpf_status fnpf_sizes(fnpf_ctx ctx, int64_t *n_v, int64_t *n_s, int64_t *n_e, i
   return FNPF_OK;
 }
 
-fnpf_status fnpf_surface_interp_weights(fnpf_ctx ctx, int32_t n_pts, const double *pts, int32_t *node, double *w) {
+fnpf_status fnpf_surface_interp_weights(fnpf_ctx ctx, int32_t n_pts, const double *pts, int32_t *node, double *w) try {
   if (!ctx) return FNPF_ERR_ARG;
   Ctx &c = ctx->c;
   if (n_pts < 0) return fail(&c, FNPF_ERR_ARG, "n_pts must be >= 0");
@@ -848,7 +877,7 @@ fnpf_status fnpf_surface_interp_weights(fnpf_ctx ctx, int32_t n_pts, const doubl
   const std::string e = surface_interp_weights(c, n_pts, pts, node, w);
   if (!e.empty()) return fail(&c, FNPF_ERR_ARG, e);
   return FNPF_OK;
-}
+} FNPF_CATCH(ctx)
 
 fnpf_status fnpf_node_coords(fnpf_ctx ctx, double *xy) {
   if (!ctx || !xy) return ctx ? fail(&ctx->c, FNPF_ERR_ARG, "xy is NULL") : FNPF_ERR_ARG;
@@ -874,10 +903,10 @@ fnpf_status fnpf_set_apply_variant(fnpf_ctx ctx, int32_t variant) {
   return FNPF_OK;
 }
 
-fnpf_status fnpf_enable_fp32(fnpf_ctx ctx) {
+fnpf_status fnpf_enable_fp32(fnpf_ctx ctx) try {
   if (!ctx) return FNPF_ERR_ARG;
   return ensure32(ctx->c);
-}
+} FNPF_CATCH(ctx)
 
 fnpf_status fnpf_geom(fnpf_ctx ctx, const double *eta, const double *h, void *stream) {
   if (!ctx) return FNPF_ERR_ARG;
@@ -996,7 +1025,7 @@ fnpf_status fnpf_neumann_load(fnpf_ctx ctx, const double *q, double *f, void *st
 }
 
 fnpf_status fnpf_solve(fnpf_ctx ctx, const double *phis, const double *f, double *phi, const fnpf_solve_opts *opts,
-                       fnpf_solve_info *info, void *stream) {
+                       fnpf_solve_info *info, void *stream) try {
   if (!ctx) return FNPF_ERR_ARG;
   Ctx &c = ctx->c;
   if (!phis || !phi) return fail(&c, FNPF_ERR_ARG, "fnpf_solve: phi_surface and phi must be device pointers");
@@ -1009,7 +1038,7 @@ fnpf_status fnpf_solve(fnpf_ctx ctx, const double *phis, const double *f, double
   if (o.precision == 1 && !c.have_geom32)
     return fail(&c, FNPF_ERR_STATE, "mixed solve needs FP32 factors: call fnpf_enable_fp32, then fnpf_geom");
   return solve_impl(c, phis, f, phi, o, info, (hipStream_t)stream);
-}
+} FNPF_CATCH(ctx)
 
 fnpf_status fnpf_w_surface(fnpf_ctx ctx, const double *phi, double *w, void *stream) {
   if (!ctx) return FNPF_ERR_ARG;
@@ -1043,7 +1072,7 @@ fnpf_status fnpf_set_linear(fnpf_ctx ctx, int32_t linear) {
   return FNPF_OK;
 }
 
-fnpf_status fnpf_set_surface_quadrature(fnpf_ctx ctx, int32_t nq) {
+fnpf_status fnpf_set_surface_quadrature(fnpf_ctx ctx, int32_t nq) try {
   if (!ctx) return FNPF_ERR_ARG;
   Ctx &c = ctx->c;
   if (nq == 0) {
@@ -1059,7 +1088,7 @@ fnpf_status fnpf_set_surface_quadrature(fnpf_ctx ctx, int32_t nq) {
     return fail(&c, std::strstr(err, "Jacobian") ? FNPF_ERR_GEOM : FNPF_ERR_ALLOC, err);
   }
   return FNPF_OK;
-}
+} FNPF_CATCH(ctx)
 
 fnpf_status fnpf_surface_quadrature_info(fnpf_ctx ctx, int32_t *nq, int32_t *iters, double *lam_lo,
                                          double *lam_hi) {
@@ -1072,7 +1101,7 @@ fnpf_status fnpf_surface_quadrature_info(fnpf_ctx ctx, int32_t *nq, int32_t *ite
   return FNPF_OK;
 }
 
-fnpf_status fnpf_multigrid_info(fnpf_ctx ctx, int32_t *levels, double *lam64, double *lam32, int32_t cap) {
+fnpf_status fnpf_multigrid_info(fnpf_ctx ctx, int32_t *levels, double *lam64, double *lam32, int32_t cap) try {
   if (!ctx) return FNPF_ERR_ARG;
   Ctx &c = ctx->c;
   if (cap < 0) return fail(&c, FNPF_ERR_ARG, "cap must be >= 0");
@@ -1087,9 +1116,9 @@ fnpf_status fnpf_multigrid_info(fnpf_ctx ctx, int32_t *levels, double *lam64, do
     if (lam32) lam32[l] = h[nl + l];
   }
   return FNPF_OK;
-}
+} FNPF_CATCH(ctx)
 
-fnpf_status fnpf_set_modal_filter(fnpf_ctx ctx, int32_t cutoff, double alpha, int32_t order) {
+fnpf_status fnpf_set_modal_filter(fnpf_ctx ctx, int32_t cutoff, double alpha, int32_t order) try {
   if (!ctx) return FNPF_ERR_ARG;
   Ctx &c = ctx->c;
   if (cutoff < 0) {
@@ -1116,7 +1145,7 @@ fnpf_status fnpf_set_modal_filter(fnpf_ctx ctx, int32_t cutoff, double alpha, in
   c.filter_alpha = alpha;
   c.filter_order = order;
   return FNPF_OK;
-}
+} FNPF_CATCH(ctx)
 
 fnpf_status fnpf_modal_filter(fnpf_ctx ctx, const double *f, double *out, void *stream) {
   if (!ctx) return FNPF_ERR_ARG;
@@ -1162,7 +1191,7 @@ fnpf_status fnpf_set_relaxation(fnpf_ctx ctx, const double *cr, const double *ec
 }
 
 fnpf_status fnpf_rk4_step(fnpf_ctx ctx, double *eta, double *phis, const double *h, double t, double dt,
-                          const fnpf_solve_opts *opts, double *tape, fnpf_solve_info *info, void *stream) {
+                          const fnpf_solve_opts *opts, double *tape, fnpf_solve_info *info, void *stream) try {
   if (!ctx) return FNPF_ERR_ARG;
   Ctx &c = ctx->c;
   hipStream_t s = (hipStream_t)stream;
@@ -1255,7 +1284,7 @@ fnpf_status fnpf_rk4_step(fnpf_ctx ctx, double *eta, double *phis, const double 
   else
     c.hist.count = 0;  // a step taken without recording breaks the sequence
   return FNPF_OK;
-}
+} FNPF_CATCH(ctx)
 
 fnpf_status fnpf_rhs_vjp(fnpf_ctx ctx, const double *eta, const double *phis, const double *w, const double *deta_bar,
                          const double *dphi_bar, double *eta_bar, double *phis_bar, double *w_bar, void *stream) {
@@ -1279,7 +1308,7 @@ fnpf_status fnpf_w_surface_vjp(fnpf_ctx ctx, const double *w, const double *w_ba
 }
 
 fnpf_status fnpf_solve_adjoint(fnpf_ctx ctx, const double *phi_bar, double *lambda, const fnpf_solve_opts *opts,
-                               fnpf_solve_info *info, void *stream) {
+                               fnpf_solve_info *info, void *stream) try {
   if (!ctx) return FNPF_ERR_ARG;
   Ctx &c = ctx->c;
   hipStream_t s = (hipStream_t)stream;
@@ -1296,7 +1325,7 @@ fnpf_status fnpf_solve_adjoint(fnpf_ctx ctx, const double *phi_bar, double *lamb
   if (st != FNPF_OK) return st;
   // the operator is symmetric: A_II lambda_I = phi_bar_I with lambda_S = 0
   return solve_impl(c, c.d_zero_s, phi_bar, lambda, o, info, s);
-}
+} FNPF_CATCH(ctx)
 
 fnpf_status fnpf_geom_vjp(fnpf_ctx ctx, const double *lambda, const double *phi, double *eta_bar, double *h_bar,
                           void *stream) {
@@ -1310,7 +1339,7 @@ fnpf_status fnpf_geom_vjp(fnpf_ctx ctx, const double *lambda, const double *phi,
 
 fnpf_status fnpf_rk4_step_vjp(fnpf_ctx ctx, const double *h, double t, double dt, const double *tape,
                               double *eta_bar, double *phis_bar, double *h_bar, const fnpf_solve_opts *opts,
-                              fnpf_solve_info *info, void *stream) {
+                              fnpf_solve_info *info, void *stream) try {
   if (!ctx) return FNPF_ERR_ARG;
   Ctx &c = ctx->c;
   hipStream_t s = (hipStream_t)stream;
@@ -1405,7 +1434,7 @@ fnpf_status fnpf_rk4_step_vjp(fnpf_ctx ctx, const double *h, double t, double dt
   HIPCHK(hipMemcpyAsync(phis_bar, c.d_accp, ns * sizeof(double), hipMemcpyDeviceToDevice, s));
   if (o.extrapolate) history_advance(c.ahist, t, dt, c.ahist.count > 0);
   return FNPF_OK;
-}
+} FNPF_CATCH(ctx)
 
 fnpf_status fnpf_get_warm_start(fnpf_ctx ctx, double *phi, void *stream) {
   if (!ctx) return FNPF_ERR_ARG;

@@ -22,6 +22,7 @@
 #include <cmath>
 #include <cstdint>
 #include <cstring>
+#include <exception>
 #include <utility>
 #include <vector>
 
@@ -1468,8 +1469,7 @@ hipError_t estimate_lambda(Ctx &c, Ctx &L, T *v, T *q, T *w1, T *w2, bool warm, 
 }  // namespace
 
 // Builds the coarse levels (contexts at degrees p/2, p/4, ..., 1) and their work vectors.
-fnpf_status mg_build(Ctx &c) {
-  if (c.mg_built) return FNPF_OK;
+static fnpf_status build_levels(Ctx &c) {
   static bool uploaded[64] = {false};
   if (c.device >= 0 && c.device < 64 && !uploaded[c.device]) {
     if (upload_tables() != hipSuccess) return FNPF_ERR_HIP;
@@ -1532,6 +1532,19 @@ fnpf_status mg_build(Ctx &c) {
   c.mg_built = true;
   c.mg_stale64 = c.mg_stale32 = true;
   return FNPF_OK;
+}
+
+// A failure leaves no level behind: a later call starts afresh.
+fnpf_status mg_build(Ctx &c) {
+  if (c.mg_built) return FNPF_OK;
+  try {
+    const fnpf_status st = build_levels(c);
+    if (st != FNPF_OK) mg_free(c);
+    return st;
+  } catch (const std::exception &) {
+    mg_free(c);
+    throw;
+  }
 }
 
 void mg_free(Ctx &c) {

@@ -209,7 +209,7 @@ std::string build_host_mesh(const fnpf_mesh_desc &m, Ctx &c, std::vector<double>
     if (!(c.h_layer_s[l + 1] > c.h_layer_s[l])) return "layer_s must be strictly increasing";
   std::vector<double> x(n1), w(n1), D(n1 * n1);
   gll_host(p, x.data(), w.data(), D.data());
-  c.h_sigma.resize(p * m.nz + 1);
+  c.h_sigma.resize((size_t)p * m.nz + 1);
   for (int l = 0; l < m.nz; ++l)
     for (int k = 0; k <= p; ++k)
       c.h_sigma[l * p + k] = c.h_layer_s[l] + (c.h_layer_s[l + 1] - c.h_layer_s[l]) * 0.5 * (x[k] + 1.0);
