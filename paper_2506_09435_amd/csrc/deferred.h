@@ -80,6 +80,9 @@ inline int64_t node_tasks(const Ctx &c, int lv) { return (c.n_s + 255) / 256 * (
 // that the kernel is one chain of loads; large meshes are bound by HBM and take one level at a time
 // (four rows of every operand at once were a third slower on the sea of 256 x 128 x 6, p = 6).
 constexpr int kNodeBlocks = 8 * 256;
+// (Kernels of one level a thread run at most 2,048 blocks.  Some need more than the 80 scalar registers
+// with which eight blocks fit a CU, and the blocks left over make a second round: launch bounds keep them
+// there.  The multigrid's FP32 update on that sea: 229 us with 80, 296 with 96.)
 inline int node_levels(const Ctx &c) {
   return node_tasks(c, 1) <= kNodeBlocks ? 1 : node_tasks(c, 2) <= kNodeBlocks ? 2 : node_tasks(c, 4) <= kNodeBlocks ? 4 : 1;
 }

@@ -160,7 +160,7 @@ template <typename T>
 struct PcgLoads { T x, r, p, d; };
 // np > 0: alpha from the np partials of p.q, else as k_fin_pq left it
 template <int LV, typename T>
-__global__ __launch_bounds__(kVecThreads) void k_pcg_update(T *x, T *r, const T *p, Deferred<T> q, const T *dinv,
+__global__ __launch_bounds__(kVecThreads, LV == 1 ? 8 : 1) void k_pcg_update(T *x, T *r, const T *p, Deferred<T> q, const T *dinv,
                                                             int64_t n_s, double *partial, PcgScalars *sc,
                                                             const double *pq, int np) {
   const int dn = sc->done;

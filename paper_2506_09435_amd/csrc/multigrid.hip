@@ -653,7 +653,7 @@ __global__ __launch_bounds__(kVecThreads) void k_post2b(T *x, const T *b, const 
 // first step of the degree-2 V-cycle that follows on the new residual, d = c0 dinv r.  np > 0: alpha
 // from the np partials of p.q (cg_alpha), else as k_fin_pq left it.
 template <int LV, typename T, bool SCALE>
-__global__ __launch_bounds__(kVecThreads) void k_mg_update(T *x, T *r, const T *p, Deferred<T> q, int64_t n_s,
+__global__ __launch_bounds__(kVecThreads, LV == 1 ? 8 : 1) void k_mg_update(T *x, T *r, const T *p, Deferred<T> q, int64_t n_s,
                                                            double *partial, PcgScalars *sc, T *d, const T *dinv,
                                                            const double *cf, const double *pq, int np) {
   const T c0 = SCALE ? (T)cf[0] : T(0);
