@@ -37,7 +37,6 @@ struct PcgScalars {
   double rr;       // r^T r of the current iterate
   double pq;       // p^T A p
   double alpha;
-  double beta;
   double tol2;     // squared absolute stopping threshold
   double bnorm2;   // ||b||^2
   double rr0;      // r^T r at the start of this (inner) solve

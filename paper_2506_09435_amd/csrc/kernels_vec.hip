@@ -1,11 +1,12 @@
 // Vector kernels of the preconditioned conjugate-gradient solve (paper Sec. 4: CG for the
 // Laplace system) and its FP64/FP32 defect correction.
 //
-// All reductions are deterministic: grid-stride kernels with a fixed grid write one FP64
-// partial per block (wave64 shuffle reduction, then the block's waves in order), and a
-// single-block finalize kernel sums the partials in a fixed order and updates the device
-// scalars (alpha, beta, convergence flag).  Once `done` is set, every later kernel of the
-// iteration returns immediately, so the host may check convergence only every few
+// All reductions are deterministic: grid-stride kernels whose grid depends on the mesh only write
+// one FP64 partial per block (wave64 shuffle reduction, then the block's waves in order).  The
+// kernel that needs the sum adds the partials in a fixed order in every block, and its first block
+// stores the device scalars (alpha, r.z, convergence flag); the p.Ap partials of large meshes, and
+// the sums at a solve's start, are added by a single-block kernel.  Once `done` is set, every later
+// kernel of the iteration leaves its vectors alone, so the host may check convergence only every few
 // iterations without changing the result.
 //
 // Vectors hold all n_v volume nodes; the free-surface level [top*n_s, n_v) of r, p, q and
@@ -97,7 +98,6 @@ __global__ __launch_bounds__(kVecThreads) void k_fin_init(const double *partial,
     sc->breakdown = (s[1] == s[1] && s[1] <= 1e300) ? 0 : 2;
     sc->done = (sc->breakdown != 0 || s[1] <= sc->tol2) ? 1 : 0;
     sc->alpha = 0.0;
-    sc->beta = 0.0;
   }
 }
 
@@ -141,7 +141,6 @@ __global__ __launch_bounds__(kVecThreads) void k_fin_outer(const double *partial
     inner->iters = 0;
     inner->breakdown = 0;
     inner->alpha = 0.0;
-    inner->beta = 0.0;
     inner->done = (outer->done || s[2] <= inner->tol2) ? 1 : 0;
   }
 }
@@ -189,8 +188,7 @@ __global__ __launch_bounds__(kVecThreads, LV == 1 ? 8 : 1) void k_pcg_update(T *
 }
 
 // after an iteration: the new r.z and r.r, convergence
-__device__ __forceinline__ void pcg_store(PcgScalars *sc, double rz, double rr, double beta) {
-  sc->beta = beta;
+__device__ __forceinline__ void pcg_store(PcgScalars *sc, double rz, double rr) {
   sc->rz2 = rz;
   sc->rr = rr;
   sc->iters += 1;
@@ -200,13 +198,6 @@ __device__ __forceinline__ void pcg_store(PcgScalars *sc, double rz, double rr, 
   } else if (rr <= sc->tol2) {
     sc->done = 1;
   }
-}
-
-__global__ __launch_bounds__(kVecThreads) void k_fin_rz(const double *partial, int np, PcgScalars *sc) {
-  if (sc->done) return;
-  double s[2];
-  final_sums<2>(partial, np, s);
-  if (threadIdx.x == 0) pcg_store(sc, s[0], s[1], s[0] / sc->rz);
 }
 
 template <typename T>
@@ -222,9 +213,9 @@ struct Vec16<float> {
   static constexpr int W = 4;
 };
 
-// p = dinv r + beta p, in 16-byte chunks (all three are allocations of the library).  np > 0: beta
-// from the np partials of (r.z, r.r), which every block sums and the first one stores with the
-// convergence test (a late block that already sees `done` leaves p, which is not used any more).
+// p = dinv r + beta p, in 16-byte chunks (all three are allocations of the library), beta from the np
+// partials of (r.z, r.r), which every block sums and the first one stores with the convergence test (a
+// late block that already sees `done` leaves p, which is not used any more).
 template <typename T>
 __global__ __launch_bounds__(kVecThreads) void k_pcg_dir(T *p, const T *r, const T *dinv, int64_t n_v,
                                                          PcgScalars *sc, const double *partial, int np) {
@@ -233,7 +224,7 @@ __global__ __launch_bounds__(kVecThreads) void k_pcg_dir(T *p, const T *r, const
   const int64_t nvec = n_v / W;
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   const int dn = sc->done;
-  const double rz = sc->rz, beta0 = sc->beta;
+  const double rz = sc->rz;
   const PartialLoads<2> sums(partial, np);
   int64_t c = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   V pv{}, rv{}, dv{};
@@ -243,17 +234,10 @@ __global__ __launch_bounds__(kVecThreads) void k_pcg_dir(T *p, const T *r, const
     dv = reinterpret_cast<const V *>(dinv)[c];
   }
   asm volatile("" ::: "memory");   // the first loads stay ahead of the test
-  double beta;
-  if (np > 0) {
-    double s[2];
-    if (sums.sums(s, dn != 0)) return;
-    beta = s[0] / rz;
-    if (blockIdx.x == 0 && threadIdx.x == 0) pcg_store(sc, s[0], s[1], beta);
-  } else {
-    if (dn) return;
-    beta = beta0;
-  }
-  const T b = (T)beta;
+  double s[2];
+  if (sums.sums(s, dn != 0)) return;
+  if (blockIdx.x == 0 && threadIdx.x == 0) pcg_store(sc, s[0], s[1]);
+  const T b = (T)(s[0] / rz);
   for (; c < nvec; c += stride) {
     const int64_t c2 = c + stride;
     V p2{}, r2{}, d2{};
@@ -400,10 +384,9 @@ hipError_t launch_pcg_iteration(const Ctx &c, T *x, T *r, T *p, const T *q, cons
   with_levels(nlv, [&](auto lv) {
     k_pcg_update<lv(), T><<<nb, kVecThreads, 0, s>>>(x, r, p, apply_result<T>(c, q), dinv, c.n_s, rz, sc, partial, np);
   });
-  const bool fin = nb <= kFinPartials;
-  if (!fin) k_fin_rz<<<1, kVecThreads, 0, s>>>(rz, nb, sc);
+  static_assert(kVecBlocks <= kFinPartials && kNodeBlocks <= kFinPartials, "k_pcg_dir sums the update's partials");
   const int nd = (int)std::min<int64_t>((c.n_v / Vec16<T>::W + kVecThreads) / kVecThreads, kVecBlocks);
-  k_pcg_dir<T><<<nd, kVecThreads, 0, s>>>(p, r, dinv, c.n_v, sc, rz, fin ? nb : 0);
+  k_pcg_dir<T><<<nd, kVecThreads, 0, s>>>(p, r, dinv, c.n_v, sc, rz, nb);
   return hipGetLastError();
 }
 template hipError_t launch_pcg_iteration<double>(const Ctx &, double *, double *, double *, const double *,

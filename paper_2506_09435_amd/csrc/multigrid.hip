@@ -143,7 +143,8 @@ __global__ __launch_bounds__(256) void k_mg_surf(const double *__restrict__ Hf, 
 // horizontal node) loads its fine line (owner columns only; the shared layer level counts in the
 // upper layer) and contracts it vertically in registers; the horizontal contraction is split in
 // two LDS stages over all threads of the column: (a, j, c) sums over i, then (a, b, c) over j.
-// q_f comes straight from the apply's first pass and is assembled here.  blockIdx.y takes a chunk of
+// On slices q_f comes straight from the apply's first pass and is assembled here (in 3D the apply that
+// leaves slots restricts by itself, and this kernel gets complete vectors).  blockIdx.y takes a chunk of
 // lpc layers.  Coarse nodes owned by the column go to b_c, the others to the coarse face slots, and
 // a chunk's top level below the next chunk behind them (deferred.h: the coarse level's first kernel
 // adds them); the coarse surface level is set to zero.  The vertical carry of the
@@ -177,7 +178,8 @@ __global__ __launch_bounds__(256) void k_restrict(const T *__restrict__ rf, Defe
   const bool own = active && (flags_f[col * NHF + t] & kOwned);
   const int chunk = blockIdx.y, nchunk = gridDim.y, l0 = chunk * lpc, l1 = min(l0 + lpc, nz);
   int4 sl = make_int4(-1, -1, -1, 0);
-  if (own && hn < qf.n_hi) sl = qf.slots[hn];
+  if constexpr (DIM == 2)
+    if (own && hn < qf.n_hi) sl = qf.slots[hn];
   T *W = sW + lc * N1C * NHF;
   T *A = sA + lc * NA;
   T *Cr = sC + lc * 2 * NHC;
@@ -205,7 +207,7 @@ __global__ __launch_bounds__(256) void k_restrict(const T *__restrict__ rf, Defe
       const bool ld = own && k < kmax;
       nr[k] = ld ? rf[idx] : T(0);
       nq[k] = (ld && qf.y) ? qf.y[idx] : T(0);
-      nf[k] = (sl.x >= 0 && k < PF) ? qf.F[(int64_t)(l * PF + k) * qf.n_slots + sl.x] : T(0);
+      nf[k] = (DIM == 2 && sl.x >= 0 && k < PF) ? qf.F[(int64_t)(l * PF + k) * qf.n_slots + sl.x] : T(0);
     }
   };
   load_layer(l0);
@@ -213,25 +215,27 @@ __global__ __launch_bounds__(256) void k_restrict(const T *__restrict__ rf, Defe
     T rv[N1F];
 #pragma unroll
     for (int k = 0; k < N1F; ++k) rv[k] = nr[k] - (nq[k] + nf[k]);
-    // the rest of q: further face slots, and at the bottom of a chunk of the apply the lower chunk's value
-    auto more = [&](int s) {
-      const T *f = qf.F + (int64_t)(l * PF) * qf.n_slots + s;
+    if constexpr (DIM == 2) {
+      // the rest of q: further face slots, and at the bottom of a chunk of the apply the lower chunk's value
+      auto more = [&](int s) {
+        const T *f = qf.F + (int64_t)(l * PF) * qf.n_slots + s;
 #pragma unroll
-      for (int k = 0; k < PF; ++k) rv[k] -= f[k * qf.n_slots];
-    };
-    if (sl.y >= 0) more(sl.y);
-    if (sl.z >= 0) more(sl.z);
-    if (sl.w > 0)
-      for (int q = 1; q <= qf.lists[sl.w]; ++q) more(qf.lists[sl.w + q]);
-    if (qf.nchunk > 1 && l > 0 && (l * PF) % qf.clev == 0 && own) {
-      const int c = l * PF / qf.clev - 1;
-      const T *top = qf.F + (int64_t)(qf.nlev + c) * qf.n_slots;
-      T z = (qf.F + (int64_t)(qf.nlev + qf.nchunk - 1) * qf.n_slots)[c * ns_f + hn];
-      if (sl.x >= 0) z += top[sl.x];
-      if (sl.y >= 0) z += top[sl.y];
-      if (sl.z >= 0) z += top[sl.z];
-      if (sl.w > 0) z = list_sum(qf, top, sl.w, z);
-      rv[0] -= z;
+        for (int k = 0; k < PF; ++k) rv[k] -= f[k * qf.n_slots];
+      };
+      if (sl.y >= 0) more(sl.y);
+      if (sl.z >= 0) more(sl.z);
+      if (sl.w > 0)
+        for (int q = 1; q <= qf.lists[sl.w]; ++q) more(qf.lists[sl.w + q]);
+      if (qf.nchunk > 1 && l > 0 && (l * PF) % qf.clev == 0 && own) {
+        const int c = l * PF / qf.clev - 1;
+        const T *top = qf.F + (int64_t)(qf.nlev + c) * qf.n_slots;
+        T z = (qf.F + (int64_t)(qf.nlev + qf.nchunk - 1) * qf.n_slots)[c * ns_f + hn];
+        if (sl.x >= 0) z += top[sl.x];
+        if (sl.y >= 0) z += top[sl.y];
+        if (sl.z >= 0) z += top[sl.z];
+        if (sl.w > 0) z = list_sum(qf, top, sl.w, z);
+        rv[0] -= z;
+      }
     }
     if (l + 1 < l1) load_layer(l + 1);
     T w[N1C];
@@ -706,10 +710,8 @@ __global__ __launch_bounds__(kVecThreads) void k_dot(const T *a, const T *b, int
   block_partials<1>(v, partial);
 }
 
-// beta = (r.z)_new / (r.z)_old (first: beta = 0); a non-positive r.z means the preconditioner
-// is not positive definite on this residual
-__device__ __forceinline__ void cg_store_rz(PcgScalars *sc, double rz, double beta) {
-  sc->beta = beta;
+// a non-positive r.z means the preconditioner is not positive definite on this residual
+__device__ __forceinline__ void cg_store_rz(PcgScalars *sc, double rz) {
   sc->rz2 = rz;
   if (!(rz > 0.0) || !(rz <= 1e300)) {
     sc->breakdown = (rz == rz) ? 1 : 2;
@@ -717,21 +719,13 @@ __device__ __forceinline__ void cg_store_rz(PcgScalars *sc, double rz, double be
   }
 }
 
-__global__ __launch_bounds__(kVecThreads) void k_mg_fin_rz(const double *partial, int np, PcgScalars *sc,
-                                                           int first) {
-  if (sc->done) return;
-  double s[1];
-  final_sums<1>(partial, np, s);
-  if (threadIdx.x == 0) cg_store_rz(sc, s[0], first ? 0.0 : s[0] / sc->rz);
-}
-
-// p = z + beta p.  np > 0: beta from the np partials of r.z (every block sums them; the first one
-// stores what the next kernels read), else as k_mg_fin_rz left it.
+// p = z + beta p, beta = (r.z)_new / (r.z)_old (first: 0) from the np partials of r.z (every block sums them; the first one stores what
+// the next kernels read).
 template <typename T>
 __global__ __launch_bounds__(kVecThreads) void k_mg_dir(T *p, const T *z, int64_t n, PcgScalars *sc, int first,
                                                         const double *partial, int np) {
   const int dn = sc->done;
-  const double rz = sc->rz, beta0 = sc->beta;
+  const double rz = sc->rz;
   const PartialLoads<1> pv(partial, np);
   int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   T z0 = T(0), p0 = T(0);
@@ -740,17 +734,10 @@ __global__ __launch_bounds__(kVecThreads) void k_mg_dir(T *p, const T *z, int64_
     if (!first) p0 = p[i];
   }
   asm volatile("" ::: "memory");   // the first loads stay ahead of the test
-  double beta;
-  if (np > 0) {
-    double s[1];
-    if (pv.sums(s, dn != 0)) return;
-    beta = first ? 0.0 : s[0] / rz;
-    if (blockIdx.x == 0 && threadIdx.x == 0) cg_store_rz(sc, s[0], beta);
-  } else {
-    if (dn) return;
-    beta = beta0;
-  }
-  const T b = (T)beta;
+  double s[1];
+  if (pv.sums(s, dn != 0)) return;
+  if (blockIdx.x == 0 && threadIdx.x == 0) cg_store_rz(sc, s[0]);
+  const T b = first ? T(0) : (T)(s[0] / rz);
   const int64_t st = (int64_t)gridDim.x * blockDim.x;
   for (; i < n; i += st) {
     const int64_t i2 = i + st;
@@ -1718,9 +1705,8 @@ static hipError_t mg_dot_dir_impl(Ctx &c, const T *r, const T *z, T *p, double *
   const int nf = (int)std::min<int64_t>((c.n_v + kVecThreads - 1) / kVecThreads, kVB<T>);
   const int np = have_partials ? partial_blocks<T>(c) : nf;
   if (!have_partials) k_dot<T><<<nf, kVecThreads, 0, s>>>(r, z, c.n_v, partial, sc);
-  const bool fin = np <= kFinPartials;
-  if (!fin) k_mg_fin_rz<<<1, kVecThreads, 0, s>>>(partial, np, sc, first);
-  k_mg_dir<T><<<nf, kVecThreads, 0, s>>>(p, z, c.n_v, sc, first, partial, fin ? np : 0);
+  static_assert(kVB<T> <= kFinPartials && kNodeBlocks <= kFinPartials, "k_mg_dir sums the partials");
+  k_mg_dir<T><<<nf, kVecThreads, 0, s>>>(p, z, c.n_v, sc, first, partial, np);
   return hipGetLastError();
 }
 
