@@ -7,6 +7,7 @@
 #include <cstdio>
 #include <cstring>
 #include <exception>
+#include <mutex>
 #include <new>
 #include <string>
 #include <vector>
@@ -681,13 +682,18 @@ static fnpf_status create_context(const fnpf_mesh_desc *m, Ctx &c) {
     return err == hipErrorOutOfMemory ? FNPF_ERR_ALLOC : FNPF_ERR_HIP;
   };
   if (he != hipSuccess) return bad(he);
-  static bool uploaded[64] = {false};
-  if (c.device >= 0 && c.device < 64 && !uploaded[c.device]) {
-    he = upload_constants(c.device);
-    if (he != hipSuccess) return bad(he);
-    he = init_noalloc_scratch(c.device);
-    if (he != hipSuccess) return bad(he);
-    uploaded[c.device] = true;
+  {
+    // contexts may be created by several threads at once: the tables are built in static memory
+    static std::mutex first_use;
+    static bool uploaded[64] = {false};
+    const std::lock_guard<std::mutex> lock(first_use);
+    if (c.device >= 0 && c.device < 64 && !uploaded[c.device]) {
+      he = upload_constants(c.device);
+      if (he != hipSuccess) return bad(he);
+      he = init_noalloc_scratch(c.device);
+      if (he != hipSuccess) return bad(he);
+      uploaded[c.device] = true;
+    }
   }
   const int nsides = 2 * (c.dim - 1);
   std::vector<int32_t> tags((size_t)c.n_eh * nsides, 0);

@@ -23,6 +23,7 @@
 #include <cstdint>
 #include <cstring>
 #include <exception>
+#include <mutex>
 #include <utility>
 #include <vector>
 
@@ -1457,10 +1458,15 @@ hipError_t estimate_lambda(Ctx &c, Ctx &L, T *v, T *q, T *w1, T *w2, bool warm, 
 
 // Builds the coarse levels (contexts at degrees p/2, p/4, ..., 1) and their work vectors.
 static fnpf_status build_levels(Ctx &c) {
-  static bool uploaded[64] = {false};
-  if (c.device >= 0 && c.device < 64 && !uploaded[c.device]) {
-    if (upload_tables() != hipSuccess) return FNPF_ERR_HIP;
-    uploaded[c.device] = true;
+  {
+    // contexts of several threads may come here at once: the tables are built in static memory
+    static std::mutex first_use;
+    static bool uploaded[64] = {false};
+    const std::lock_guard<std::mutex> lock(first_use);
+    if (c.device >= 0 && c.device < 64 && !uploaded[c.device]) {
+      if (upload_tables() != hipSuccess) return FNPF_ERR_HIP;
+      uploaded[c.device] = true;
+    }
   }
   Ctx *F = &c;
   while (F->p > 1) {
