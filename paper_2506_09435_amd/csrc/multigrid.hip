@@ -1504,7 +1504,8 @@ static fnpf_status build_levels(Ctx &c) {
     c.mg.push_back(L);
     F = c.mg.back().c;
   }
-  if (!c.mg.empty() && (size_t)27 * c.mg.back().c->n_v * sizeof(float) <= kP1MaxBytes) {
+  // (its kernels have a level a block in the grid's y and z, which HIP limits to 65,536)
+  if (!c.mg.empty() && (size_t)27 * c.mg.back().c->n_v * sizeof(float) <= kP1MaxBytes && c.nz + 1 <= 65535) {
     const fnpf_status st = p1_build(*c.mg.back().c);
     if (st != FNPF_OK && st != FNPF_ERR_ARG) return st;   // ARG: a node with too many neighbours stays matrix-free
   }
