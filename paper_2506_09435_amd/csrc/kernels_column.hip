@@ -1155,7 +1155,7 @@ __global__ __launch_bounds__(256) void k_apply_lines(const T *__restrict__ x, T 
 // interface each, the nodes without slots.
 constexpr int kFaceLevels = 8;
 
-template <typename T, bool MASK>
+template <typename T, bool MASK, bool SPLIT>
 __global__ __launch_bounds__(256) void k_apply_faces(T *__restrict__ y, const T *__restrict__ F,
                                                      const int32_t *__restrict__ ps_node,
                                                      const int32_t *__restrict__ ps_ptr,
@@ -1166,7 +1166,7 @@ __global__ __launch_bounds__(256) void k_apply_faces(T *__restrict__ y, const T 
   if (skip != nullptr && *skip) return;
   constexpr int LC = kFaceLevels;
   const T *Z = F + (int64_t)(nlev + nchunk - 1) * n_slots;
-  if ((int)blockIdx.x >= nba) {
+  if (SPLIT && (int)blockIdx.x >= nba) {
     const int nbx = (int)((n_s + 255) >> 8);
     const int c = ((int)blockIdx.x - nba) / nbx;
     const int64_t n = (int64_t)(((int)blockIdx.x - nba) - c * nbx) * 256 + threadIdx.x;
@@ -1188,8 +1188,8 @@ __global__ __launch_bounds__(256) void k_apply_faces(T *__restrict__ y, const T 
   const int a = ps_ptr[k], b = ps_ptr[k + 1];
   // chunk below the interface at level v, -1 at other levels
   auto below = [&](int v) {
-    const int c = v / clev - 1;
-    return nchunk > 1 && v > 0 && v < nlev - 1 && v == (c + 1) * clev ? c : -1;
+    const int c = SPLIT ? v / clev - 1 : -1;
+    return SPLIT && v > 0 && v < nlev - 1 && v == (c + 1) * clev ? c : -1;
   };
   T acc[LC];
 #pragma unroll
@@ -1273,7 +1273,8 @@ static hipError_t faces_impl(Ctx &c, T *y, const T *F, bool mask, const int32_t 
   const int nba = face_blocks_n(c, n);
   const int nb = nba + (nchunk - 1) * (int)((c.n_s + 255) / 256);
   if (nb == 0) return hipSuccess;
-  auto kern = mask ? k_apply_faces<T, true> : k_apply_faces<T, false>;
+  auto kern = nchunk > 1 ? (mask ? k_apply_faces<T, true, true> : k_apply_faces<T, false, true>)
+                         : (mask ? k_apply_faces<T, true, false> : k_apply_faces<T, false, false>);
   kern<<<nb, 256, 0, s>>>(y, F, node, ptr, slot, n, c.p * c.nz + 1, c.n_s, n_slots, nba, slots, n_hi, c.lpc * c.p,
                           nchunk, skip);
   return hipGetLastError();
