@@ -38,9 +38,9 @@ METRIC = "GDOF/s Laplace apply; s per RK4 step, FP64 vs mixed @1e-8; adjoint/for
 # HBM bytes of one C5 FP64 apply from rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE (scaled by what the
 # counters read for kernels of known size), valid only for the kernel source they were taken from.
 MEASURED_TRAFFIC = {
-    "kernel_source_sha256": "0af795b56925b751cd576a6c4efbed7b396ccda5673541e3eceb13f25e35a3a2",
-    "fetch_bytes_per_apply": 799834965,
-    "write_bytes_per_apply": 518372418,
+    "kernel_source_sha256": "a5cf479b37e0ccc4fd3cfb2dbf8c3454c812417d8725160634e7f9aa8481d073",
+    "fetch_bytes_per_apply": 802029594,
+    "write_bytes_per_apply": 518346812,
 }
 
 

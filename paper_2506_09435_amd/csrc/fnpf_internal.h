@@ -221,8 +221,8 @@ struct Ctx {
   double *d_sigma = nullptr;              // [p nz + 1]
   double *d_layer_s = nullptr;            // [nz + 1]
   double *d_mlump_s = nullptr;            // [n_s] sum_e w_i w_j det J_h (surface mass)
-  // apply variant: 0 fused geometry (factors recomputed in registers), 1 stored factors,
-  // 2 fused geometry, unrolled schedule; the schedule of 0 is refined by the fields below
+  // apply variant: 0 fused geometry (factors recomputed in registers), 1 stored factors; the
+  // schedule of 0 is refined by the fields below
   int apply_variant = 0;
   bool apply_lines = false;               // 3D fused apply with the xi/eta line schedule
   bool apply_owner = false;               // owner-computes assembly (3D: of the line schedule; 2D: of columns)
@@ -262,7 +262,7 @@ struct Ctx {
   std::vector<int32_t> h_gslot, h_gx_ptr, h_gx_slot;
   int64_t n_gslots = 0;
   int32_t *d_gslot = nullptr, *d_gx_ptr = nullptr, *d_gx_slot = nullptr;
-  double *d_F64 = nullptr;                // [p nz + 1][largest of n_slots, n_tslots, n_gslots]
+  double *d_F64 = nullptr;                // [n_F]: face slots of the apply, the geometry or the restriction
   float *d_F32 = nullptr;
   double *d_cg64 = nullptr;               // [5|3][n_eh*nh] H, H_xi, h_xi, (H_eta, h_eta) per column node
   float *d_cg32 = nullptr;
@@ -279,8 +279,6 @@ struct Ctx {
   bool keep_diag = false;                 // store it at every geometry update (line smoothing reads it)
   double *d_dinv = nullptr;
   float *d_dinv32 = nullptr;
-  const double *geom_eta = nullptr;       // eta/h of the last fnpf_geom (caller-owned, used by w recovery)
-  const double *geom_h = nullptr;
   bool have_geom = false;
   bool have_geom32 = false;
   bool want32 = false;

@@ -8,11 +8,16 @@
 // shared by two stacked layers is carried in a register, so each thread
 // writes every volume node of its line exactly once.
 //
-// Assembly across columns uses a colouring of the columns (columns of one
-// colour share no horizontal node), one launch per colour, no atomics: the
-// first colour that touches a horizontal node stores, later colours
-// read-add-store, and the last one sees the assembled value (used for fused
-// dot products, w recovery and the RK4 update).
+// Assembly across columns, without atomics, in one of two ways.  Owner-computes
+// (the default apply, the 3D geometry, the surface right-hand sides and VJPs):
+// one launch over all columns, in which a column (or the tile of a workgroup's
+// columns) stores the nodes it owns and leaves its other contributions in face
+// slots, which a second kernel or the next reader adds.  Colours (the other
+// apply variants, 2D geometry, Neumann load, line bands, modal filter, and calls
+// that may not use the slots): one launch per colour of a colouring in which
+// columns of one colour share no horizontal node; the first colour that touches
+// a node stores, later ones read-add-store, and the last one sees the assembled
+// value (used for fused dot products).  The w recovery needs no assembly.
 //
 // Notation: D is the GLL derivative matrix, W the GLL weights, G the six
 // (3D) or three (2D) symmetric per-point factors w_q det(J) (J^-1 J^-T)_ab of
@@ -763,7 +768,9 @@ __global__ __launch_bounds__(256) void k_apply_fused2(const T *__restrict__ x, T
 // multigrid.hip's k_restrict leaves them.  A x never goes to memory, and the exchange and its barrier
 // fall away.  On the sea of 256 x 128 x 6 elements, p = 6, FP32:
 // 195 us, where the apply took 112 and the restriction 137; wave of 40 x 40 x 4, p = 5, FP64: 14.3 us
-// for 11.0 and 8.4.  (Its xi and eta contractions as register lines, operands uniform over the wave but
+// for 11.0 and 8.4.  Its LDS, the line arrays and CPB (NA + 2 NHC) words instead of the exchange, holds
+// four blocks a CU in FP64 as the plain apply's does, but three at degree 4 (42.6 KB): the chunks of small
+// meshes are counted for four.  (Its xi and eta contractions as register lines, operands uniform over the wave but
 // half the lanes idle: 229 and 16.9 us.)
 template <typename T>
 struct RestrictArgs {

@@ -1,7 +1,8 @@
 // partials.h - capacity of a context's buffer of per-block partial sums (host logic only).
 //
 // Every reduction in the library is deterministic: each block of a launch writes its sums to
-// partial[block * sums + k] and a one-block kernel adds them in block order.  One buffer per
+// partial[block * sums + k], and they are added in a fixed order by a one-block kernel or by every
+// block of the kernel that needs the sum (reduce.h).  One buffer per
 // context serves all such launches, so it must hold the largest blocks x sums of any of them.
 // partial_uses lists every kind of launch that writes partials, partial_capacity is the size
 // that holds them all, and partials_fit is the check made before each launch.
@@ -22,7 +23,7 @@ struct PartialUse {
 };
 
 // colour_blocks: blocks of the colour-scheduled apply summed over its colours (one partial each);
-// owner_blocks: blocks of both passes of the owner-computes apply (one partial each).
+// owner_blocks: blocks of the owner-computes apply's first pass, which has one partial each.
 inline std::vector<PartialUse> partial_uses(int64_t colour_blocks, int64_t owner_blocks) {
   const int64_t v64 = kPartialVecBlocks, v32 = 2 * kPartialVecBlocks;
   return {

@@ -478,7 +478,8 @@ std::string build_host_mesh(const fnpf_mesh_desc &m, Ctx &c, std::vector<double>
         c.h_tps_ptr.push_back((int32_t)c.h_tps_slot.size());
       }
       c.n_tps = (int)c.h_tps_node.size();
-      // the owner tile's representative takes the dot product of nodes without face slots
+      // an owned node that other tiles (or columns without an exchange entry) contribute to: the geometry
+      // leaves its tile's value in the face layout and the inverses to the face pass
       for (int64_t o = 0; o < n_eh * nh; ++o)
         if ((flags[o] & kTOwn) && slot_of_node[m.eh_nodes[o]] >= 0) flags[o] |= kTShared;
       // The geometry's face layout: the same contributions, placed by the position k of their
