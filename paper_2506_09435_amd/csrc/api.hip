@@ -101,8 +101,6 @@ void free_all(Ctx &c) {
   dfree(c.d_p_lists);
   dfree(c.d_F64);
   dfree(c.d_F32);
-  dfree(c.d_aF64);
-  dfree(c.d_aF32);
   dfree(c.d_tslot);
   dfree(c.d_xch);
   dfree(c.d_tps_node);
@@ -199,6 +197,13 @@ hipError_t upload_cast(float **d, const std::vector<T> &h) {
   return upload(d, f.data(), f.size());
 }
 
+// elements behind d_F64's (d_F32's) n_F: the public slice apply's own slots (fixed for the default schedule,
+// whichever is set)
+size_t slice_slots(const Ctx &c) {
+  const size_t n = face_buffer_elements(c, c.n_tslots);
+  return c.dim == 2 && n * sizeof(double) <= noalloc_scratch_bytes() ? n : 0;
+}
+
 fnpf_status ensure32(Ctx &c) {
   if (c.want32) return FNPF_OK;
   HIPCHK(dalloc(&c.d_cg32, (size_t)c.ncg * c.n_eh * c.nh));
@@ -211,8 +216,8 @@ fnpf_status ensure32(Ctx &c) {
   HIPCHK(dalloc(&c.d_p32, c.n_v));
   HIPCHK(dalloc(&c.d_q32, c.n_v));
   HIPCHK(dalloc(&c.d_d32, c.n_v));
-  HIPCHK(dalloc(&c.d_F32, c.n_F));
-  if (c.d_aF64) HIPCHK(dalloc(&c.d_aF32, face_buffer_elements(c, c.n_tslots)));
+  HIPCHK(dalloc(&c.d_F32, c.n_F + slice_slots(c)));
+  if (slice_slots(c) > 0) c.d_aF32 = c.d_F32 + c.n_F;
   c.want32 = true;
   c.have_geom32 = false;
   return FNPF_OK;
@@ -745,7 +750,8 @@ static fnpf_status create_context(const fnpf_mesh_desc *m, Ctx &c) {
     // at most this level's)
     c.n_F = std::max({face_buffer_elements(c, c.n_tslots), (size_t)(c.p * c.nz + 1) * (size_t)c.n_gslots,
                       face_buffer_elements(c, c.n_slots), (size_t)1});
-    AL(c.d_F64, c.n_F);
+    AL(c.d_F64, c.n_F + slice_slots(c));
+    if (slice_slots(c) > 0) c.d_aF64 = c.d_F64 + c.n_F;
     // the lists may be empty (a mesh within one tile): upload one unused entry then
     if (c.h_tps_node.empty()) c.h_tps_node.push_back(0);
     if (c.h_tps_slot.empty()) c.h_tps_slot.push_back(0);
@@ -790,7 +796,6 @@ static fnpf_status create_context(const fnpf_mesh_desc *m, Ctx &c) {
   AL(c.d_geoh, c.n_s);
   AL(c.d_sk, 2 * c.n_s);
   AL(c.d_sF, kSlotRows * std::max<int64_t>(c.n_slots, 1));
-  if (c.dim == 2 && owner_apply_active(c)) AL(c.d_aF64, face_buffer_elements(c, c.n_tslots));
   {
     const auto uses = partial_uses(c.max_colour_blocks, owner_apply_blocks(c));
     c.n_partial = (int)partial_capacity(uses);

@@ -253,7 +253,7 @@ struct Ctx {
   int32_t *d_t_lists = nullptr;
   int64_t t_n_hi = 0;
   int lpc = 1;                            // layers per block of the owner-computes apply
-  size_t n_F = 0;                         // elements of d_F64 (and d_F32)
+  size_t n_F = 0;                         // elements of d_F64 (and d_F32), the public slice apply's apart
   int16_t *d_xch = nullptr;
   // the geometry's face layout (k_geom, k_diag_faces): per column node its place in a level row
   // of n_gslots entries (-1 none): the owner tile's value at a node with slots at k (its position
@@ -292,7 +292,7 @@ struct Ctx {
   double *d_w = nullptr;                  // recovered w at the surface
   double *d_geoH = nullptr, *d_geoh = nullptr;    // eta + h and h of the last fnpf_geom
   double *d_sk = nullptr;   // [2][n_s] surface right-hand sides, owned contributions
-  double *d_aF64 = nullptr; // slices: face slots of the public apply, apart from the solves'
+  double *d_aF64 = nullptr; // slices: face slots of the public apply, behind the solves' in one allocation
   float *d_aF32 = nullptr;
   double *d_sF = nullptr;   // [kSlotRows][n_slots] face slots of the surface kernels, rows of its own each
   hipStream_t slot_stream = nullptr;       // slots_usable: the stream that has the slots
