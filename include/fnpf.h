@@ -42,7 +42,8 @@
  *     surface quadrature, fnpf_geom_vjp, fnpf_neumann_load, and on slices
  *     both forms of fnpf_laplace_apply.  (The first
  *     stream that makes such a call takes a shorter path; results differ
- *     between the paths by the order of the sums at shared nodes only.)
+ *     between the paths by the order of the sums at shared nodes only.  Let
+ *     its calls finish before it is destroyed: a new stream may get its handle.)
  */
 #ifndef FNPF_H
 #define FNPF_H

@@ -1228,6 +1228,8 @@ bool owner_apply_active(const Ctx &c) {
   return c.n_v * 8 < lim && (int64_t)(c.p * c.nz + 1) * std::max(c.n_slots, c.n_tslots) * 8 < lim;
 }
 
+// (A stream is known by its handle only.  One that was destroyed with calls under way could pass its handle
+// to a new stream that overlaps them; the header asks for them to finish first.)
 bool slots_usable(Ctx &c, hipStream_t s) {
   if (s == hipStreamPerThread) return false;   // one handle for the streams of all threads
   if (s != nullptr) {                          // (the null stream cannot be captured)
