@@ -51,11 +51,14 @@ fnpf_status caught(fnpf_ctx ctx);
     if (e__ != hipSuccess) return hipfail(&c, e__, #expr); \
   } while (0)
 
+// n elements in *p, unless it has them: what allocates on first use may have failed half way before
 template <typename T>
 hipError_t dalloc(T **p, size_t n) {
-  *p = nullptr;
+  if (*p != nullptr) return hipSuccess;
   if (n == 0) n = 1;
-  return hipMalloc((void **)p, n * sizeof(T));
+  const hipError_t e = hipMalloc((void **)p, n * sizeof(T));
+  if (e != hipSuccess) *p = nullptr;
+  return e;
 }
 
 template <typename T>
@@ -284,7 +287,7 @@ void history_advance(Ctx::History &H, double t, double dt, bool continues) {
 }
 
 fnpf_status ensure_flat(Ctx &c, hipStream_t s) {
-  if (c.d_flat) return FNPF_OK;
+  if (c.d_flat && c.d_scr_s) return FNPF_OK;
   HIPCHK(dalloc(&c.d_flat, c.n_s));
   HIPCHK(dalloc(&c.d_scr_s, c.n_s));
   HIPCHK(launch_fill(c.d_flat, 0.0, c.n_s, s));
@@ -1140,7 +1143,7 @@ fnpf_status fnpf_set_modal_filter(fnpf_ctx ctx, int32_t cutoff, double alpha, in
   if (!(alpha >= 0.0) || !std::isfinite(alpha)) return fail(&c, FNPF_ERR_ARG, "modal filter alpha must be >= 0");
   if (order < 1) return fail(&c, FNPF_ERR_ARG, "modal filter order must be >= 1");
   const int n1 = c.p + 1;
-  if (!c.d_filt_M) {
+  if (!c.d_filt_tmp) {   // the last of them
     std::vector<double> inv(c.n_s, 0.0);
     for (int32_t v : c.h_eh_nodes) inv[v] += 1.0;
     for (auto &x : inv) x = 1.0 / x;

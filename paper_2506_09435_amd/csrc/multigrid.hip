@@ -885,9 +885,13 @@ struct Prec<float> {
   static bool &evokf(Ctx &c) { return c.mg_ev_ok32; }
 };
 
+// n elements in *p, unless it has them (an earlier call may have failed half way)
 template <typename T>
 hipError_t dalloc_t(T **p, size_t n) {
-  return hipMalloc((void **)p, n * sizeof(T));
+  if (*p != nullptr) return hipSuccess;
+  const hipError_t e = hipMalloc((void **)p, n * sizeof(T));
+  if (e != hipSuccess) *p = nullptr;
+  return e;
 }
 
 #define MG_DISPATCH(DIMV, PV, CALL)                    \
@@ -1580,8 +1584,7 @@ template <typename T>
 fnpf_status mg_refresh(Ctx &c, hipStream_t s) {
   fnpf_status st = mg_build(c);
   if (st != FNPF_OK) return st;
-  const bool fresh = Prec<T>::fv(c)[0] == nullptr;
-  if (fresh) {
+  {
     T **fv = const_cast<T **>(Prec<T>::fv(c));
     for (int k = 0; k < 4; ++k)
       if (dalloc_t(&fv[k], c.n_v) != hipSuccess) return FNPF_ERR_ALLOC;
